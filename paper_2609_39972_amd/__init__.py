@@ -38,7 +38,7 @@ STATUS = {0: "UBT_OK", 1: "UBT_ERR_NULL", 2: "UBT_ERR_SHAPE", 3: "UBT_ERR_VALUE"
 
 # Every symbol include/ubt.h declares.
 EXPORTS = ("ubt_status_str", "ubt_abi_version", "ubt_last_hip_error", "ubt_topk",
-           "ubt_lm_head_topk_workspace_bytes", "ubt_lm_head_topk", "ubt_bigram_scores", "ubt_build_tree", "ubt_draft_tree", "ubt_draft_step_workspace_bytes",
+           "ubt_lm_head_topk_workspace_bytes", "ubt_lm_head_topk_full_workspace_bytes", "ubt_lm_head_topk", "ubt_bigram_scores", "ubt_build_tree", "ubt_draft_tree", "ubt_draft_step_workspace_bytes",
            "ubt_draft_step", "ubt_draft_step_noalloc", "ubt_edge_scores", "ubt_build_tree_best_first", "ubt_tree_mask", "ubt_tree_attention", "ubt_verify_accept", "ubt_commit_kv",
            "ubt_tree_kl_loss")
 
@@ -73,6 +73,8 @@ def lib() -> ctypes.CDLL:
         L.ubt_topk.argtypes = [_p, _i32, _i32, _i32, _i64, _i64, _i64, _i32, _p, _p, _p, _p, _p]
         L.ubt_lm_head_topk_workspace_bytes.argtypes = [_i32, _i32, _i64, _i32]
         L.ubt_lm_head_topk_workspace_bytes.restype = ctypes.c_size_t
+        L.ubt_lm_head_topk_full_workspace_bytes.argtypes = [_i32, _i32, _i64, _i32]
+        L.ubt_lm_head_topk_full_workspace_bytes.restype = ctypes.c_size_t
         L.ubt_lm_head_topk.argtypes = [_p, _p, _i32, _i32, _i64, _i32, _p, _p, _p, _p, _p, ctypes.c_size_t, _p]
         L.ubt_bigram_scores.argtypes = [_p, _p, _p, _i32, _i64, _i32, _p, _p, _p, _p, _p, _i32, _i32, _i32, _p, _p,
                                         _p]
@@ -163,7 +165,7 @@ def topk(logits: torch.Tensor, K: int, out: dict | None = None, with_logprob: bo
 def lm_head_workspace(M: int, d: int, V: int, K: int, device="cuda") -> torch.Tensor:
     """A workspace for :func:`lm_head_topk` (uint8, 256-byte aligned; its contents are
     never read before they are written, so it serves calls of any shape in turn)."""
-    n = lib().ubt_lm_head_topk_workspace_bytes(M, d, V, K)
+    n = lib().ubt_lm_head_topk_full_workspace_bytes(M, d, V, K)
     if n == 0:
         raise ValueError("invalid shape for ubt_lm_head_topk")
     ws = torch.empty(n, dtype=torch.uint8, device=device)

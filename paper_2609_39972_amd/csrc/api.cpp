@@ -114,6 +114,13 @@ size_t ubt_lm_head_topk_workspace_bytes(int M, int d, int64_t V, int K) {
   return ubt::lm_head_workspace_bytes(M, d, V, K);
 }
 
+size_t ubt_lm_head_topk_full_workspace_bytes(int M, int d, int64_t V, int K) {
+  const size_t need = ubt_lm_head_topk_workspace_bytes(M, d, V, K);
+  if (need == 0) return 0;
+  const size_t gemm = ubt::lm_gemm_workspace_bytes(M, d, V, K);
+  return gemm > need ? gemm : need;
+}
+
 ubt_status_t ubt_lm_head_topk(const void* h, const void* w_lm, int M, int d, int64_t V, int K, int32_t* cand_ids,
                               float* cand_logit, float* cand_logprob, float* lse, void* workspace, size_t ws_bytes,
                               hipStream_t stream) {
@@ -124,6 +131,11 @@ ubt_status_t ubt_lm_head_topk(const void* h, const void* w_lm, int M, int d, int
   const size_t need = ubt::lm_head_workspace_bytes(M, d, V, K);
   if (need == 0) return UBT_ERR_UNSUPPORTED;
   if (!workspace || ws_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return UBT_ERR_WORKSPACE;
+  // Several row groups and a full workspace: the matrix product (lmgemm.hip).
+  const size_t gemm = ubt::lm_gemm_workspace_bytes(M, d, V, K);
+  if (gemm != 0 && ws_bytes >= gemm)
+    return hip_status(ubt::launch_lm_gemm_topk(h, w_lm, M, d, V, K, cand_ids, cand_logit, cand_logprob, lse, workspace,
+                                               stream));
   return hip_status(ubt::launch_lm_head_topk(h, w_lm, M, d, V, K, cand_ids, cand_logit, cand_logprob, lse, workspace,
                                              stream));
 }

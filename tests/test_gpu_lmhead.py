@@ -130,3 +130,54 @@ def test_lm_head_workspace_reuse_across_shapes():
     for i, (M, d, V, K) in enumerate(cases):
         x = synth.lm_head_inputs(20 + i, M, d, V)
         parity.check_lm_head(_run(x["h"], x["w"], K, workspace=ws), x["h"], x["w"], K)
+
+
+@pytest.mark.parametrize("M,d,V,K", [
+    # One row block of every height (32 rows per step), d / 32 odd and even, one k stage and many
+    (32, 32, 700, 8), (48, 96, 4099, 64), (65, 128, 2000, 16), (128, 224, 4097, 10), (130, 64, 5003, 64),
+    (161, 320, 1000, 8), (193, 96, 3333, 4), (256, 256, 2049, 64),
+    # Two row blocks (the last rows of the second past M), several products per call
+    (257, 64, 3000, 8), (480, 160, 70001, 8), (530, 64, 5000, 64), (1030, 32, 300, 8),
+    # Ranges of several tiles per workgroup, the last tile of one to four 64-row passes
+    (17, 64, 151936, 8), (40, 64, 100003, 16), (20, 32, 262145, 4),
+])
+def test_lm_head_product_integer_inputs_exact(M, d, V, K):
+    """The matrix product of calls with more than 16 rows (full workspace): integer-valued
+    inputs, so every logit is exact in fp32 and ids, ties included, must match bit for bit.
+    The workspace starts out filled with a pattern: nothing in it is read unwritten."""
+    import paper_2609_39972_amd as ubt
+
+    print(f"lm_head product M={M} d={d} V={V} K={K}", flush=True)
+    hb, wb = _int_bits(M, d, V, seed=M * 1000 + d + V, lo=-3, hi=3)
+    ws = ubt.lm_head_workspace(M, d, V, K)
+    assert ws.numel() >= ubt.lib().ubt_lm_head_topk_workspace_bytes(M, d, V, K)
+    ws.fill_(0x7F)  # as fp32: 3.4e38, above every logit
+    parity.check_lm_head(_run(hb, wb, K, workspace=ws), hb, wb, K, exact=True)
+
+
+@pytest.mark.parametrize("K", [1, 64])
+def test_lm_head_product_all_logits_tied(K):
+    """h = 0 in some rows: all of the row's logits tie, far more than the select kernel ranks
+    in LDS; the lowest ids win."""
+    print(f"lm_head product ties K={K}", flush=True)
+    hb, wb = _int_bits(24, 64, 30011, seed=5)
+    hb[::2] = 0
+    parity.check_lm_head(_run(hb, wb, K), hb, wb, K, exact=True)
+
+
+def test_lm_head_product_and_row_groups_agree():
+    """A workspace of the plain query's size (smaller than the product needs here) keeps a call
+    with many rows on the row-group kernels; both routes give the same ids and values on
+    exact inputs."""
+    import torch
+
+    import paper_2609_39972_amd as ubt
+
+    print("lm_head product against row groups", flush=True)
+    hb, wb = _int_bits(40, 512, 30011, seed=6)
+    small = torch.empty(ubt.lib().ubt_lm_head_topk_workspace_bytes(40, 512, 30011, 16), dtype=torch.uint8, device="cuda")
+    assert small.numel() < ubt.lm_head_workspace(40, 512, 30011, 16).numel()
+    a, b = _run(hb, wb, 16, workspace=small), _run(hb, wb, 16)
+    for k in ("cand_ids", "cand_logit"):
+        np.testing.assert_array_equal(a[k], b[k])
+    np.testing.assert_allclose(a["lse"], b["lse"], rtol=1e-6)
