@@ -432,6 +432,20 @@ ubt_status_t ubt_tree_attention(const void* q, const void* k_cache, const void* 
                                 int B, int N, int H, int H_kv, int D, float scale, void* out,
                                 ubt_dtype_t out_dt, float* lse, hipStream_t stream);
 
+/* ubt_tree_attention_split -- the same call with a workspace (256-byte aligned device
+ * memory, contents never read before they are written; calls that share it must not
+ * overlap).  With at least ubt_tree_attention_workspace_bytes(...) bytes (0: the shape has
+ * nothing to gain) the keys of a (sequence, head) are cut into parts that run on their own
+ * compute units, and a second kernel combines them in a fixed order; with NULL or less it
+ * is ubt_tree_attention.  The two agree within the rounding of the weights to bf16 (each
+ * part rounds relative to its own running maximum).  UBT_ERR_WORKSPACE: misaligned. */
+size_t ubt_tree_attention_workspace_bytes(int B, int N, int H, int H_kv, int D, int64_t P_max);
+ubt_status_t ubt_tree_attention_split(const void* q, const void* k_cache, const void* v_cache,
+                                      const int32_t* prefix_len, int64_t P_max, const void* k_tree,
+                                      const void* v_tree, const uint32_t* mask, const int32_t* n_nodes, int B, int N,
+                                      int H, int H_kv, int D, float scale, void* out, ubt_dtype_t out_dt, float* lse,
+                                      void* workspace, size_t ws_bytes, hipStream_t stream);
+
 /* ------------------------------------------------------------------------------------
  * ubt_verify_accept -- the acceptance walk.  Appendix A / Verification via
  * Tree-attention: from the root, follow the child whose token equals the target model's

@@ -39,7 +39,7 @@ STATUS = {0: "UBT_OK", 1: "UBT_ERR_NULL", 2: "UBT_ERR_SHAPE", 3: "UBT_ERR_VALUE"
 # Every symbol include/ubt.h declares.
 EXPORTS = ("ubt_status_str", "ubt_abi_version", "ubt_last_hip_error", "ubt_topk",
            "ubt_lm_head_topk_workspace_bytes", "ubt_lm_head_topk_full_workspace_bytes", "ubt_lm_head_topk", "ubt_bigram_scores", "ubt_build_tree", "ubt_draft_tree", "ubt_draft_step_workspace_bytes",
-           "ubt_draft_step", "ubt_draft_step_noalloc", "ubt_edge_scores", "ubt_build_tree_best_first", "ubt_tree_mask", "ubt_tree_attention", "ubt_verify_accept", "ubt_commit_kv",
+           "ubt_draft_step", "ubt_draft_step_noalloc", "ubt_edge_scores", "ubt_build_tree_best_first", "ubt_tree_mask", "ubt_tree_attention", "ubt_tree_attention_split", "ubt_tree_attention_workspace_bytes", "ubt_verify_accept", "ubt_commit_kv",
            "ubt_tree_kl_loss")
 
 _p = ctypes.c_void_p
@@ -96,12 +96,15 @@ def lib() -> ctypes.CDLL:
                                                 _p]
         L.ubt_tree_attention.argtypes = [_p, _p, _p, _p, _i64, _p, _p, _p, _p, _i32, _i32, _i32, _i32, _i32, _f32,
                                          _p, _i32, _p, _p]
+        L.ubt_tree_attention_split.argtypes = [*L.ubt_tree_attention.argtypes[:-1], _p, ctypes.c_size_t, _p]
+        L.ubt_tree_attention_workspace_bytes.argtypes = [_i32, _i32, _i32, _i32, _i32, _i64]
+        L.ubt_tree_attention_workspace_bytes.restype = ctypes.c_size_t
         L.ubt_verify_accept.argtypes = [_p, _p, _p, _p, _i32, _i32, _p, _p, _p, _p]
         L.ubt_commit_kv.argtypes = [_p, _p, _p, _p, _p, _p, _p, _i32, _i32, _i32, _i32, _i64, _p]
         L.ubt_tree_kl_loss.argtypes = [_p, _i32, _i32, _i32, _i64, _i64, _i64, _p, _p, _p, _i32, _p, _i64, _i64, _p,
                                        _p, _p, _p, _p, _i32, _i32, _p, _p, _f32, _f32, _p, _p, _p, _p, _p, _p]
         for f in (L.ubt_topk, L.ubt_lm_head_topk, L.ubt_bigram_scores, L.ubt_build_tree, L.ubt_draft_tree, L.ubt_tree_mask,
-                  L.ubt_draft_step, L.ubt_draft_step_noalloc, L.ubt_edge_scores, L.ubt_build_tree_best_first, L.ubt_tree_attention, L.ubt_verify_accept, L.ubt_commit_kv, L.ubt_tree_kl_loss):
+                  L.ubt_draft_step, L.ubt_draft_step_noalloc, L.ubt_edge_scores, L.ubt_build_tree_best_first, L.ubt_tree_attention, L.ubt_tree_attention_split, L.ubt_verify_accept, L.ubt_commit_kv, L.ubt_tree_kl_loss):
             f.restype = _i32
         _lib = L
     return _lib
@@ -127,6 +130,17 @@ def _ptr(t: torch.Tensor | None):
 def _stream(stream) -> ctypes.c_void_p:
     s = torch.cuda.current_stream() if stream is None else stream
     return ctypes.c_void_p(s.cuda_stream)
+
+
+def _scratch(n: int, device, stream) -> torch.Tensor | None:
+    """Scratch memory for one call on ``stream``, from that stream's pool: the allocator hands
+    it out again only to work that is ordered after the call."""
+    if n == 0:
+        return None
+    if stream is None:
+        return torch.empty(n, dtype=torch.uint8, device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(n, dtype=torch.uint8, device=device)
 
 
 def _need_gpu(*ts: torch.Tensor) -> None:
@@ -480,9 +494,11 @@ def tree_attention(q: torch.Tensor, k_cache: torch.Tensor | None, v_cache: torch
         out = torch.empty(B, N, H, D, dtype=out_dtype, device=q.device)
     if lse is None:
         lse = torch.empty(B, N, H, dtype=torch.float32, device=q.device)
-    st = lib().ubt_tree_attention(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(prefix_len), Pmax, _ptr(k_tree),
-                                  _ptr(v_tree), _ptr(mask), _ptr(n_nodes), B, N, H, Hkv, D, float(scale), _ptr(out),
-                                  _dtype_code(out), _ptr(lse), _stream(stream))
+    n = lib().ubt_tree_attention_workspace_bytes(B, N, H, Hkv, D, Pmax)
+    workspace = _scratch(n, q.device, stream)
+    st = lib().ubt_tree_attention_split(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(prefix_len), Pmax, _ptr(k_tree),
+                                        _ptr(v_tree), _ptr(mask), _ptr(n_nodes), B, N, H, Hkv, D, float(scale),
+                                        _ptr(out), _dtype_code(out), _ptr(lse), _ptr(workspace), n, _stream(stream))
     _check("ubt_tree_attention", st)
     return out, lse
 

@@ -352,10 +352,17 @@ ubt_status_t ubt_tree_mask(const int32_t* parent, const int32_t* n_nodes, int B,
   return hip_status(ubt::launch_tree_mask(parent, n_nodes, B, N, mask, stream));
 }
 
-ubt_status_t ubt_tree_attention(const void* q, const void* k_cache, const void* v_cache, const int32_t* prefix_len,
+size_t ubt_tree_attention_workspace_bytes(int B, int N, int H, int H_kv, int D, int64_t P_max) {
+  if (B < 1 || N < 1 || N > UBT_MAX_BUDGET + 1 || H < 1 || H_kv < 1 || H % H_kv != 0 || P_max < 0 ||
+      P_max >= (int64_t(1) << 31) || (D != 64 && D != 128))
+    return 0;
+  return ubt::tree_attention_workspace_bytes(B, N, H, H_kv, D, P_max);
+}
+
+ubt_status_t ubt_tree_attention_split(const void* q, const void* k_cache, const void* v_cache, const int32_t* prefix_len,
                                 int64_t P_max, const void* k_tree, const void* v_tree, const uint32_t* mask,
                                 const int32_t* n_nodes, int B, int N, int H, int H_kv, int D, float scale, void* out,
-                                ubt_dtype_t out_dt, float* lse, hipStream_t stream) {
+                                ubt_dtype_t out_dt, float* lse, void* workspace, size_t ws_bytes, hipStream_t stream) {
   if (!q || !prefix_len || !k_tree || !v_tree || !mask || !n_nodes || !out) return UBT_ERR_NULL;
   if (P_max > 0 && (!k_cache || !v_cache)) return UBT_ERR_NULL;
   if (B < 1 || N < 1 || N > UBT_MAX_BUDGET + 1 || H < 1 || H_kv < 1 || H % H_kv != 0 || P_max < 0 ||
@@ -369,6 +376,7 @@ ubt_status_t ubt_tree_attention(const void* q, const void* k_cache, const void* 
   if (!aligned16(q) || !aligned16(k_tree) || !aligned16(v_tree) || !aligned16(out) ||
       (P_max > 0 && (!aligned16(k_cache) || !aligned16(v_cache))))
     return UBT_ERR_UNSUPPORTED;
+  if (workspace && (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return UBT_ERR_WORKSPACE;
   ubt::TreeAttnArgs a{};
   a.q = q;
   a.k_cache = k_cache;
@@ -388,7 +396,15 @@ ubt_status_t ubt_tree_attention(const void* q, const void* k_cache, const void* 
   a.out = out;
   a.out_f32 = out_dt == UBT_F32 ? 1 : 0;
   a.lse = lse;
-  return hip_status(ubt::launch_tree_attention(a, stream));
+  return hip_status(ubt::launch_tree_attention(a, workspace, ws_bytes, stream));
+}
+
+ubt_status_t ubt_tree_attention(const void* q, const void* k_cache, const void* v_cache, const int32_t* prefix_len,
+                                int64_t P_max, const void* k_tree, const void* v_tree, const uint32_t* mask,
+                                const int32_t* n_nodes, int B, int N, int H, int H_kv, int D, float scale, void* out,
+                                ubt_dtype_t out_dt, float* lse, hipStream_t stream) {
+  return ubt_tree_attention_split(q, k_cache, v_cache, prefix_len, P_max, k_tree, v_tree, mask, n_nodes, B, N, H, H_kv,
+                                  D, scale, out, out_dt, lse, nullptr, 0, stream);
 }
 
 ubt_status_t ubt_verify_accept(const int32_t* token, const int32_t* parent, const int32_t* n_nodes,

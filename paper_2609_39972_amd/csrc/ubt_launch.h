@@ -129,7 +129,10 @@ struct TreeAttnArgs {
   int out_f32;
   float* lse;  // optional [B, N, H]
 };
-hipError_t launch_tree_attention(const TreeAttnArgs& a, hipStream_t stream);
+// The keys of a (sequence, head) are cut over several workgroups when the shape leaves the
+// chip idle and the workspace (256-byte aligned; 0 bytes: nothing to cut) is large enough.
+size_t tree_attention_workspace_bytes(int B, int N, int H, int Hkv, int D, int64_t Pmax);
+hipError_t launch_tree_attention(const TreeAttnArgs& a, void* workspace, size_t ws_bytes, hipStream_t stream);
 hipError_t launch_verify_accept(const int32_t* token, const int32_t* parent, const int32_t* n_nodes,
                                 const int32_t* target, int B, int N, int32_t* accept_len, int32_t* accept_nodes,
                                 int32_t* bonus, hipStream_t stream);

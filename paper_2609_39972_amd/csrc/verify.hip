@@ -98,7 +98,20 @@ struct AttnArgs {
   void* out;
   int out_f32;
   float* lse;
+  int splits;     // most parts a key/value range is cut into; 1: no partial results
+  float* part_o;  // [B * Hkv][splits][R][D] unnormalised outputs of the parts
+  float2* part_ml;  // [B * Hkv][splits][R] (running maximum in log2 units, sum of weights)
 };
+
+// The parts a sequence's blocks are cut into: one per kMinPart context blocks, at most
+// `splits`.  Part s holds blocks [s T / n, (s + 1) T / n) of the T = npb + tree blocks; with
+// kMinPart >= 8 >= the tree's blocks every part starts with a context block, of which every
+// query sees a key, so its running maximum is finite.
+constexpr int kMinPart = 8;
+__device__ __forceinline__ int part_count(int npb, int splits) {
+  const int n = (npb + kMinPart - 1) / kMinPart;
+  return n < 1 ? 1 : (n < splits ? n : splits);
+}
 
 // Where the keys and values of block `blk` of sequence b, head h live: the context for
 // blk < npb, else the tree.  Rows at or past `lim` do not exist; reads are clamped to row
@@ -211,7 +224,7 @@ __device__ __forceinline__ uint32_t lane_bits(uint32_t keys32, int kg) {
 // first, then the tree's; `ml` is the tile row's node in the mask rows staged in LDS, or
 // -1 for a row with no query.
 struct VisCtx {
-  int P, npb, nn, kg;
+  int P, npb, nn, kg, nblk;  // context keys and blocks, and all blocks, from this workgroup's first on
 };
 
 template <int D>
@@ -323,7 +336,7 @@ __device__ __forceinline__ void score_block(AttnLds<D>& lds, int blk, const uint
   const int lr = lane & 15, kg = lane >> 4;
   // The next block's maximum of tile j (none when this is the last block: its scores are
   // stale).
-  const bool has_next = blk + 1 < vc.npb + (vc.nn + kKB - 1) / kKB;
+  const bool has_next = blk + 1 < vc.nblk;
   auto next_max = [&](int j) {
     const uint32_t vis = kFullNext ? 0xFFu : (has_next ? tile_vis<D>(lds, vc, blk + 1, ml[j]) : 0u);
     return tile_max<kFullNext>(S.s0[j], S.s1[j], vis, c);
@@ -376,15 +389,16 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attention_kernel(AttnArgs p
   __shared__ __attribute__((aligned(16))) uint16_t k_ring[kRing][kKB * D];
   __shared__ __attribute__((aligned(16))) uint16_t v_ring[kRing][kKB * D];
 
-  // Workgroup -> (sequence, key/value head, row group).  Consecutive workgroups go to
+  // Workgroup -> (part, sequence, key/value head, row group).  Consecutive workgroups go to
   // different XCDs; the remap puts the row groups of one (sequence, head) on one XCD, so
   // they share its key/value blocks through that XCD's L2.
-  const int total = p.B * p.Hkv * p.groups;
+  const int total = p.B * p.Hkv * p.groups * p.splits;
   const int L = static_cast<int>(blockIdx.x);
   const int T8 = total - total % 8;
   const int id = L < T8 ? (L % 8) * (T8 / 8) + L / 8 : L;
   const int grp = id % p.groups;
-  const int bh = id / p.groups;
+  const int part = id / (p.B * p.Hkv * p.groups);
+  const int bh = (id / p.groups) % (p.B * p.Hkv);
   const int h = bh % p.Hkv;
   const int b = bh / p.Hkv;
 
@@ -400,8 +414,15 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attention_kernel(AttnArgs p
   const int P = min(max(p.prefix_len[b], 0), static_cast<int>(p.Pmax));
   const int nn = min(max(p.n_nodes[b], 0), p.N);
   const int npb = (P + kKB - 1) / kKB;
-  const int nblk = npb + (nn + kKB - 1) / kKB;
   const int words = (p.N + 31) / 32;
+  // This workgroup's blocks: nblk from block lo on.  Block numbers below count from lo.
+  const int n_all = npb + (nn + kKB - 1) / kKB;
+  const int parts = part_count(npb, p.splits);
+  if (part >= parts) return;
+  const int lo = static_cast<int>(static_cast<int64_t>(part) * n_all / parts);
+  const int hi = static_cast<int>(static_cast<int64_t>(part + 1) * n_all / parts);
+  const int nblk = hi - lo;
+  const int Pl = P - lo * kKB, npl = npb - lo;
 
   // Tile j of this pair holds query rows r0 + 16 (pair + 4 j) + [0, 16) (slot pair + 4 j
   // of the LDS hand-over); this lane is the column lr of each.  Rows past R (and nodes
@@ -440,16 +461,16 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attention_kernel(AttnArgs p
       S.l_part[j] = 0.f;
       S.m_run[j] = 0.f;
     }
-    const VisCtx vc{P, npb, nn, kg};
+    const VisCtx vc{Pl, npl, nn, kg, nblk};
     if (lane == 0) lds.rescale[0][pair] = 0u;
     // The score waves load V: block X goes to ring slot X % 4 at step X - 3 (blocks 0..2
     // before the first step); the output waves transpose it at step X.  Past the last
     // block the loads repeat it into free slots, so every step issues the same count.
-    const int last = max(nblk - 1, 0);
+    const int last = max(hi - 1, 0);
     const uint32_t row_bytes = static_cast<uint32_t>(p.Hkv) * D * 2;
     const DmaLanes<D, true> dl(row_bytes, wr, lane);
     auto load_v_block = [&](int x) {
-      dl.load(p, block_src(p, min(x, last), npb, P, nn), row_bytes, v_ring[x % kRing], b, h);
+      dl.load(p, block_src(p, min(lo + x, last), npb, P, nn), row_bytes, v_ring[x % kRing], b, h);
     };
     if (nblk > 0) {
       load_v_block(0);
@@ -482,7 +503,7 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attention_kernel(AttnArgs p
       ring_barrier<2 * kBlkLoads>();
     };
     // Blocks 0 .. nf - 1 lie wholly inside the context; each loop below runs one variant.
-    const int nf = P / kKB;
+    const int nf = min(Pl / kKB, nblk);
     int blk = 0;
     for (; blk + 1 < nf; ++blk) step(BoolTag<true>{}, BoolTag<true>{}, blk);
     if (blk < nf) step(BoolTag<true>{}, BoolTag<false>{}, blk++);
@@ -509,11 +530,11 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attention_kernel(AttnArgs p
     // The output waves load K: block X goes to ring slot X % 4 at step X - 4 (blocks 0..3
     // before the first step), and the score waves read it at step X - 1.  Past the last
     // block the loads repeat it into free slots, so every step issues the same count.
-    const int last = max(nblk - 1, 0);
+    const int last = max(hi - 1, 0);
     const uint32_t row_bytes = static_cast<uint32_t>(p.Hkv) * D * 2;
     const DmaLanes<D, false> dl(row_bytes, wr, lane);
     auto load_k_block = [&](int x) {
-      dl.load(p, block_src(p, min(x, last), npb, P, nn), row_bytes, k_ring[x % kRing], b, h);
+      dl.load(p, block_src(p, min(lo + x, last), npb, P, nn), row_bytes, k_ring[x % kRing], b, h);
     };
     if (nblk > 0) {
       load_k_block(0);
@@ -561,6 +582,14 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attention_kernel(AttnArgs p
       const int r = tile_row(j);
       if (r >= p.R) continue;
       const float l = lds.fin_l[pair + kPairs * j][lr];
+      if (parts > 1) {  // partial results, combined by attention_combine_kernel
+        const int64_t at = (static_cast<int64_t>(bh) * p.splits + part) * p.R + r;
+        float* op = p.part_o + at * D;
+#pragma unroll
+        for (int i = 0; i < DT; ++i) *reinterpret_cast<v4f*>(op + 16 * i + 4 * kg) = o[j][i];
+        if (kg == 0) p.part_ml[at] = make_float2(lds.fin_m[pair + kPairs * j][lr], l);
+        continue;
+      }
       const bool has = has_query(r) && l > 0.f;
       const float inv = has ? 1.f / l : 0.f;
       const int64_t orow = (static_cast<int64_t>(b) * p.N + r / p.g) * p.H + h * p.g + r % p.g;
@@ -581,6 +610,66 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attention_kernel(AttnArgs p
         p.lse[orow] = has ? (lds.fin_m[pair + kPairs * j][lr] + __builtin_amdgcn_logf(l)) * kLn2 : neg_inf();
     }
   }
+}
+
+// The parts of one query row, weighted by exp2(m_s - max m): one half wave per row, each
+// lane D / 32 dims, the loads of kCombineBatch parts at once.
+constexpr int kCombineBatch = 8;
+constexpr int kCombineThreads = 256;
+
+template <int D>
+__global__ __launch_bounds__(kCombineThreads) void attention_combine_kernel(AttnArgs p) {
+  constexpr int E = D / 32;  // 2 or 4 dims per lane
+  typedef float vef __attribute__((ext_vector_type(E)));
+  const int64_t row = (static_cast<int64_t>(blockIdx.x) * kCombineThreads + threadIdx.x) / 32;
+  const int l32 = static_cast<int>(threadIdx.x) % 32;
+  const int64_t bh = row / p.R;
+  if (bh >= static_cast<int64_t>(p.B) * p.Hkv) return;
+  const int r = static_cast<int>(row - bh * p.R);
+  const int b = static_cast<int>(bh / p.Hkv), h = static_cast<int>(bh % p.Hkv);
+  const int P = min(max(p.prefix_len[b], 0), static_cast<int>(p.Pmax));
+  const int nn = min(max(p.n_nodes[b], 0), p.N);
+  const int parts = part_count((P + kKB - 1) / kKB, p.splits);
+  if (parts == 1) return;  // stored by the attention kernel
+  const int64_t at = bh * p.splits * p.R + r;
+  float M = neg_inf(), L = 0.f;
+  vef o = 0.f;
+  for (int s0 = 0; s0 < parts; s0 += kCombineBatch) {
+    float2 ml[kCombineBatch];
+    vef x[kCombineBatch];
+#pragma unroll
+    for (int e = 0; e < kCombineBatch; ++e) {
+      const int64_t s = at + static_cast<int64_t>(min(s0 + e, parts - 1)) * p.R;
+      ml[e] = p.part_ml[s];
+      x[e] = *reinterpret_cast<const vef*>(p.part_o + s * D + E * l32);
+    }
+    float m = M;
+#pragma unroll
+    for (int e = 0; e < kCombineBatch; ++e) m = fmaxf(m, ml[e].x);  // a repeated part changes nothing
+    const float f = __builtin_amdgcn_exp2f(M - m);
+    L *= f;
+    o *= f;
+    M = m;
+#pragma unroll
+    for (int e = 0; e < kCombineBatch; ++e) {
+      const float c = s0 + e < parts ? __builtin_amdgcn_exp2f(ml[e].x - m) : 0.f;
+      L += c * ml[e].y;
+      o += c * x[e];
+    }
+  }
+  const bool has = r / p.g < nn && L > 0.f;
+  const float inv = has ? 1.f / L : 0.f;
+  const int64_t orow = (static_cast<int64_t>(b) * p.N + r / p.g) * p.H + h * p.g + r % p.g;
+  vef y = o * inv;
+  if (!has) y = 0.f;
+  if (p.out_f32) {
+    *reinterpret_cast<vef*>(static_cast<float*>(p.out) + orow * D + E * l32) = y;
+  } else {
+    uint32_t* op = reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(p.out) + orow * D + E * l32);
+#pragma unroll
+    for (int i = 0; i < E / 2; ++i) op[i] = pack_bf16(y[2 * i], y[2 * i + 1]);
+  }
+  if (p.lse && l32 == 0) p.lse[orow] = has ? (M + __builtin_amdgcn_logf(L)) * kLn2 : neg_inf();
 }
 
 // ---- acceptance walk: one wave per sequence ----------------------------------------------
@@ -657,7 +746,55 @@ __global__ __launch_bounds__(256) void commit_kv_kernel(const uint16_t* __restri
 
 }  // namespace
 
-hipError_t launch_tree_attention(const TreeAttnArgs& a, hipStream_t stream) {
+namespace {
+
+// Parts per (sequence, head).  One workgroup runs on a compute unit, so `base` = B * Hkv *
+// groups workgroups leave the chip idle when they are few (one sequence of 8 heads: 8 of
+// 256 units) or when their last round is.  The lengths are on the device: the host picks
+// the cut that is best for a full cache, priced in key blocks with about 6 per workgroup for its
+// start and end and 8 for the second kernel; short sequences are cut less (part_count).
+int attention_splits(int64_t base, int64_t Pmax, int N) {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+    cus = 256;
+  const int64_t ctx = (Pmax + kKB - 1) / kKB, all = ctx + (N + kKB - 1) / kKB;
+  int best = 1;
+  int64_t best_cost = (base + cus - 1) / cus * (all + 6);
+  for (int s = 2; s <= 64 && static_cast<int64_t>(s - 1) * kMinPart < ctx; ++s) {
+    const int64_t cost = (base * s + cus - 1) / cus * ((all + s - 1) / s + 6) + 8;
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = s;
+    }
+  }
+  return best;
+}
+
+struct AttnWorkspace {
+  int splits;
+  size_t ml, total;  // (m, l) pairs first, then the outputs
+};
+
+AttnWorkspace attention_workspace(int B, int N, int H, int Hkv, int D, int64_t Pmax) {
+  const int64_t R = static_cast<int64_t>(N) * (H / Hkv);
+  const int64_t base = static_cast<int64_t>(B) * Hkv * ((R + kAttnRows - 1) / kAttnRows);
+  AttnWorkspace w{};
+  w.splits = attention_splits(base, Pmax, N);
+  if (w.splits == 1 || base * w.splits >= (int64_t(1) << 31)) return AttnWorkspace{1, 0, 0};
+  const size_t rows = static_cast<size_t>(B) * Hkv * w.splits * R;
+  w.ml = (rows * sizeof(float2) + 255) & ~static_cast<size_t>(255);
+  w.total = w.ml + rows * D * sizeof(float);
+  return w;
+}
+
+}  // namespace
+
+size_t tree_attention_workspace_bytes(int B, int N, int H, int Hkv, int D, int64_t Pmax) {
+  return attention_workspace(B, N, H, Hkv, D, Pmax).total;
+}
+
+hipError_t launch_tree_attention(const TreeAttnArgs& a, void* workspace, size_t ws_bytes, hipStream_t stream) {
   AttnArgs p{};
   p.q = static_cast<const uint16_t*>(a.q);
   p.kc = static_cast<const uint16_t*>(a.k_cache);
@@ -679,7 +816,14 @@ hipError_t launch_tree_attention(const TreeAttnArgs& a, hipStream_t stream) {
   p.out = a.out;
   p.out_f32 = a.out_f32;
   p.lse = a.lse;
-  const dim3 grid(static_cast<unsigned>(p.B * p.Hkv * p.groups));
+  p.splits = 1;
+  const AttnWorkspace ws = attention_workspace(a.B, a.N, a.H, a.Hkv, a.D, a.Pmax);
+  if (workspace && ws.total != 0 && ws_bytes >= ws.total) {
+    p.splits = ws.splits;
+    p.part_ml = static_cast<float2*>(workspace);
+    p.part_o = reinterpret_cast<float*>(static_cast<char*>(workspace) + ws.ml);
+  }
+  const dim3 grid(static_cast<unsigned>(p.B * p.Hkv * p.groups * p.splits));
   // Tiles per pair: enough for the group's rows (1, 3 or 5; rows past R are empty tiles).
   const int tiles = (min(p.R, kAttnRows) + 15) / 16;
   const int tw = (tiles + kPairs - 1) / kPairs;
@@ -693,6 +837,14 @@ hipError_t launch_tree_attention(const TreeAttnArgs& a, hipStream_t stream) {
   } else {
     hipLaunchKernelGGL((tree_attention_kernel<64, kMaxTiles>), grid, dim3(kAttnThreads), 0, stream, p);
   }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || p.splits == 1) return e;
+  const int64_t rows = static_cast<int64_t>(p.B) * p.Hkv * p.R;
+  const dim3 cgrid(static_cast<unsigned>((rows * 32 + kCombineThreads - 1) / kCombineThreads));
+  if (a.D == 128)
+    hipLaunchKernelGGL((attention_combine_kernel<128>), cgrid, dim3(kCombineThreads), 0, stream, p);
+  else
+    hipLaunchKernelGGL((attention_combine_kernel<64>), cgrid, dim3(kCombineThreads), 0, stream, p);
   return hipGetLastError();
 }
 

@@ -295,3 +295,21 @@ def test_lm_head_full_workspace_bytes():
     assert full(0, 2560, 1000, 8) == 0
     assert full(40, 48, 1000, 8) == 0
     assert full(40, 2560, 2 ** 31 - 1, 64) == 0
+
+
+def test_tree_attention_workspace_bytes():
+    """Partial outputs (D floats) and (max, sum) per query row and part when few workgroups
+    would run, nothing when they fill the chip or the context is short; 0 for bad shapes."""
+    f = ubt.lib().ubt_tree_attention_workspace_bytes
+    n = f(1, 65, 32, 8, 128, 16384)
+    assert n > 0 and n % (8 * 65 * 4 * 128 * 4) == (n // (8 * 65 * 4 * 128 * 4 + 8 * 65 * 4 * 8)) * 8 * 65 * 4 * 8
+    assert f(32, 65, 32, 8, 128, 4096) == 0
+    assert f(1, 65, 32, 8, 128, 256) == 0 and f(1, 65, 32, 8, 128, 0) == 0
+    assert f(1, 65, 30, 8, 128, 16384) == 0 and f(1, 300, 32, 8, 128, 16384) == 0 and f(1, 65, 32, 8, 96, 16384) == 0
+
+
+def test_tree_attention_split_workspace_alignment():
+    """A misaligned workspace is refused before any launch."""
+    bad = ctypes.c_void_p(0x10010)
+    assert ubt.lib().ubt_tree_attention_split(FAKE, FAKE, FAKE, FAKE, 1000, FAKE, FAKE, FAKE, FAKE, 2, 17, 4, 2, 64,
+                                              ctypes.c_float(0.1), FAKE, 1, None, bad, 1 << 30, None) == 5

@@ -102,6 +102,28 @@ def test_tree_attention_small(B, N, H, Hkv, D, Pmax, plen, nn, out_dtype):
         assert not out[b, int(nn[b]):].any(), "rows past n_nodes must be zero"
 
 
+@pytest.mark.parametrize("B,N,H,Hkv,D,Pmax,plen,nn", [
+    (1, 65, 32, 8, 128, 3001, (3001,), (65,)),          # many parts, ragged last block
+    (3, 33, 16, 2, 64, 2000, (2000, 257, 0), (33, 20, 5)),  # the most parts, two, one (no context)
+    (2, 256, 4, 1, 128, 600, (257, 600), (256, 130)),   # the shortest cut context with 8 tree blocks behind it
+    (4, 129, 8, 2, 128, 700, (700, 256, 288, 31), (129, 1, 0, 64)),  # two row groups; an empty tree
+    (1, 17, 4, 4, 64, 9000, (8500,), (17,)),            # a cache larger than the context
+])
+@pytest.mark.parametrize("out_dtype", ["f32", "bf16"])
+def test_tree_attention_split_keys(B, N, H, Hkv, D, Pmax, plen, nn, out_dtype):
+    """Shapes whose keys are cut over several workgroups and combined: within the tolerance of
+    the whole attention (each part's weights are rounded relative to its own maximum, the
+    combination is fp32)."""
+    import torch
+
+    import paper_2609_39972_amd as ubt
+    from gpu_util import say
+
+    say(f"tree_attention split B={B} N={N} H={H} Hkv={Hkv} D={D} P={plen} nn={nn} out={out_dtype}")
+    assert ubt.lib().ubt_tree_attention_workspace_bytes(B, N, H, Hkv, D, Pmax) > 0
+    test_tree_attention_small(B, N, H, Hkv, D, Pmax, plen, nn, out_dtype)
+
+
 def test_tree_attention_on_draft_trees():
     """Trees, masks and node counts from the draft step of the headline workload,
     attended over a 1000-token context with Qwen3-8B's head layout."""
