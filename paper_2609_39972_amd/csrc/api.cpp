@@ -252,7 +252,13 @@ ubt_status_t draft_step_impl(const void* logits, ubt_dtype_t dt, int B, int gamm
   s.cand_logit = cand_logit;
   s.logq = logq;
   s.sc = sc;
-  if (!ubt::draft_step_fused(static_cast<int>(dt), aligned, B, gamma, V, K, static_cast<int>(feat_dt), W)) {
+  bool one_launch = ubt::draft_step_fused(static_cast<int>(dt), B, gamma, V, K, static_cast<int>(feat_dt), W);
+  // Unaligned rows never needed a workspace: without one they keep the separate kernels.
+  if (one_launch && !aligned && !use_static &&
+      (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 ||
+       workspace_bytes < ubt::step_workspace_bytes(B, gamma, V, K, static_cast<int>(dt))))
+    one_launch = false;
+  if (!one_launch) {
     st = hip_status(ubt::launch_topk(logits, static_cast<int>(dt), aligned, B, gamma, V, stride_b, stride_i, K,
                                      cand_ids, cand_logit, cand_logprob, lse, stream));
     if (st != UBT_OK) return st;
@@ -285,8 +291,8 @@ ubt_status_t draft_step_impl(const void* logits, ubt_dtype_t dt, int B, int gamm
   } else if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < need) {
     return UBT_ERR_WORKSPACE;
   }
-  return hip_status(ubt::launch_draft_step(logits, static_cast<int>(dt), B, gamma, V, stride_b, stride_i, K, cand_ids,
-                                           cand_logit, cand_logprob, lse, s, a, workspace, stream));
+  return hip_status(ubt::launch_draft_step(logits, static_cast<int>(dt), aligned, B, gamma, V, stride_b, stride_i, K,
+                                           cand_ids, cand_logit, cand_logprob, lse, s, a, workspace, stream));
 }
 
 }  // namespace

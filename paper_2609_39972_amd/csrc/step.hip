@@ -78,6 +78,7 @@ struct PipeArgs {
   const void* logits;
   int64_t V, stride_b, stride_i;
   int B, gamma, K;
+  int aligned;        // rows of whole, aligned 16-byte groups
   int chunks;         // C: chunks per row
   int64_t chunk_len;  // elements per chunk, a whole number of tiles; the last chunk is shorter
   int32_t* cand_ids;
@@ -104,8 +105,11 @@ __device__ __forceinline__ void pipe_worker(const PipeArgs& p, RowLdsT<kPipeWave
   const int64_t c0 = static_cast<int64_t>(c) * p.chunk_len;
   const int64_t len = p.V - c0 < p.chunk_len ? p.V - c0 : p.chunk_len;
   const T* rp = static_cast<const T*>(p.logits) + b * p.stride_b + i * p.stride_i + c0;
-  sweep_row<T, true, kPipeWaves>(lds, rp, len, p.K, row * p.chunks + c,
-                                 RowOut{p.part_ids, p.part_logit, nullptr, p.part_lse, true});
+  const RowOut out{p.part_ids, p.part_logit, nullptr, p.part_lse, true};
+  if (p.aligned)
+    sweep_row<T, true, kPipeWaves>(lds, rp, len, p.K, row * p.chunks + c, out);
+  else
+    sweep_row<T, false, kPipeWaves>(lds, rp, len, p.K, row * p.chunks + c, out);
   // Wave 0 wrote the chunk's results with agent-scope atomic stores; once they have
   // completed, the row's counter goes up.
   if (w == 0) {
@@ -368,8 +372,8 @@ size_t step_workspace_bytes(int B, int gamma, int64_t V, int K, int dtype) {
   return pipe_workspace(B, gamma, V, K, dtype).total;
 }
 
-bool draft_step_fused(int dtype, bool aligned, int B, int gamma, int64_t V, int K, int feat_dtype, int W) {
-  if (!aligned || feat_dtype != 1 || B > kMaxStepSequences) return false;
+bool draft_step_fused(int dtype, int B, int gamma, int64_t V, int K, int feat_dtype, int W) {
+  if (feat_dtype != 1 || B > kMaxStepSequences) return false;
   if (!draft_tree_fused(feat_dtype, gamma, K, W)) return false;
   (void)dtype;
   (void)V;
@@ -394,8 +398,8 @@ hipError_t launch_draft_step_k64(const SelectorArgs& s, const TreeArgs& a, void*
   return launch_draft_tree_k64(s, ta, reinterpret_cast<uint32_t*>(ws + kCountBase), stream);
 }
 
-hipError_t launch_draft_step(const void* logits, int dtype, int B, int gamma, int64_t V, int64_t stride_b,
-                             int64_t stride_i, int K, int32_t* cand_ids, float* cand_logit, float* cand_logprob,
+hipError_t launch_draft_step(const void* logits, int dtype, bool aligned, int B, int gamma, int64_t V,
+                             int64_t stride_b, int64_t stride_i, int K, int32_t* cand_ids, float* cand_logit, float* cand_logprob,
                              float* lse, const SelectorArgs& s, const TreeArgs& a, void* workspace,
                              hipStream_t stream) {
   PipeArgs p{};
@@ -406,6 +410,7 @@ hipError_t launch_draft_step(const void* logits, int dtype, int B, int gamma, in
   p.B = B;
   p.gamma = gamma;
   p.K = K;
+  p.aligned = aligned && (V * (dtype == 1 ? 2 : 4)) % 16 == 0 ? 1 : 0;
   pipe_chunks(V, K, dtype, p.chunks, p.chunk_len);
   p.cand_ids = cand_ids;
   p.cand_logit = cand_logit;

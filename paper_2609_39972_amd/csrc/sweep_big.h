@@ -73,13 +73,13 @@ __device__ __forceinline__ void sweep_row_big(BigRowLds& lds, const T* __restric
   const int nw = blockDim.x / kWave;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int lane = threadIdx.x % kWave;
-  const __amdgpu_buffer_rsrc_t rsrc = row_resource(rp, static_cast<uint32_t>(V * static_cast<int64_t>(sizeof(T))));
+  const RowIn<T, kAligned> in(rp, V);
   auto& s = lds.wave[w];
   for (int e = static_cast<int>(threadIdx.x); e < (kKeyPasses + kIdPasses) * 256; e += static_cast<int>(blockDim.x))
     (&lds.hist[0][0])[e] = 0u;
   if (threadIdx.x == 0) lds.nfin = 0u;  // published by the barrier inside the pass
   WaveState st;
-  stream_row<T, kAligned, kWaves, true>(s, lds.lane_max, rp, V, K, nw, w, lane, rsrc, st);
+  stream_row<T, kAligned, kWaves, true>(s, lds.lane_max, in, K, nw, w, lane, st);
 
   // Candidates of this wave: the buffered elements that pass its threshold (strictly once
   // it holds a running top K: later elements carry larger ids) and, if it merged, its
@@ -97,10 +97,10 @@ __device__ __forceinline__ void sweep_row_big(BigRowLds& lds, const T* __restric
         const int g = e / EPG, j = e % EPG;
         const uint32_t word = reinterpret_cast<const uint32_t*>(&s.data[g])[j * 4 / EPG];
         const uint32_t bits = EPG == 8 ? (word >> (16 * (j & 1))) & 0xFFFFu : word;
-        const int64_t gid = static_cast<int64_t>(s.base[g]) + j;
-        if (gid < V) {
+        const uint32_t gid = s.base[g] + static_cast<uint32_t>(j);
+        if (gid < static_cast<uint32_t>(V)) {
           k = Traits<T>::key_bits(bits);
-          id = static_cast<uint32_t>(gid);
+          id = gid;
           live = (st.strict ? k > st.thr : k >= st.thr) && k >= tall;
         }
       }
@@ -126,7 +126,8 @@ __device__ __forceinline__ void sweep_row_big(BigRowLds& lds, const T* __restric
         const uint32_t word = v[j * 4 / EPG];
         const uint32_t bits = EPG == 8 ? (word >> (16 * (j & 1))) & 0xFFFFu : word;
         km[j] = Traits<T>::key_bits(bits);
-        const bool in = static_cast<int64_t>(gbase) + j < V && (st.strict ? km[j] > st.thr : km[j] >= st.thr);
+        const bool in = gbase + static_cast<uint32_t>(j) < static_cast<uint32_t>(V) &&
+                        (st.strict ? km[j] > st.thr : km[j] >= st.thr);
         live |= in ? 1u << j : 0u;
         top = max(top, in ? km[j] : 0u);
       }
@@ -192,7 +193,7 @@ __device__ __forceinline__ void sweep_row_big(BigRowLds& lds, const T* __restric
   int need = K, pass = 0, n_eq = 0;
   uint32_t kstar = ktop;
   {
-    int shift = 32 - __builtin_clz(tall ^ ktop | 1u);  // bits [shift, 32) are common
+    int shift = 32 - __builtin_clz((tall ^ ktop) | 1u);  // bits [shift, 32) are common
     if (tall == ktop) shift = 0;
     uint32_t prefix = shift >= 32 ? 0u : ktop >> shift;
     int above = 0, in_bin = 0;

@@ -51,6 +51,8 @@ void launch_typed(const void* logits, int B, int gamma, int64_t V, int64_t strid
 hipError_t launch_topk(const void* logits, int dtype, bool aligned, int B, int gamma, int64_t V, int64_t stride_b,
                        int64_t stride_i, int K, int32_t* cand_ids, float* cand_logit, float* cand_logprob, float* lse,
                        hipStream_t stream) {
+  // Rows of whole 16-byte groups need no masks at their ends (RowIn).
+  aligned = aligned && (V * (dtype == 1 ? 2 : 4)) % 16 == 0;
   if (dtype == 1) {
     if (aligned)
       launch_typed<uint16_t, true>(logits, B, gamma, V, stride_b, stride_i, K, cand_ids, cand_logit, cand_logprob,

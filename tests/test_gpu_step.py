@@ -262,3 +262,31 @@ def test_step_neg_inf():
     lg[1, 1, 100:] = 0xFF80
     d["logits"] = lg
     _check(w, w.W, d=d)
+
+
+@pytest.mark.parametrize("kw", [
+    dict(B=2, L=5, V=8193, K=16, W=8, budget=40),                  # a last chunk of one element
+    dict(B=3, L=6, V=12287, K=4, W=3, budget=12),                  # every row at another offset
+    dict(B=2, L=4, V=30001, dtype="f32", K=8),                     # fp32
+    dict(B=5, L=3, V=4099, K=8, W=4, budget=20),                   # few tiles
+])
+def test_step_unaligned_rows_one_launch(kw):
+    """Rows that start between 16-byte boundaries take the one launch too; without a workspace
+    they keep the separate kernels, with the same candidates and tree."""
+    import torch
+
+    import paper_2609_39972_amd as ubt
+    from gpu_util import to_np
+
+    w = _custom(304, **kw)
+    d = synth.inputs(w, 0)
+    _check(w, w.W, d=d)
+    one = ubt.DraftStep(*_args(w, d, w.W), one_call=True,
+                        logit_dtype=torch.bfloat16 if w.dtype == "bf16" else torch.float32)
+    a = to_np(one.run(_logits_tensor(w, d)))
+    one.check()
+    one.workspace = torch.zeros(16, dtype=torch.uint8, device="cuda")
+    b = to_np(one.run(_logits_tensor(w, d)))
+    torch.cuda.synchronize()
+    for k in EXACT_KEYS:
+        assert np.array_equal(a[k], b[k]), f"{k} differs without a workspace"

@@ -194,3 +194,23 @@ def test_row_counts_around_the_wave_switch(B, gamma):
     """Fewer and more rows than compute units use different workgroup sizes."""
     rng = np.random.default_rng(B * gamma)
     _check(synth.store(rng.normal(0, 2, (B, gamma, 9000)), "bf16"), 8)
+
+
+@pytest.mark.parametrize("dt,off", [("bf16", o) for o in range(1, 8)] + [("f32", o) for o in range(1, 4)])
+@pytest.mark.parametrize("V,K", [(1, 1), (7, 4), (2041, 8), (2048, 16), (4097, 64), (33333, 10), (131071, 20)])
+def test_rows_off_the_16_byte_boundary(dt, off, V, K):
+    """Rows that start `off` elements past a 16-byte boundary, in the middle of much larger
+    values: the elements that share the row's first and last 16 bytes never leak in.  One row
+    is constant (ties across every tile), one holds -inf only before its last element."""
+    from gpu_util import say
+
+    say(f"topk off={off} V={V} dtype={dt} K={K}")
+    rng = np.random.default_rng(V * 10 + off)
+    stride = (V + 40) // 8 * 8 + 8  # odd row counts of 16-byte groups between the rows
+    x = np.full((2, 3, stride), 1e30)
+    rows = rng.normal(0, 2.5, (2, 3, V))
+    rows[0, 1] = 0.5
+    rows[1, 2, :-1] = -np.inf
+    x[:, :, off:off + V] = rows
+    g = _run(synth.store(x, dt), K, view=lambda t: t[:, :, off:off + V])
+    parity.check_topk(g, oracle.topk(synth.store(rows, dt), K))
