@@ -293,6 +293,22 @@ ubt_status_t ubt_draft_step(const void* logits, ubt_dtype_t dt, int B, int gamma
                             float* score, uint32_t* mask, void* workspace, size_t workspace_bytes,
                             hipStream_t stream);
 
+/* ubt_draft_step_full -- ubt_draft_step for callers whose workspace is zero-filled before
+ * its first use and never shared by overlapping calls, for every shape: rows that are not
+ * 16-byte aligned then take the one launch too (with at least
+ * ubt_draft_step_workspace_bytes(...) bytes), and so does K = 64 with 16 < W <= 32 its
+ * selector + search launch.  With a missing, short or misaligned workspace those shapes run
+ * the separate kernels; everything else, errors included, is ubt_draft_step's. */
+ubt_status_t ubt_draft_step_full(const void* logits, ubt_dtype_t dt, int B, int gamma, int64_t V,
+                                 int64_t stride_b, int64_t stride_i, int K, const void* phi_tab,
+                                 const void* psi_tab, const void* gate, ubt_dtype_t feat_dt, int r,
+                                 const int32_t* anchor, const float* alpha, const float* lambda, int W,
+                                 int budget, float zeta, int32_t* cand_ids, float* cand_logit,
+                                 float* cand_logprob, float* lse, float* logq, int32_t* n_nodes,
+                                 int32_t* token, int32_t* parent, int32_t* depth, int32_t* cand_rank,
+                                 float* score, uint32_t* mask, void* workspace, size_t workspace_bytes,
+                                 hipStream_t stream);
+
 /* ------------------------------------------------------------------------------------
  * ubt_draft_step_noalloc -- ubt_draft_step for callers that cannot allocate device
  * memory (code under HIP graph capture, tight serving loops, harnesses that forbid

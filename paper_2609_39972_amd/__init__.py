@@ -39,7 +39,7 @@ STATUS = {0: "UBT_OK", 1: "UBT_ERR_NULL", 2: "UBT_ERR_SHAPE", 3: "UBT_ERR_VALUE"
 # Every symbol include/ubt.h declares.
 EXPORTS = ("ubt_status_str", "ubt_abi_version", "ubt_last_hip_error", "ubt_topk",
            "ubt_lm_head_topk_workspace_bytes", "ubt_lm_head_topk_full_workspace_bytes", "ubt_lm_head_topk", "ubt_bigram_scores", "ubt_build_tree", "ubt_draft_tree", "ubt_draft_step_workspace_bytes",
-           "ubt_draft_step", "ubt_draft_step_noalloc", "ubt_edge_scores", "ubt_build_tree_best_first", "ubt_tree_mask", "ubt_tree_attention", "ubt_tree_attention_split", "ubt_tree_attention_workspace_bytes", "ubt_verify_accept", "ubt_commit_kv",
+           "ubt_draft_step", "ubt_draft_step_full", "ubt_draft_step_noalloc", "ubt_edge_scores", "ubt_build_tree_best_first", "ubt_tree_mask", "ubt_tree_attention", "ubt_tree_attention_split", "ubt_tree_attention_workspace_bytes", "ubt_verify_accept", "ubt_commit_kv",
            "ubt_tree_kl_loss")
 
 _p = ctypes.c_void_p
@@ -88,6 +88,7 @@ def lib() -> ctypes.CDLL:
         L.ubt_draft_step.argtypes = [_p, _i32, _i32, _i32, _i64, _i64, _i64, _i32, _p, _p, _p, _i32, _i32, _p, _p,
                                      _p, _i32, _i32, _f32, _p, _p, _p, _p, _p, _p, _p, _p, _p, _p, _p, _p, _p,
                                      ctypes.c_size_t, _p]
+        L.ubt_draft_step_full.argtypes = L.ubt_draft_step.argtypes
         L.ubt_draft_step_noalloc.argtypes = [_p, _i32, _i32, _i32, _i64, _i64, _i64, _i32, _p, _p, _p, _i32, _i32,
                                              _p, _p, _p, _i32, _i32, _f32, _p, _p, _p, _p, _p, _p, _p, _p, _p, _p,
                                              _p, _p, _p]
@@ -104,7 +105,7 @@ def lib() -> ctypes.CDLL:
         L.ubt_tree_kl_loss.argtypes = [_p, _i32, _i32, _i32, _i64, _i64, _i64, _p, _p, _p, _i32, _p, _i64, _i64, _p,
                                        _p, _p, _p, _p, _i32, _i32, _p, _p, _f32, _f32, _p, _p, _p, _p, _p, _p]
         for f in (L.ubt_topk, L.ubt_lm_head_topk, L.ubt_bigram_scores, L.ubt_build_tree, L.ubt_draft_tree, L.ubt_tree_mask,
-                  L.ubt_draft_step, L.ubt_draft_step_noalloc, L.ubt_edge_scores, L.ubt_build_tree_best_first, L.ubt_tree_attention, L.ubt_tree_attention_split, L.ubt_verify_accept, L.ubt_commit_kv, L.ubt_tree_kl_loss):
+                  L.ubt_draft_step, L.ubt_draft_step_full, L.ubt_draft_step_noalloc, L.ubt_edge_scores, L.ubt_build_tree_best_first, L.ubt_tree_attention, L.ubt_tree_attention_split, L.ubt_verify_accept, L.ubt_commit_kv, L.ubt_tree_kl_loss):
             f.restype = _i32
         _lib = L
     return _lib
@@ -424,13 +425,14 @@ def draft_step(logits: torch.Tensor, phi: torch.Tensor, psi: torch.Tensor, gate:
     if workspace is None:
         workspace = draft_step_workspace(B, gamma, V, K, logits.dtype, dev)
     a, l = _host_f32(alpha, gamma), _host_f32(lam, gamma)
-    st = lib().ubt_draft_step(_ptr(logits), _dtype_code(logits), B, gamma, V, logits.stride(0), logits.stride(1), K,
-                              _ptr(phi), _ptr(psi), _ptr(gate), _dtype_code(phi), r, _ptr(anchor), a, l, W, budget,
-                              float(zeta), _ptr(cand["cand_ids"]), _ptr(cand["cand_logit"]),
-                              _ptr(cand.get("cand_logprob")), _ptr(cand.get("lse")), _ptr(logq),
-                              _ptr(out["n_nodes"]), _ptr(out["token"]), _ptr(out["parent"]), _ptr(out["depth"]),
-                              _ptr(out["cand_rank"]), _ptr(out["score"]), _ptr(out.get("mask")), _ptr(workspace),
-                              workspace.numel(), _stream(stream))
+    # The workspace is zero-filled and serves one stream, whatever the shape.
+    st = lib().ubt_draft_step_full(_ptr(logits), _dtype_code(logits), B, gamma, V, logits.stride(0), logits.stride(1),
+                                   K, _ptr(phi), _ptr(psi), _ptr(gate), _dtype_code(phi), r, _ptr(anchor), a, l, W,
+                                   budget, float(zeta), _ptr(cand["cand_ids"]), _ptr(cand["cand_logit"]),
+                                   _ptr(cand.get("cand_logprob")), _ptr(cand.get("lse")), _ptr(logq),
+                                   _ptr(out["n_nodes"]), _ptr(out["token"]), _ptr(out["parent"]), _ptr(out["depth"]),
+                                   _ptr(out["cand_rank"]), _ptr(out["score"]), _ptr(out.get("mask")),
+                                   _ptr(workspace), workspace.numel(), _stream(stream))
     _check("ubt_draft_step", st)
     return {**cand, "logq": logq, **out}
 

@@ -217,15 +217,18 @@ size_t ubt_draft_step_workspace_bytes(int B, int gamma, int64_t V, int K, ubt_dt
 
 namespace {
 
-// ubt_draft_step and ubt_draft_step_noalloc: the same checks and kernels; the one-launch
-// kernel's workspace is the caller's (use_static = false) or the library's static array.
+// ubt_draft_step, ubt_draft_step_full and ubt_draft_step_noalloc: the same checks and
+// kernels; the one-launch kernel's workspace is the caller's (use_static = false) or the
+// library's static array.  full: the caller's workspace is zero-filled and unshared for every
+// shape, so the shapes that ubt_draft_step promises to leave it alone for may use it too.
 ubt_status_t draft_step_impl(const void* logits, ubt_dtype_t dt, int B, int gamma, int64_t V, int64_t stride_b,
                              int64_t stride_i, int K, const void* phi_tab, const void* psi_tab, const void* gate,
                              ubt_dtype_t feat_dt, int r, const int32_t* anchor, const float* alpha,
                              const float* lambda, int W, int budget, float zeta, int32_t* cand_ids, float* cand_logit,
                              float* cand_logprob, float* lse, float* logq, int32_t* n_nodes, int32_t* token,
                              int32_t* parent, int32_t* depth, int32_t* cand_rank, float* score, uint32_t* mask,
-                             void* workspace, size_t workspace_bytes, bool use_static, hipStream_t stream) {
+                             void* workspace, size_t workspace_bytes, bool use_static, bool full,
+                             hipStream_t stream) {
   if (!logits || !cand_ids || !cand_logit || !logq) return UBT_ERR_NULL;
   if (!valid_dtype(dt)) return UBT_ERR_VALUE;
   if (B < 1 || gamma < 1 || gamma > UBT_MAX_GAMMA || K < 1 || K > UBT_MAX_K || V < K || V >= (int64_t(1) << 31))
@@ -253,9 +256,9 @@ ubt_status_t draft_step_impl(const void* logits, ubt_dtype_t dt, int B, int gamm
   s.logq = logq;
   s.sc = sc;
   bool one_launch = ubt::draft_step_fused(static_cast<int>(dt), B, gamma, V, K, static_cast<int>(feat_dt), W);
-  // Unaligned rows never needed a workspace: without one they keep the separate kernels.
-  if (one_launch && !aligned && !use_static &&
-      (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 ||
+  // Unaligned rows need no workspace: without a full one they run the separate kernels.
+  if (one_launch && !aligned &&
+      (!full || !workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 ||
        workspace_bytes < ubt::step_workspace_bytes(B, gamma, V, K, static_cast<int>(dt))))
     one_launch = false;
   if (!one_launch) {
@@ -263,7 +266,7 @@ ubt_status_t draft_step_impl(const void* logits, ubt_dtype_t dt, int B, int gamm
                                      cand_ids, cand_logit, cand_logprob, lse, stream));
     if (st != UBT_OK) return st;
     // K = 64: the selector and the search in one launch when a workspace is at hand.
-    if (ubt::draft_step_k64(static_cast<int>(feat_dt), B, gamma, K, W)) {
+    if (ubt::draft_step_k64(static_cast<int>(feat_dt), B, gamma, K, W) && (full || W <= 16)) {
       const size_t need = ubt::step_k64_workspace_bytes(B, gamma);
       if (use_static && need <= ubt::step_static_scratch_bytes()) {
         st = hip_status(ubt::step_static_scratch(&workspace));
@@ -308,7 +311,20 @@ ubt_status_t ubt_draft_step(const void* logits, ubt_dtype_t dt, int B, int gamma
                             void* workspace, size_t workspace_bytes, hipStream_t stream) {
   return draft_step_impl(logits, dt, B, gamma, V, stride_b, stride_i, K, phi_tab, psi_tab, gate, feat_dt, r, anchor,
                          alpha, lambda, W, budget, zeta, cand_ids, cand_logit, cand_logprob, lse, logq, n_nodes,
-                         token, parent, depth, cand_rank, score, mask, workspace, workspace_bytes, false, stream);
+                         token, parent, depth, cand_rank, score, mask, workspace, workspace_bytes, false, false, stream);
+}
+
+ubt_status_t ubt_draft_step_full(const void* logits, ubt_dtype_t dt, int B, int gamma, int64_t V, int64_t stride_b,
+                                 int64_t stride_i, int K, const void* phi_tab, const void* psi_tab, const void* gate,
+                                 ubt_dtype_t feat_dt, int r, const int32_t* anchor, const float* alpha,
+                                 const float* lambda, int W, int budget, float zeta, int32_t* cand_ids,
+                                 float* cand_logit, float* cand_logprob, float* lse, float* logq, int32_t* n_nodes,
+                                 int32_t* token, int32_t* parent, int32_t* depth, int32_t* cand_rank, float* score,
+                                 uint32_t* mask, void* workspace, size_t workspace_bytes, hipStream_t stream) {
+  return draft_step_impl(logits, dt, B, gamma, V, stride_b, stride_i, K, phi_tab, psi_tab, gate, feat_dt, r, anchor,
+                         alpha, lambda, W, budget, zeta, cand_ids, cand_logit, cand_logprob, lse, logq, n_nodes,
+                         token, parent, depth, cand_rank, score, mask, workspace, workspace_bytes, false, true,
+                         stream);
 }
 
 ubt_status_t ubt_draft_step_noalloc(const void* logits, ubt_dtype_t dt, int B, int gamma, int64_t V,
@@ -321,7 +337,7 @@ ubt_status_t ubt_draft_step_noalloc(const void* logits, ubt_dtype_t dt, int B, i
                                     uint32_t* mask, hipStream_t stream) {
   return draft_step_impl(logits, dt, B, gamma, V, stride_b, stride_i, K, phi_tab, psi_tab, gate, feat_dt, r, anchor,
                          alpha, lambda, W, budget, zeta, cand_ids, cand_logit, cand_logprob, lse, logq, n_nodes,
-                         token, parent, depth, cand_rank, score, mask, nullptr, 0, true, stream);
+                         token, parent, depth, cand_rank, score, mask, nullptr, 0, true, false, stream);
 }
 
 ubt_status_t ubt_edge_scores(const void* phi_tab, const void* psi_tab, const void* gate, ubt_dtype_t feat_dt,

@@ -32,18 +32,20 @@ __device__ __forceinline__ int div_k(int e, uint64_t magic) {
 //  * the supertree keys of all depths are loaded once into registers for Top_budget;
 //    the ancestor mask is built by pointer jumping (ceil(log2(gamma+1)) rounds).
 constexpr int kFastMaxWK = 1024;
+constexpr int kWideMaxW = 64;  // the four-wave search (any K <= 64)
 constexpr int kFastMaxGW = 1024;
 constexpr int kFastMaxW = 64;
 constexpr int kStageLive = 272;                // up to 255 selected entries + 16 zero entries
 constexpr int kStageCap = kStageLive + kWave;  // + one dummy slot per lane
 constexpr int kMaskWords = 8;                  // ceil(256 / 32)
-constexpr int kBoundWords = 32;                // K = 64: per-parent best keys (16), per-wave counts
+constexpr int kBoundWords = kWideMaxW + 4;     // four-wave search: per-parent best keys, per-wave counts
 
 struct FastLayout {
   uint32_t slab, rmax, cids, xpose, stage, s_key, s_info, f_slot, anc, mk, ready, fail, bound, total;
 };
 
-__host__ __device__ inline FastLayout fast_layout(int gamma, int K, int W) {
+// wide: the four-wave search (expand_depths_wide), else the one-wave search.
+__host__ __device__ inline FastLayout fast_layout(int gamma, int K, int W, bool wide = false) {
   FastLayout L{};
   uint32_t p = 0;
   auto take = [&p](size_t bytes) {
@@ -51,13 +53,14 @@ __host__ __device__ inline FastLayout fast_layout(int gamma, int K, int W) {
     p += static_cast<uint32_t>((bytes + 15) & ~static_cast<size_t>(15));
     return at;
   };
-  // K = 64: the slabs (gamma K^2 floats) do not fit; two depths' slabs at a time are staged.
-  const bool in_lds = K <= 16;
+  // Four-wave search: the slabs (gamma K^2 floats) may not fit; two depths' slabs at a time
+  // are staged.
+  const bool in_lds = !wide;
   L.slab = take((in_lds ? static_cast<size_t>(gamma) : 2) * K * K * sizeof(float));
   L.rmax = take(in_lds ? static_cast<size_t>(gamma) * K * sizeof(float) : 0);
   L.cids = take(static_cast<size_t>(gamma) * K * sizeof(int32_t));
-  // K = 64: the survivors' stage (up to W K entries, 16 zero entries, a dummy per lane).
-  L.xpose = take(K <= 16 ? kFastMaxWK * sizeof(float) : (kFastMaxWK + 16 + kWave) * sizeof(uint2));
+  // Four-wave search: the survivors' stage (up to W K entries, 16 zero entries, a dummy per lane).
+  L.xpose = take(in_lds ? kFastMaxWK * sizeof(float) : (static_cast<size_t>(W) * K + 16 + kWave) * sizeof(uint2));
   L.stage = take(kStageCap * sizeof(uint2));
   L.s_key = take(static_cast<size_t>(gamma) * W * sizeof(uint32_t));
   L.s_info = take(static_cast<size_t>(gamma) * W * sizeof(uint32_t));
@@ -72,8 +75,14 @@ __host__ __device__ inline FastLayout fast_layout(int gamma, int K, int W) {
 }
 
 __host__ __device__ inline bool fast_tree_fits(int gamma, int K, int W) {
-  const bool shape = ((K == 4 || K == 8 || K == 16) && W * K <= 512) || (K == 64 && W * K <= kFastMaxWK);
-  return shape && W <= kFastMaxW && gamma * W <= kFastMaxGW;
+  return (K == 4 || K == 8 || K == 16) && W * K <= 512 && W <= kFastMaxW && gamma * W <= kFastMaxGW;
+}
+
+// The four-wave search: every other shape of up to 64 parents and 1024 supertree nodes.  Its
+// depth costs about 1.9 us whatever K is, the general kernel's 3.5 us (K = 10, W = 10) to
+// 16 us (K = 64, W = 20); the one-wave search above stays the faster one where it applies.
+__host__ __device__ inline bool wide_tree_fits(int gamma, int K, int W) {
+  return K <= 64 && W <= kWideMaxW && gamma * W <= kFastMaxGW;
 }
 
 // Selects the `need` best live entries under (key desc, index asc), where entry (r, lane)
@@ -218,7 +227,7 @@ struct FastSmem {
   uint32_t* mk;
   uint32_t* ready;  // per position: its slab is in LDS (one-launch kernels only)
   uint32_t* fail;   // nonzero once a wait of this workgroup ran out of time (one-launch kernels only)
-  uint32_t* bound;  // K = 64: [0, 16) best child key per parent, [16, 20) survivors per wave
+  uint32_t* bound;  // four-wave search: [0, 64) best child key per parent, [64, 68) survivors per wave
 };
 
 // Top_budget over the supertree: stages the selected entries (as compact_selected does).
@@ -444,7 +453,7 @@ __device__ __forceinline__ void frontier_store(const TreeArgs& a, const FastSmem
 template <int KT, int R, bool kWait>
 __device__ __forceinline__ void expand_depths(const TreeArgs& a, const FastSmem& sm, int64_t b, int lane,
                                               int& total) {
-  static_assert(KT <= 16, "K = 64 stages its slabs (expand_depths64)");
+  static_assert(KT <= 16, "larger K runs expand_depths_wide");
   constexpr int kLogK = KT == 4 ? 2 : (KT == 8 ? 3 : 4);
   const int gamma = a.gamma, W = a.W;
   // Frontier entry on lane j < np: score key, position in F, and its slab row for the
@@ -518,12 +527,13 @@ __device__ __forceinline__ void expand_depths(const TreeArgs& a, const FastSmem&
   }
 }
 
-// The same expansion for K = 64 on kK64Waves waves of one workgroup (a lone wave issues
-// too slowly for the 64 W entries of a depth).  The slabs (gamma K^2 floats) do not fit
-// in LDS: two are staged at a time, each wave loading a quarter of the slab two depths
+// The same expansion for any K <= 64 on kK64Waves waves of one workgroup (a lone wave
+// issues too slowly for the W K entries of a depth).  The slabs (gamma K^2 floats) may not
+// fit in LDS: two are staged at a time, each wave loading a quarter of the slab two depths
 // ahead into registers while the current one is searched.  Entry (r, lane) of depth d is
-// child `lane` of the frontier entry of rank r in F_{d-1} (index r * 64 + lane: index
-// order is (parent rank, candidate rank)); wave w holds the parents r = w, w + 4, ...
+// child `lane` (dead for lane >= K) of the frontier entry of rank r in F_{d-1} (index
+// r * 64 + lane: index order is (parent rank, candidate rank)); wave w holds the parents
+// r = w, w + 4, ...
 //
 // Selection: each parent's best child is a wave maximum over its register, and the
 // smallest of these W maxima is a lower bound of the W-th best entry (they are W distinct
@@ -533,24 +543,35 @@ __device__ __forceinline__ void expand_depths(const TreeArgs& a, const FastSmem&
 // ranked.  All waves return with the same `total`.
 constexpr int kK64Waves = 4;
 
-//
+// KC: K = 64 exactly (KC = 64 and kExact), else K <= KC in {16, 32, 64}.  RW: registers of
+// one parent's children per wave (W <= 4 RW).
 // kWait: the slabs are written by other workgroups of the same launch.  Before loading the
 // slab of depth d a wave waits for ready[d - 1] (an agent-scope word its producer sets
 // once the slab's agent-scope stores have completed), then loads it with agent-scope
 // loads; a wait that runs out of time sets the workgroup's fail word.  t0: the wave's
 // start time.
-template <int RW, bool vec, bool kWait = false>
-__device__ __forceinline__ void expand_depths64(const TreeArgs& a, const FastSmem& sm, int64_t b, int w, int lane,
+template <int KC, bool kExact, int RW, bool vec, bool kWait = false>
+__device__ __forceinline__ void expand_depths_wide(const TreeArgs& a, const FastSmem& sm, int64_t b, int w, int lane,
                                                 int& total, const uint32_t* ready = nullptr, uint64_t t0 = 0) {
   static_assert(!(kWait && vec), "waited slabs are loaded word by word");
-  constexpr int KT = 64;
-  constexpr int kQuarter = KT * KT / kK64Waves;  // floats of a slab staged by one wave
+  static_assert(kExact || !(kWait || vec), "waited and vector slabs: K = 64");
+  static_assert(KC == 64 || !kExact, "exact: K = 64");
+  constexpr int kQuarter = KC * KC / kK64Waves;  // most floats of a slab staged by one wave
   const int gamma = a.gamma, W = a.W;
-  const float* gq = a.logq + b * gamma * KT * KT + w * kQuarter;
+  const int K = kExact ? KC : a.K;
+  const int KK = K * K;
+  // Exact: wave w stages one quarter of the slab; else every fourth 64 floats of it.
+  const int s_off = kExact ? w * kQuarter : w * kWave;
+  constexpr int s_step = kExact ? kWave : kK64Waves * kWave;
+  const float* gq = a.logq + b * gamma * KK + s_off;
   float P[kQuarter / kWave];  // this wave's quarter of a slab, in flight
   auto load_slab = [&](int d) {  // slab of depth d (1-based)
-    const float* src = gq + static_cast<int64_t>(d - 1) * KT * KT;
-    if constexpr (kWait) {
+    const float* src = gq + static_cast<int64_t>(d - 1) * KK;
+    if constexpr (!kExact) {
+#pragma unroll
+      for (int i = 0; i < kQuarter / kWave; ++i)
+        if (s_off + i * s_step + lane < KK) P[i] = src[i * s_step + lane];
+    } else if constexpr (kWait) {
       wait_agent_word(ready + (d - 1), sm.fail, t0);
       const uint32_t* u = reinterpret_cast<const uint32_t*>(src);
 #pragma unroll
@@ -570,8 +591,12 @@ __device__ __forceinline__ void expand_depths64(const TreeArgs& a, const FastSme
     }
   };
   auto store_slab = [&](int d) {
-    float* dst = sm.slab + ((d - 1) & 1) * KT * KT + w * kQuarter;
-    if constexpr (vec) {
+    float* dst = sm.slab + ((d - 1) & 1) * KK + s_off;
+    if constexpr (!kExact) {
+#pragma unroll
+      for (int i = 0; i < kQuarter / kWave; ++i)
+        if (s_off + i * s_step + lane < KK) dst[i * s_step + lane] = P[i];
+    } else if constexpr (vec) {
 #pragma unroll
       for (int i = 0; i < kQuarter / (4 * kWave); ++i)
         reinterpret_cast<float4*>(dst)[i * kWave + lane] = make_float4(P[4 * i], P[4 * i + 1], P[4 * i + 2], P[4 * i + 3]);
@@ -581,9 +606,9 @@ __device__ __forceinline__ void expand_depths64(const TreeArgs& a, const FastSme
     }
   };
   uint32_t* s_best = sm.bound;
-  uint32_t* s_cnt = sm.bound + 16;
+  uint32_t* s_cnt = sm.bound + kWideMaxW;
   uint2* surv = reinterpret_cast<uint2*>(sm.xpose);  // [0, ns) survivors, then 16 zeros
-  const int dummy = kFastMaxWK + 16 + lane;
+  const int dummy = W * K + 16 + lane;
   load_slab(1);
   store_slab(1);
   if (gamma > 1) load_slab(2);
@@ -600,7 +625,7 @@ __device__ __forceinline__ void expand_depths64(const TreeArgs& a, const FastSme
       store_slab(d + 1);
       if (d + 2 <= gamma) load_slab(d + 2);
     }
-    const float* slab = sm.slab + ((d - 1) & 1) * KT * KT;
+    const float* slab = sm.slab + ((d - 1) & 1) * KK;
     // F_{d-1}: entry r on lane r (depth 1: the root, score 0, extends through row 0).
     uint32_t pkey = f32_key(0.f), pinfo = 0u;
     if (d > 1 && lane < W) {
@@ -613,11 +638,11 @@ __device__ __forceinline__ void expand_depths64(const TreeArgs& a, const FastSme
       const int r = i * kK64Waves + w;
       const float base = f32_key_value(__builtin_amdgcn_readlane(pkey, r));
       const int row = static_cast<int>(__builtin_amdgcn_readlane(pinfo, r) >> 16);
-      float v = base + slab[row * KT + lane];
+      float v = base + slab[row * K + (kExact || lane < K ? lane : 0)];
       if (with_zeta) v += zeta;
-      key[i] = r < np ? f32_key(v) : 0u;
+      key[i] = r < np && (kExact || lane < K) ? f32_key(v) : 0u;
     }
-    const int n = np * KT;
+    const int n = np * K;
     const int w_d = n < W ? n : W;
     // The bound: the smallest best child over the W parents (np = W from depth 2 on).
     uint32_t kbound = 1u;  // keys of live entries are nonzero
@@ -654,7 +679,7 @@ __device__ __forceinline__ void expand_depths64(const TreeArgs& a, const FastSme
     for (int i = 0; i < RW; ++i) {
       const int r = i * kK64Waves + w;
       const int at = lane_in(sel[i]) ? pos + static_cast<int>(lanes_below(sel[i])) : dummy;
-      surv[at] = make_uint2(~static_cast<uint32_t>(r * KT + lane), key[i]);
+      surv[at] = make_uint2(~static_cast<uint32_t>(r * kWave + lane), key[i]);
       pos += popc(sel[i]);
     }
     if (w == 0) surv[lane < 16 ? ns + lane : dummy] = make_uint2(0u, 0u);
@@ -668,7 +693,7 @@ __device__ __forceinline__ void expand_depths64(const TreeArgs& a, const FastSme
       const int rank = rank_in_stage(surv, ns, order_value(mx, my));
       const bool have = live && rank < w_d;
       const int e = have ? static_cast<int>(~mx) : 0;
-      frontier_store(a, sm, b, w == 0 && j0 == 0 ? lane : kWave, d, w_d, have, rank, my, e >> 6, e & (KT - 1));
+      frontier_store(a, sm, b, w == 0 && j0 == 0 ? lane : kWave, d, w_d, have, rank, my, e >> 6, e & (kWave - 1));
     }
     np = w_d;
     total += w_d;
@@ -678,7 +703,7 @@ __device__ __forceinline__ void expand_depths64(const TreeArgs& a, const FastSme
 
 // Global pruning (Eq. ubtree-pruning), emission and the mask, once the supertree's keys
 // and infos are in s_key / s_info (F_d in rank order at (d - 1) * W + rank) and `total`
-// counts its nodes.  With kCheckFail, a wait of the workgroup that ran out of time marks
+// counts its nodes (KT: K, or 0 to take it from the arguments).  With kCheckFail, a wait of the workgroup that ran out of time marks
 // the sequence with n_nodes = 0 and sets the launch's error word.
 template <int KT, bool kCheckFail>
 __device__ __forceinline__ void finish_tree(const TreeArgs& a, const FastSmem& sm, int64_t b, int lane,
@@ -745,7 +770,7 @@ __device__ __forceinline__ void finish_tree(const TreeArgs& a, const FastSmem& s
       const int c = static_cast<int>(info >> 16);
       const int ps = d == 1 ? 0 : sm.f_slot[(d - 2) * W + p];
       const int s = slot[rb];
-      tok[s] = sm.cids[(d - 1) * KT + c];
+      tok[s] = sm.cids[(d - 1) * (KT != 0 ? KT : a.K) + c];
       par[s] = ps;
       dep[s] = d;
       crk[s] = c;

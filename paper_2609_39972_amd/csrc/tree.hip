@@ -327,7 +327,7 @@ __global__ __launch_bounds__(kWave) void build_tree_kernel(TreeArgs a, int stage
 
 template <int KT, int R>
 __global__ __launch_bounds__(kWave) void build_tree_fast_kernel(TreeArgs a, uint64_t magic_w) {
-  static_assert(KT <= 16, "K = 64 runs build_tree_k64_kernel");
+  static_assert(KT <= 16, "larger K runs build_tree_wide_kernel");
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int lane = threadIdx.x;
   const int64_t b = blockIdx.x;
@@ -355,31 +355,36 @@ __global__ __launch_bounds__(kWave) void build_tree_fast_kernel(TreeArgs a, uint
   fast_search<KT, R, false>(a, sm, b, lane, magic_w);
 }
 
-// K = 64: kK64Waves waves search one sequence together, staging its slabs two depths at a
-// time; wave 0 then prunes, emits the tree and builds the mask.  RW = registers of
-// 64 entries per wave (W <= 4 RW).
-template <int RW>
-__global__ __launch_bounds__(kK64Waves* kWave) void build_tree_k64_kernel(TreeArgs a, uint64_t magic_w) {
+// kK64Waves waves search one sequence together, staging its slabs two depths at a time;
+// wave 0 then prunes, emits the tree and builds the mask.  RW = registers of one parent's
+// children per wave (W <= 4 RW); KC, kExact as in expand_depths_wide.
+template <int KC, bool kExact, int RW>
+__global__ __launch_bounds__(kK64Waves* kWave) void build_tree_wide_kernel(TreeArgs a, uint64_t magic_w) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
   const int lane = static_cast<int>(threadIdx.x) % kWave;
   const int64_t b = blockIdx.x;
   const int gamma = a.gamma;
-  const FastSmem sm = fast_smem(smem_raw, fast_layout(gamma, 64, a.W));
-  const int32_t* gids = a.cand_ids + b * gamma * 64;
-  for (int e = static_cast<int>(threadIdx.x); e < gamma * 64; e += static_cast<int>(blockDim.x)) sm.cids[e] = gids[e];
+  const int K = kExact ? KC : a.K;
+  const FastSmem sm = fast_smem(smem_raw, fast_layout(gamma, K, a.W, true));
+  const int32_t* gids = a.cand_ids + b * gamma * K;
+  for (int e = static_cast<int>(threadIdx.x); e < gamma * K; e += static_cast<int>(blockDim.x)) sm.cids[e] = gids[e];
   // (the first barrier of the expansion publishes the ids)
   int total = 0;
-  if ((reinterpret_cast<uintptr_t>(a.logq) & 15u) == 0)
-    expand_depths64<RW, true>(a, sm, b, w, lane, total);
-  else
-    expand_depths64<RW, false>(a, sm, b, w, lane, total);
+  if constexpr (kExact) {
+    if ((reinterpret_cast<uintptr_t>(a.logq) & 15u) == 0)
+      expand_depths_wide<KC, true, RW, true>(a, sm, b, w, lane, total);
+    else
+      expand_depths_wide<KC, true, RW, false>(a, sm, b, w, lane, total);
+  } else {
+    expand_depths_wide<KC, false, RW, false>(a, sm, b, w, lane, total);
+  }
   if (w != 0) return;
-  finish_tree<64, false>(a, sm, b, lane, magic_w, total);
+  finish_tree<kExact ? KC : 0, false>(a, sm, b, lane, magic_w, total);
 }
 
 // K = 64: selector scores and tree search in one launch (the one-call draft step).
-// Workgroups 0..B-1 search, one per sequence, as build_tree_k64_kernel does.  The other
+// Workgroups 0..B-1 search, one per sequence, as build_tree_wide_kernel does.  The other
 // workgroups compute score slab t (position t / B of sequence t % B, depth-major, so the
 // first positions' slabs come first) on four waves (bigram_split_tile), write it with
 // agent-scope stores, wait until they have completed and set the slab's ready word.  A
@@ -408,14 +413,14 @@ __global__ __launch_bounds__(kK64Waves* kWave) __attribute__((amdgpu_waves_per_e
   if (static_cast<int>(blockIdx.x) < a.B) {
     const int64_t b = blockIdx.x;
     const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-    const FastSmem sm = fast_smem(smem_raw, fast_layout(gamma, 64, a.W));
+    const FastSmem sm = fast_smem(smem_raw, fast_layout(gamma, 64, a.W, true));
     const int32_t* gids = a.cand_ids + b * gamma * 64;
     for (int e = static_cast<int>(threadIdx.x); e < gamma * 64; e += static_cast<int>(blockDim.x))
       sm.cids[e] = gids[e];
     if (threadIdx.x == 0) *sm.fail = 0u;
     __syncthreads();
     int total = 0;
-    expand_depths64<RW, false, true>(a, sm, b, w, lane, total, ready + b * gamma, t0);
+    expand_depths_wide<64, true, RW, false, true>(a, sm, b, w, lane, total, ready + b * gamma, t0);
     // Every wave has passed every wait (each depth ends with a workgroup barrier).
     if (w == 0 && lane < gamma) agent_store_u32(ready + b * gamma + lane, 0u);
     if (w != 0) return;
@@ -539,30 +544,52 @@ hipError_t launch_build_tree(const TreeArgs& a, hipStream_t stream) {
     else                        \
       UBT_FAST_LAUNCH(KK, 8);   \
   } while (0)
-#define UBT_K64_LAUNCH(RW)                                                                                   \
-  do {                                                                                                       \
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&build_tree_k64_kernel<RW>),                     \
-                              hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem));           \
-    hipLaunchKernelGGL((build_tree_k64_kernel<RW>), grid, dim3(kK64Waves * kWave), smem, stream, a, magic_w); \
-  } while (0)
-    if (a.K == 4) {
+    if (a.K == 4)
       UBT_FAST_ROWS(4);
-    } else if (a.K == 8) {
+    else if (a.K == 8)
       UBT_FAST_ROWS(8);
-    } else if (a.K == 16) {
+    else
       UBT_FAST_ROWS(16);
-    } else if (a.W <= 4) {
-      UBT_K64_LAUNCH(1);
-    } else if (a.W <= 8) {
-      UBT_K64_LAUNCH(2);
-    } else if (a.W <= 12) {
-      UBT_K64_LAUNCH(3);
-    } else {
-      UBT_K64_LAUNCH(4);
-    }
-#undef UBT_K64_LAUNCH
 #undef UBT_FAST_ROWS
 #undef UBT_FAST_LAUNCH
+    return hipGetLastError();
+  }
+  if (wide_tree_fits(a.gamma, a.K, a.W)) {
+    const uint64_t magic_w = (0x100000000ull + a.W - 1) / a.W;
+    const size_t smem = fast_layout(a.gamma, a.K, a.W, true).total;
+#define UBT_WIDE_LAUNCH(KC, EX, RW)                                                                           \
+  do {                                                                                                       \
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&build_tree_wide_kernel<KC, EX, RW>),            \
+                              hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem));           \
+    hipLaunchKernelGGL((build_tree_wide_kernel<KC, EX, RW>), grid, dim3(kK64Waves * kWave), smem, stream, a, magic_w); \
+  } while (0)
+#define UBT_WIDE_ROWS(KC, EX)     \
+  do {                            \
+    if (a.W <= 4)                 \
+      UBT_WIDE_LAUNCH(KC, EX, 1); \
+    else if (a.W <= 8)            \
+      UBT_WIDE_LAUNCH(KC, EX, 2); \
+    else if (a.W <= 12)           \
+      UBT_WIDE_LAUNCH(KC, EX, 3); \
+    else if (a.W <= 16)           \
+      UBT_WIDE_LAUNCH(KC, EX, 4); \
+    else if (a.W <= 24)           \
+      UBT_WIDE_LAUNCH(KC, EX, 6); \
+    else if (a.W <= 32)           \
+      UBT_WIDE_LAUNCH(KC, EX, 8); \
+    else                          \
+      UBT_WIDE_LAUNCH(KC, EX, 16); \
+  } while (0)
+    if (a.K == 64)
+      UBT_WIDE_ROWS(64, true);
+    else if (a.K <= 16)
+      UBT_WIDE_ROWS(16, false);
+    else if (a.K <= 32)
+      UBT_WIDE_ROWS(32, false);
+    else
+      UBT_WIDE_ROWS(64, false);
+#undef UBT_WIDE_ROWS
+#undef UBT_WIDE_LAUNCH
     return hipGetLastError();
   }
   const bool stage_slabs = static_cast<int64_t>(a.gamma) * a.K * a.K <= kMaxSlabFloats;
@@ -595,7 +622,7 @@ hipError_t launch_build_tree(const TreeArgs& a, hipStream_t stream) {
 }
 
 bool draft_tree_fused(int feat_dtype, int gamma, int K, int W) {
-  return feat_dtype == 1 && K <= 16 && fast_tree_fits(gamma, K, W);
+  return feat_dtype == 1 && fast_tree_fits(gamma, K, W);
 }
 
 hipError_t launch_draft_tree(const SelectorArgs& s, const TreeArgs& a, hipStream_t stream) {
@@ -635,12 +662,12 @@ hipError_t launch_draft_tree(const SelectorArgs& s, const TreeArgs& a, hipStream
 }
 
 bool draft_tree_k64_fused(int feat_dtype, int gamma, int K, int W) {
-  return feat_dtype == 1 && K == 64 && fast_tree_fits(gamma, K, W);
+  return feat_dtype == 1 && K == 64 && W <= 32 && wide_tree_fits(gamma, K, W);
 }
 
 hipError_t launch_draft_tree_k64(const SelectorArgs& s, const TreeArgs& a, uint32_t* ready, hipStream_t stream) {
   const uint64_t magic_w = (0x100000000ull + a.W - 1) / a.W;
-  const size_t search_smem = fast_layout(a.gamma, 64, a.W).total;
+  const size_t search_smem = fast_layout(a.gamma, 64, a.W, true).total;
   const size_t slab_smem = kSplitPartBytes<4>;
   const size_t smem = search_smem > slab_smem ? search_smem : slab_smem;
   const int slabs = a.B * a.gamma;
@@ -658,8 +685,12 @@ hipError_t launch_draft_tree_k64(const SelectorArgs& s, const TreeArgs& a, uint3
     UBT_K64_DRAFT(2);
   else if (a.W <= 12)
     UBT_K64_DRAFT(3);
-  else
+  else if (a.W <= 16)
     UBT_K64_DRAFT(4);
+  else if (a.W <= 24)
+    UBT_K64_DRAFT(6);
+  else
+    UBT_K64_DRAFT(8);
 #undef UBT_K64_DRAFT
   return hipGetLastError();
 }

@@ -77,7 +77,7 @@ struct SelectorArgs {
 // resident search: K in {4, 8, 16}, W <= 64, W*K <= 512, gamma*W <= 1024).
 bool draft_tree_fused(int feat_dtype, int gamma, int K, int W);
 // True if draft_tree_k64_kernel handles the shape (bf16 features, K = 64 and the
-// four-wave search: W*64 <= 1024, W <= 64, gamma*W <= 1024).
+// four-wave search: W <= 32, gamma*W <= 1024).
 bool draft_tree_k64_fused(int feat_dtype, int gamma, int K, int W);
 // Selector scores and the K = 64 search in one launch; ready: B*gamma zero words, left zero.
 hipError_t launch_draft_tree_k64(const SelectorArgs& s, const TreeArgs& a, uint32_t* ready, hipStream_t stream);

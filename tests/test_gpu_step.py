@@ -217,6 +217,8 @@ def _custom(cfg: int, **kw) -> synth.Workload:
     dict(B=3, L=2, V=3000, K=64, W=4, r=64, budget=20),     # one position (no slab two depths ahead)
     dict(B=2, L=17, V=5000, K=64, W=16, r=48, budget=120),  # W = 16, 16 positions, fewer k-steps than waves
     dict(B=2, L=9, V=6000, K=64, W=16, r=32, budget=16),    # W = budget
+    dict(B=2, L=9, V=6000, K=64, W=21, r=32, budget=90),    # W > 16: six registers of children per wave
+    dict(B=3, L=5, V=6000, K=64, W=32, r=64, budget=128),
 ])
 def test_step_shapes(kw):
     w = _custom(300, **kw)

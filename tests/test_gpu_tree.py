@@ -112,3 +112,16 @@ def test_tree_mask_matches_fused_and_oracle():
     torch.cuda.synchronize()
     assert np.array_equal(m, oracle.tree_mask(parent, n_nodes))
     del to_np
+
+
+@pytest.mark.parametrize("tie_frac,levels", [(0.0, 64), (0.8, 4)])
+@pytest.mark.parametrize("B,gamma,K,W,budget", [
+    # The four-wave search: each class of K at its edges (1, 2, 15, 17, 31 .. 33, 63, 64), W at
+    # the edges of the register counts (4, 5, 8, 9, 12, 13, 16, 17, 24, 25, 32, 33, 64),
+    # gamma = 1, gamma * W = 1024, and both ways to read a slab at K = 64
+    (2, 1, 10, 10, 20), (3, 5, 1, 4, 8), (2, 9, 2, 5, 30), (2, 11, 10, 10, 48), (2, 7, 15, 13, 60),
+    (2, 6, 17, 17, 100), (2, 15, 24, 24, 128), (2, 5, 31, 25, 128), (2, 32, 32, 32, 255), (2, 8, 33, 9, 40),
+    (1, 16, 63, 64, 255), (2, 16, 64, 64, 255), (3, 7, 64, 33, 100), (2, 20, 64, 20, 100), (2, 6, 16, 33, 200),
+])
+def test_four_wave_search(B, gamma, K, W, budget, tie_frac, levels):
+    _compare(B, gamma, K, W, budget, seed=K * 100 + W, tie_frac=tie_frac, levels=levels)
