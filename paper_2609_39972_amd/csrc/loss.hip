@@ -42,21 +42,25 @@ __device__ __forceinline__ float logit_at<uint16_t>(const uint16_t* p, int64_t i
 __device__ __forceinline__ bool valid_token(int32_t y, int64_t V) { return y >= 0 && y < V; }
 
 // grad[row][v] = beta * exp(u[row][v] - lse[row]) for valid rows, 0 for invalid ones.
-// Grid: (B * gamma rows, chunks of kDenseThreads * 8 * kDenseUnroll elements).
+// Grid: B * gamma rows x chunks of kDenseThreads * 8 * kDenseUnroll elements, the chunks of a
+// row next to each other: workgroups that run together then stream neighbouring memory (480
+// rows of 151,936 bf16: 89 us, 4.9 TB/s, the rate of a large copy; with the rows next to
+// each other 93-96 us; nontemporal loads and stores 104-115 us).
 template <typename T, bool kVec>
-__global__ __launch_bounds__(kDenseThreads) void kl_dense_kernel(const T* __restrict__ logits, int gamma, int64_t V,
+__global__ __launch_bounds__(kDenseThreads) void kl_dense_kernel(const T* __restrict__ logits, int gamma, int chunks,
+                                                                 int64_t V,
                                                                  int64_t stride_b, int64_t stride_i,
                                                                  const float* __restrict__ lse,
                                                                  const int32_t* __restrict__ y_star, float beta,
                                                                  float* __restrict__ grad) {
-  const int64_t row = blockIdx.x;
+  const int64_t row = blockIdx.x / chunks;
   const int64_t b = row / gamma, i = row - b * gamma;
   const T* u = logits + b * stride_b + i * stride_i;
   float* g = grad + row * V;
   const bool valid = valid_token(y_star[row], V);
   const float shift = valid ? lse[row] * kLog2e : 0.f;
   constexpr int64_t kChunk = static_cast<int64_t>(kDenseThreads) * 8 * kDenseUnroll;
-  const int64_t c0 = static_cast<int64_t>(blockIdx.y) * kChunk;
+  const int64_t c0 = (blockIdx.x - row * chunks) * kChunk;
   if (kVec) {
     // Whole 8-element groups (V % 8 == 0 and 16-byte aligned rows).
     float x[kDenseUnroll][8];
@@ -175,6 +179,7 @@ __global__ __launch_bounds__(kWave) void kl_position_kernel(LossArgs p) {
     const F* g = static_cast<const F*>(p.gate) + row * p.r;
     const F* ph = static_cast<const F*>(p.phi) + static_cast<int64_t>(a) * p.r;
     const F* ps = static_cast<const F*>(p.psi) + c * p.r;
+#pragma unroll 4
     for (int k = 0; k < p.r; k += 8) {
       float gv[8], pv[8], sv[8];
       feat8<F>(g, k, gv);
@@ -232,13 +237,14 @@ template <typename T, typename F>
 void launch_typed(const LossArgs& p, int rows, bool vec, hipStream_t stream) {
   if (p.grad) {
     constexpr int64_t kChunk = static_cast<int64_t>(kDenseThreads) * 8 * kDenseUnroll;
-    const dim3 grid(static_cast<unsigned>(rows), static_cast<unsigned>((p.V + kChunk - 1) / kChunk));
+    const int chunks = static_cast<int>((p.V + kChunk - 1) / kChunk);
+    const dim3 grid(static_cast<unsigned>(rows) * static_cast<unsigned>(chunks));
     const T* u = static_cast<const T*>(p.logits);
     if (vec)
-      hipLaunchKernelGGL((kl_dense_kernel<T, true>), grid, dim3(kDenseThreads), 0, stream, u, p.gamma, p.V,
+      hipLaunchKernelGGL((kl_dense_kernel<T, true>), grid, dim3(kDenseThreads), 0, stream, u, p.gamma, chunks, p.V,
                          p.stride_b, p.stride_i, p.lse, p.y_star, p.beta, p.grad);
     else
-      hipLaunchKernelGGL((kl_dense_kernel<T, false>), grid, dim3(kDenseThreads), 0, stream, u, p.gamma, p.V,
+      hipLaunchKernelGGL((kl_dense_kernel<T, false>), grid, dim3(kDenseThreads), 0, stream, u, p.gamma, chunks, p.V,
                          p.stride_b, p.stride_i, p.lse, p.y_star, p.beta, p.grad);
   }
   hipLaunchKernelGGL((kl_position_kernel<T, F>), dim3(static_cast<unsigned>(rows)), dim3(kWave), 0, stream, p);
