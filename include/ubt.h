@@ -108,6 +108,17 @@ ubt_status_t ubt_topk(const void* logits, ubt_dtype_t dt, int B, int gamma, int6
                       int64_t stride_b, int64_t stride_i, int K, int32_t* cand_ids,
                       float* cand_logit, float* cand_logprob, float* lse, hipStream_t stream);
 
+/* ubt_topk_split -- the same call with a workspace (256-byte aligned device memory, contents
+ * never read before they are written; calls that share it must not overlap).  With at least
+ * ubt_topk_workspace_bytes(...) bytes (0: nothing to gain) few rows are cut over several
+ * workgroups and merged by a second kernel: the same candidates, lse and log-probabilities
+ * to fp32 rounding.  With NULL or less it is ubt_topk.  UBT_ERR_WORKSPACE: misaligned. */
+size_t ubt_topk_workspace_bytes(int B, int gamma, int64_t V, int K, ubt_dtype_t dt);
+ubt_status_t ubt_topk_split(const void* logits, ubt_dtype_t dt, int B, int gamma, int64_t V,
+                            int64_t stride_b, int64_t stride_i, int K, int32_t* cand_ids,
+                            float* cand_logit, float* cand_logprob, float* lse, void* workspace,
+                            size_t ws_bytes, hipStream_t stream);
+
 /* ------------------------------------------------------------------------------------
  * ubt_lm_head_topk -- the LM-head projection followed by ubt_topk's outputs, without
  * writing the logits.  Background, "DFlash & DFlash 2": the proposer's hidden state h_i
@@ -298,7 +309,10 @@ ubt_status_t ubt_draft_step(const void* logits, ubt_dtype_t dt, int B, int gamma
  * 16-byte aligned then take the one launch too (with at least
  * ubt_draft_step_workspace_bytes(...) bytes), and so does K = 64 with 16 < W <= 32 its
  * selector + search launch.  With a missing, short or misaligned workspace those shapes run
- * the separate kernels; everything else, errors included, is ubt_draft_step's. */
+ * the separate kernels; everything else, errors included, is ubt_draft_step's.
+ * ubt_draft_step_full_workspace_bytes(...) adds room for ubt_topk_split's workspace, which the
+ * shapes that run a separate sweep then use. */
+size_t ubt_draft_step_full_workspace_bytes(int B, int gamma, int64_t V, int K, ubt_dtype_t dt);
 ubt_status_t ubt_draft_step_full(const void* logits, ubt_dtype_t dt, int B, int gamma, int64_t V,
                                  int64_t stride_b, int64_t stride_i, int K, const void* phi_tab,
                                  const void* psi_tab, const void* gate, ubt_dtype_t feat_dt, int r,

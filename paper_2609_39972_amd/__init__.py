@@ -37,8 +37,8 @@ STATUS = {0: "UBT_OK", 1: "UBT_ERR_NULL", 2: "UBT_ERR_SHAPE", 3: "UBT_ERR_VALUE"
           5: "UBT_ERR_WORKSPACE", 6: "UBT_ERR_HIP"}
 
 # Every symbol include/ubt.h declares.
-EXPORTS = ("ubt_status_str", "ubt_abi_version", "ubt_last_hip_error", "ubt_topk",
-           "ubt_lm_head_topk_workspace_bytes", "ubt_lm_head_topk_full_workspace_bytes", "ubt_lm_head_topk", "ubt_bigram_scores", "ubt_build_tree", "ubt_draft_tree", "ubt_draft_step_workspace_bytes",
+EXPORTS = ("ubt_status_str", "ubt_abi_version", "ubt_last_hip_error", "ubt_topk", "ubt_topk_split", "ubt_topk_workspace_bytes",
+           "ubt_lm_head_topk_workspace_bytes", "ubt_lm_head_topk_full_workspace_bytes", "ubt_lm_head_topk", "ubt_bigram_scores", "ubt_build_tree", "ubt_draft_tree", "ubt_draft_step_workspace_bytes", "ubt_draft_step_full_workspace_bytes",
            "ubt_draft_step", "ubt_draft_step_full", "ubt_draft_step_noalloc", "ubt_edge_scores", "ubt_build_tree_best_first", "ubt_tree_mask", "ubt_tree_attention", "ubt_tree_attention_split", "ubt_tree_attention_workspace_bytes", "ubt_verify_accept", "ubt_commit_kv",
            "ubt_tree_kl_loss")
 
@@ -71,6 +71,9 @@ def lib() -> ctypes.CDLL:
         L.ubt_abi_version.restype = _i32
         L.ubt_last_hip_error.restype = _i32
         L.ubt_topk.argtypes = [_p, _i32, _i32, _i32, _i64, _i64, _i64, _i32, _p, _p, _p, _p, _p]
+        L.ubt_topk_split.argtypes = [*L.ubt_topk.argtypes[:-1], _p, ctypes.c_size_t, _p]
+        L.ubt_topk_workspace_bytes.argtypes = [_i32, _i32, _i64, _i32, _i32]
+        L.ubt_topk_workspace_bytes.restype = ctypes.c_size_t
         L.ubt_lm_head_topk_workspace_bytes.argtypes = [_i32, _i32, _i64, _i32]
         L.ubt_lm_head_topk_workspace_bytes.restype = ctypes.c_size_t
         L.ubt_lm_head_topk_full_workspace_bytes.argtypes = [_i32, _i32, _i64, _i32]
@@ -85,6 +88,8 @@ def lib() -> ctypes.CDLL:
         L.ubt_tree_mask.argtypes = [_p, _p, _i32, _i32, _p, _p]
         L.ubt_draft_step_workspace_bytes.argtypes = [_i32, _i32, _i64, _i32, _i32]
         L.ubt_draft_step_workspace_bytes.restype = ctypes.c_size_t
+        L.ubt_draft_step_full_workspace_bytes.argtypes = [_i32, _i32, _i64, _i32, _i32]
+        L.ubt_draft_step_full_workspace_bytes.restype = ctypes.c_size_t
         L.ubt_draft_step.argtypes = [_p, _i32, _i32, _i32, _i64, _i64, _i64, _i32, _p, _p, _p, _i32, _i32, _p, _p,
                                      _p, _i32, _i32, _f32, _p, _p, _p, _p, _p, _p, _p, _p, _p, _p, _p, _p, _p,
                                      ctypes.c_size_t, _p]
@@ -104,7 +109,7 @@ def lib() -> ctypes.CDLL:
         L.ubt_commit_kv.argtypes = [_p, _p, _p, _p, _p, _p, _p, _i32, _i32, _i32, _i32, _i64, _p]
         L.ubt_tree_kl_loss.argtypes = [_p, _i32, _i32, _i32, _i64, _i64, _i64, _p, _p, _p, _i32, _p, _i64, _i64, _p,
                                        _p, _p, _p, _p, _i32, _i32, _p, _p, _f32, _f32, _p, _p, _p, _p, _p, _p]
-        for f in (L.ubt_topk, L.ubt_lm_head_topk, L.ubt_bigram_scores, L.ubt_build_tree, L.ubt_draft_tree, L.ubt_tree_mask,
+        for f in (L.ubt_topk, L.ubt_topk_split, L.ubt_lm_head_topk, L.ubt_bigram_scores, L.ubt_build_tree, L.ubt_draft_tree, L.ubt_tree_mask,
                   L.ubt_draft_step, L.ubt_draft_step_full, L.ubt_draft_step_noalloc, L.ubt_edge_scores, L.ubt_build_tree_best_first, L.ubt_tree_attention, L.ubt_tree_attention_split, L.ubt_verify_accept, L.ubt_commit_kv, L.ubt_tree_kl_loss):
             f.restype = _i32
         _lib = L
@@ -156,9 +161,18 @@ def _contig(t: torch.Tensor, name: str) -> torch.Tensor:
     return t
 
 
-def topk(logits: torch.Tensor, K: int, out: dict | None = None, with_logprob: bool = True, stream=None) -> dict:
+def topk_workspace(B: int, gamma: int, V: int, K: int, dtype=torch.bfloat16, device="cuda") -> torch.Tensor | None:
+    """A workspace for :func:`topk` (its contents are never read before they are written), or
+    None when the shape needs none."""
+    n = lib().ubt_topk_workspace_bytes(B, gamma, V, K, UBT_BF16 if dtype == torch.bfloat16 else UBT_F32)
+    return torch.empty(n, dtype=torch.uint8, device=device) if n else None
+
+
+def topk(logits: torch.Tensor, K: int, out: dict | None = None, with_logprob: bool = True, stream=None,
+         workspace: torch.Tensor | None = None) -> dict:
     """Top-K candidates and softmax statistics of ``logits [B, gamma, V]`` (any strides with
-    unit stride along V; e.g. ``u[:, 1:, :]`` of a ``[B, L, V]`` block)."""
+    unit stride along V; e.g. ``u[:, 1:, :]`` of a ``[B, L, V]`` block).  ``workspace`` from
+    :func:`topk_workspace` saves the call's own scratch allocation."""
     _need_gpu(logits)
     if logits.dim() != 3 or logits.stride(2) != 1:
         raise ValueError("logits must be [B, gamma, V] with unit stride along V")
@@ -170,9 +184,12 @@ def topk(logits: torch.Tensor, K: int, out: dict | None = None, with_logprob: bo
                    cand_logit=torch.empty(B, gamma, K, dtype=torch.float32, device=dev),
                    cand_logprob=torch.empty(B, gamma, K, dtype=torch.float32, device=dev) if with_logprob else None,
                    lse=torch.empty(B, gamma, dtype=torch.float32, device=dev))
-    st = lib().ubt_topk(_ptr(logits), code, B, gamma, V, logits.stride(0), logits.stride(1), K,
-                        _ptr(out["cand_ids"]), _ptr(out["cand_logit"]), _ptr(out.get("cand_logprob")),
-                        _ptr(out.get("lse")), _stream(stream))
+    if workspace is None:
+        workspace = _scratch(lib().ubt_topk_workspace_bytes(B, gamma, V, K, code), dev, stream)
+    st = lib().ubt_topk_split(_ptr(logits), code, B, gamma, V, logits.stride(0), logits.stride(1), K,
+                              _ptr(out["cand_ids"]), _ptr(out["cand_logit"]), _ptr(out.get("cand_logprob")),
+                              _ptr(out.get("lse")), _ptr(workspace), 0 if workspace is None else workspace.numel(),
+                              _stream(stream))
     _check("ubt_topk", st)
     return out
 
@@ -379,7 +396,7 @@ def draft_step_workspace(B: int, gamma: int, V: int, K: int, dtype=torch.bfloat1
     call resets the counters it uses, so one workspace serves consecutive calls on one
     stream."""
     code = UBT_BF16 if dtype == torch.bfloat16 else UBT_F32
-    n = lib().ubt_draft_step_workspace_bytes(B, gamma, V, K, code)
+    n = lib().ubt_draft_step_full_workspace_bytes(B, gamma, V, K, code)
     if n == 0:
         raise ValueError("invalid shape for ubt_draft_step")
     ws = torch.zeros(n, dtype=torch.uint8, device=device)
@@ -593,6 +610,7 @@ class DraftStep:
         self.fused = fused and not with_delta and not debug
         self.one_call = one_call and self.fused
         self.workspace = draft_step_workspace(B, gamma, V, K, logit_dtype, dev) if self.one_call else None
+        self.topk_workspace = None if self.one_call else topk_workspace(B, gamma, V, K, logit_dtype, dev)
         self.logit_dtype_code = UBT_BF16 if logit_dtype == torch.bfloat16 else UBT_F32
 
     def outputs(self) -> dict:
@@ -618,7 +636,7 @@ class DraftStep:
             draft_step(logits, self.phi, self.psi, self.gate, self.anchor, self.alpha, self.lam, self.K, self.W,
                        self.budget, self.zeta, self.workspace, self.cand, self.sel["logq"], self.tree, stream=stream)
             return {**self.cand, **self.sel, **self.tree}
-        topk(logits, self.K, self.cand, stream=stream)
+        topk(logits, self.K, self.cand, stream=stream, workspace=self.topk_workspace)
         if self.fused:
             draft_tree(self.phi, self.psi, self.gate, self.anchor, self.cand["cand_ids"], self.cand["cand_logit"],
                        self.alpha, self.lam, self.W, self.budget, self.zeta, self.sel["logq"], self.tree,

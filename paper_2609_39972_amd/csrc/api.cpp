@@ -92,9 +92,16 @@ int ubt_abi_version(void) { return UBT_ABI_VERSION; }
 
 int ubt_last_hip_error(void) { return g_last_hip_error; }
 
-ubt_status_t ubt_topk(const void* logits, ubt_dtype_t dt, int B, int gamma, int64_t V, int64_t stride_b,
-                      int64_t stride_i, int K, int32_t* cand_ids, float* cand_logit, float* cand_logprob, float* lse,
-                      hipStream_t stream) {
+size_t ubt_topk_workspace_bytes(int B, int gamma, int64_t V, int K, ubt_dtype_t dt) {
+  if (B < 1 || gamma < 1 || gamma > UBT_MAX_GAMMA || K < 1 || K > UBT_MAX_K || V < K || V >= (int64_t(1) << 31) ||
+      !valid_dtype(dt))
+    return 0;
+  return ubt::topk_workspace_bytes(B, gamma, V, K, dt == UBT_BF16 ? 1 : 0);
+}
+
+ubt_status_t ubt_topk_split(const void* logits, ubt_dtype_t dt, int B, int gamma, int64_t V, int64_t stride_b,
+                            int64_t stride_i, int K, int32_t* cand_ids, float* cand_logit, float* cand_logprob,
+                            float* lse, void* workspace, size_t ws_bytes, hipStream_t stream) {
   if (!logits || !cand_ids || !cand_logit) return UBT_ERR_NULL;
   if (!valid_dtype(dt)) return UBT_ERR_VALUE;
   if (B < 1 || gamma < 1 || gamma > UBT_MAX_GAMMA || K < 1 || K > UBT_MAX_K || V < K || V >= (int64_t(1) << 31))
@@ -102,10 +109,18 @@ ubt_status_t ubt_topk(const void* logits, ubt_dtype_t dt, int B, int gamma, int6
   if (stride_i < V || stride_b < static_cast<int64_t>(gamma) * stride_i) return UBT_ERR_SHAPE;
   if (static_cast<int64_t>(B) * gamma > 0x7FFFFFFF) return UBT_ERR_SHAPE;
   if (V * (dt == UBT_BF16 ? 2 : 4) >= (int64_t(1) << 32)) return UBT_ERR_SHAPE;  // a row is one buffer range
+  if (workspace && (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return UBT_ERR_WORKSPACE;
   const int64_t es = dt == UBT_BF16 ? 2 : 4;
   const bool aligned = aligned16(logits) && (stride_b * es) % 16 == 0 && (stride_i * es) % 16 == 0;
   return hip_status(ubt::launch_topk(logits, static_cast<int>(dt), aligned, B, gamma, V, stride_b, stride_i, K,
-                                     cand_ids, cand_logit, cand_logprob, lse, stream));
+                                     cand_ids, cand_logit, cand_logprob, lse, workspace, ws_bytes, stream));
+}
+
+ubt_status_t ubt_topk(const void* logits, ubt_dtype_t dt, int B, int gamma, int64_t V, int64_t stride_b,
+                      int64_t stride_i, int K, int32_t* cand_ids, float* cand_logit, float* cand_logprob, float* lse,
+                      hipStream_t stream) {
+  return ubt_topk_split(logits, dt, B, gamma, V, stride_b, stride_i, K, cand_ids, cand_logit, cand_logprob, lse,
+                        nullptr, 0, stream);
 }
 
 size_t ubt_lm_head_topk_workspace_bytes(int M, int d, int64_t V, int K) {
@@ -213,6 +228,11 @@ size_t ubt_draft_step_workspace_bytes(int B, int gamma, int64_t V, int K, ubt_dt
   return ubt::step_workspace_bytes(B, gamma, V, K, dt == UBT_BF16 ? 1 : 0);
 }
 
+size_t ubt_draft_step_full_workspace_bytes(int B, int gamma, int64_t V, int K, ubt_dtype_t dt) {
+  const size_t need = ubt_draft_step_workspace_bytes(B, gamma, V, K, dt);
+  return need == 0 ? 0 : need + ubt::topk_workspace_bytes(B, gamma, V, K, dt == UBT_BF16 ? 1 : 0);
+}
+
 }  // extern "C"
 
 namespace {
@@ -262,8 +282,17 @@ ubt_status_t draft_step_impl(const void* logits, ubt_dtype_t dt, int B, int gamm
        workspace_bytes < ubt::step_workspace_bytes(B, gamma, V, K, static_cast<int>(dt))))
     one_launch = false;
   if (!one_launch) {
+    // A full workspace has room for the cut sweep, at its end: far from the words at its start
+    // that must be zero between calls.
+    void* sweep_ws = nullptr;
+    size_t sweep_bytes = ubt::topk_workspace_bytes(B, gamma, V, K, static_cast<int>(dt));
+    if (full && workspace && (reinterpret_cast<uintptr_t>(workspace) & 255u) == 0 && sweep_bytes != 0 &&
+        workspace_bytes >= ubt::step_workspace_bytes(B, gamma, V, K, static_cast<int>(dt)) + sweep_bytes)
+      sweep_ws = static_cast<char*>(workspace) + (workspace_bytes - sweep_bytes) / 256 * 256;
+    else
+      sweep_bytes = 0;
     st = hip_status(ubt::launch_topk(logits, static_cast<int>(dt), aligned, B, gamma, V, stride_b, stride_i, K,
-                                     cand_ids, cand_logit, cand_logprob, lse, stream));
+                                     cand_ids, cand_logit, cand_logprob, lse, sweep_ws, sweep_bytes, stream));
     if (st != UBT_OK) return st;
     // K = 64: the selector and the search in one launch when a workspace is at hand.
     if (ubt::draft_step_k64(static_cast<int>(feat_dt), B, gamma, K, W) && (full || W <= 16)) {

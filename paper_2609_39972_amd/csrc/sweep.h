@@ -581,6 +581,12 @@ struct RowOut {
   float* cand_logprob;
   float* lse;
   bool coherent;
+  float* row_max = nullptr;  // given: the row's maximum, and `lse` receives the sum of exp(u - max) instead
+  __device__ __forceinline__ void put_stats(int64_t row, float m, float e, float l) const {
+    if (!lse) return;
+    put(lse + row, __float_as_uint(row_max ? e : l));
+    if (row_max) put(row_max + row, __float_as_uint(m));
+  }
   template <typename P>
   __device__ __forceinline__ void put(P* p, uint32_t bits) const {
     uint32_t* q = reinterpret_cast<uint32_t*>(p);
@@ -833,7 +839,7 @@ __device__ __forceinline__ void sweep_row(RowLdsT<MW>& lds, const T* __restrict_
     out.put(out.cand_logit + o, __float_as_uint(v));
     if (out.cand_logprob) out.put(out.cand_logprob + o, __float_as_uint(v - l));
   }
-  if (lane == 0 && out.lse) out.put(out.lse + row, __float_as_uint(l));
+  if (lane == 0) out.put_stats(row, m, e, l);
 }
 
 

@@ -295,7 +295,7 @@ __device__ __forceinline__ void sweep_row_big(BigRowLds& lds, const T* __restric
       if (out.cand_logprob) out.put(out.cand_logprob + o, __float_as_uint(v - l));
     }
   }
-  if (threadIdx.x == 0 && out.lse) out.put(out.lse + row, __float_as_uint(l));
+  if (threadIdx.x == 0) out.put_stats(row, m, e, l);
 }
 
 }  // namespace

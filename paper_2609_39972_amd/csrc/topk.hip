@@ -32,6 +32,153 @@ __global__ __launch_bounds__(kWave* kWaves, 4) void topk_row_kernel(const T* __r
   }
 }
 
+// ---- few rows: each row cut over several workgroups -----------------------------------
+//
+// One workgroup per row leaves most compute units idle when there are few rows.  A chunk's
+// workgroup runs the same sweep on its elements and leaves its maximum, sum of exponentials
+// and sorted top K in the workspace; the merge kernel combines them in chunk order.
+constexpr int kSplitMaxChunks = 8;
+constexpr int kMergeThreads = kSplitMaxChunks * 64;  // one per chunk candidate
+
+struct SplitArgs {
+  int chunks;
+  int64_t len;        // elements per chunk, whole tiles; the last chunk takes the rest
+  int32_t* ids;       // [rows][chunks][K] sorted, ids relative to the chunk
+  float* logit;       // [rows][chunks][K]
+  float* sum;         // [rows][chunks]
+  float* row_max;     // [rows][chunks]
+};
+
+template <typename T, bool kAligned, bool kBig>
+__global__ __launch_bounds__(kWave* kWaves, 4) void topk_chunk_kernel(const T* __restrict__ logits, int gamma,
+                                                                      int64_t V, int64_t stride_b, int64_t stride_i,
+                                                                      int K, SplitArgs p) {
+  const int64_t rc = blockIdx.x;
+  const int64_t row = rc / p.chunks;
+  const int64_t c0 = (rc - row * p.chunks) * p.len;
+  const int64_t b = row / gamma, i = row - b * gamma;
+  const int64_t len = rc % p.chunks == p.chunks - 1 ? V - c0 : p.len;
+  const T* rp = logits + b * stride_b + i * stride_i + c0;
+  const RowOut out{p.ids, p.logit, nullptr, p.sum, false, p.row_max};
+  if constexpr (kBig) {
+    __shared__ BigRowLds lds;
+    sweep_row_big<T, kAligned>(lds, rp, len, K, rc, out);
+  } else {
+    __shared__ RowLds lds;
+    sweep_row<T, kAligned, kWaves, false>(lds, rp, len, K, rc, out);
+  }
+}
+
+// One workgroup per row: a chunk candidate's rank is its place in its own list plus, for
+// every other list, the entries above it (binary search in the sorted list).
+template <typename T>
+__global__ __launch_bounds__(kMergeThreads) void topk_merge_kernel(SplitArgs p, int K, int32_t* __restrict__ cand_ids,
+                                                                   float* __restrict__ cand_logit,
+                                                                   float* __restrict__ cand_logprob,
+                                                                   float* __restrict__ lse) {
+  __shared__ uint64_t ord[kMergeThreads];
+  const int t = static_cast<int>(threadIdx.x);
+  const int64_t row = blockIdx.x;
+  const int C = p.chunks;
+  const bool on = t < C * K;
+  const int c = on ? t / K : 0, e = on ? t - c * K : 0;
+  float v = 0.f;
+  uint32_t id = 0u;
+  uint64_t mine = 0ull;
+  if (on) {
+    const int64_t o = row * C * K + t;
+    id = static_cast<uint32_t>(p.ids[o] + c * p.len);
+    v = p.logit[o];
+    mine = cand_order(Traits<T>::key_value(v), id);
+  }
+  float m = neg_inf(), s = 0.f;
+  float cm[kSplitMaxChunks], cs[kSplitMaxChunks];
+#pragma unroll
+  for (int j = 0; j < kSplitMaxChunks; ++j) {
+    cm[j] = j < C ? p.row_max[row * C + j] : neg_inf();
+    cs[j] = j < C ? p.sum[row * C + j] : 0.f;
+  }
+  if (on) ord[t] = mine;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kSplitMaxChunks; ++j) m = fmaxf(m, cm[j]);
+#pragma unroll
+  for (int j = 0; j < kSplitMaxChunks; ++j)
+    if (cm[j] != neg_inf()) s += cs[j] * fast_exp2((cm[j] - m) * kLog2e);
+  const float l = m == neg_inf() ? neg_inf() : m + fast_log2(s) * kLn2;
+  if (t == 0 && lse) lse[row] = l;
+  if (!on) return;
+  int lo[kSplitMaxChunks];  // entries of list j known to be above mine
+#pragma unroll
+  for (int j = 0; j < kSplitMaxChunks; ++j) lo[j] = 0;
+  for (int step = 64; step > 0; step >>= 1) {
+#pragma unroll
+    for (int j = 0; j < kSplitMaxChunks; ++j)
+      if (j < C && lo[j] + step <= K && ord[j * K + lo[j] + step - 1] > mine) lo[j] += step;
+  }
+  int rank = e;
+#pragma unroll
+  for (int j = 0; j < kSplitMaxChunks; ++j) rank += j != c ? lo[j] : 0;
+  if (rank < K) {
+    const int64_t o = row * K + rank;
+    cand_ids[o] = static_cast<int32_t>(id);
+    cand_logit[o] = v;
+    if (cand_logprob) cand_logprob[o] = v - l;
+  }
+}
+
+size_t up256(size_t n) { return (n + 255) & ~static_cast<size_t>(255); }
+
+struct SplitPlan {
+  int chunks;  // 1: not cut
+  int64_t len;
+  size_t ids, logit, sum, row_max, total;
+};
+
+// Rows are cut when there are at most 32 of at least 64 tiles (131,072 bf16 elements).  A
+// chunk keeps a row's start and selection (about 10 us at K = 64) and the merge adds 5 us, so
+// only a long row has enough streaming to share out; with more rows the chunks of one compute
+// unit queue up.  15 rows of 151,936 bf16: whole 22.6 us, cut 18.1 us at K = 64, 17.5 and 14.3
+// us at K = 16; 60 rows 23.2 and 22.3; 240 rows 24.1 and 28.1; 15 rows of 50,000 13.9 and 16.2.
+constexpr int kSplitMaxRows = 32, kSplitMinTiles = 64;
+
+SplitPlan split_plan(int64_t rows, int64_t V, int K, int dtype) {
+  SplitPlan p{};
+  p.chunks = 1;
+  const int64_t tile = static_cast<int64_t>(kSubGroups) * kWave * (dtype == 1 ? 8 : 4);
+  const int64_t tiles = (V + tile - 1) / tile;
+  if (rows > kSplitMaxRows || tiles < kSplitMinTiles) return p;
+  int64_t c = kSplitMaxChunks;
+  p.len = (tiles + c - 1) / c * tile;
+  c = (V + p.len - 1) / p.len;
+  if (V - (c - 1) * p.len < kWave) --c;  // a remainder of fewer than 64 >= K elements joins the chunk before it
+  p.chunks = static_cast<int>(c);
+  const size_t n = static_cast<size_t>(rows) * c;
+  p.ids = 0;
+  p.logit = p.ids + up256(n * K * sizeof(int32_t));
+  p.sum = p.logit + up256(n * K * sizeof(float));
+  p.row_max = p.sum + up256(n * sizeof(float));
+  p.total = p.row_max + up256(n * sizeof(float));
+  return p;
+}
+
+template <typename T, bool kAligned>
+void launch_split(const void* logits, int B, int gamma, int64_t V, int64_t stride_b, int64_t stride_i, int K,
+                  int32_t* cand_ids, float* cand_logit, float* cand_logprob, float* lse, const SplitArgs& p,
+                  hipStream_t stream) {
+  const int64_t rows = static_cast<int64_t>(B) * gamma;
+  const dim3 grid(static_cast<unsigned>(rows * p.chunks)), block(kWave * kWaves);
+  if (K > 16)
+    hipLaunchKernelGGL((topk_chunk_kernel<T, kAligned, true>), grid, block, 0, stream, static_cast<const T*>(logits),
+                       gamma, V, stride_b, stride_i, K, p);
+  else
+    hipLaunchKernelGGL((topk_chunk_kernel<T, kAligned, false>), grid, block, 0, stream, static_cast<const T*>(logits),
+                       gamma, V, stride_b, stride_i, K, p);
+  const int threads = (p.chunks * K + kWave - 1) / kWave * kWave;
+  hipLaunchKernelGGL((topk_merge_kernel<T>), dim3(static_cast<unsigned>(rows)), dim3(static_cast<unsigned>(threads)),
+                     0, stream, p, K, cand_ids, cand_logit, cand_logprob, lse);
+}
+
 template <typename T, bool kAligned>
 void launch_typed(const void* logits, int B, int gamma, int64_t V, int64_t stride_b, int64_t stride_i, int K,
                   int32_t* cand_ids, float* cand_logit, float* cand_logprob, float* lse, hipStream_t stream) {
@@ -48,11 +195,43 @@ void launch_typed(const void* logits, int B, int gamma, int64_t V, int64_t strid
 
 }  // namespace
 
+size_t topk_workspace_bytes(int B, int gamma, int64_t V, int K, int dtype) {
+  return split_plan(static_cast<int64_t>(B) * gamma, V, K, dtype).total;
+}
+
 hipError_t launch_topk(const void* logits, int dtype, bool aligned, int B, int gamma, int64_t V, int64_t stride_b,
                        int64_t stride_i, int K, int32_t* cand_ids, float* cand_logit, float* cand_logprob, float* lse,
-                       hipStream_t stream) {
+                       void* workspace, size_t ws_bytes, hipStream_t stream) {
   // Rows of whole 16-byte groups need no masks at their ends (RowIn).
   aligned = aligned && (V * (dtype == 1 ? 2 : 4)) % 16 == 0;
+  if (workspace) {
+    const SplitPlan sp = split_plan(static_cast<int64_t>(B) * gamma, V, K, dtype);
+    if (sp.chunks > 1 && ws_bytes >= sp.total) {
+      char* ws = static_cast<char*>(workspace);
+      SplitArgs p{};
+      p.chunks = sp.chunks;
+      p.len = sp.len;
+      p.ids = reinterpret_cast<int32_t*>(ws + sp.ids);
+      p.logit = reinterpret_cast<float*>(ws + sp.logit);
+      p.sum = reinterpret_cast<float*>(ws + sp.sum);
+      p.row_max = reinterpret_cast<float*>(ws + sp.row_max);
+#define UBT_SPLIT(T, AL) \
+  launch_split<T, AL>(logits, B, gamma, V, stride_b, stride_i, K, cand_ids, cand_logit, cand_logprob, lse, p, stream)
+      if (dtype == 1) {
+        if (aligned)
+          UBT_SPLIT(uint16_t, true);
+        else
+          UBT_SPLIT(uint16_t, false);
+      } else {
+        if (aligned)
+          UBT_SPLIT(float, true);
+        else
+          UBT_SPLIT(float, false);
+      }
+#undef UBT_SPLIT
+      return hipGetLastError();
+    }
+  }
   if (dtype == 1) {
     if (aligned)
       launch_typed<uint16_t, true>(logits, B, gamma, V, stride_b, stride_i, K, cand_ids, cand_logit, cand_logprob,

@@ -11,7 +11,10 @@ namespace ubt {
 // ---- top-K sweep --------------------------------------------------------------------
 hipError_t launch_topk(const void* logits, int dtype, bool aligned, int B, int gamma, int64_t V,
                        int64_t stride_b, int64_t stride_i, int K, int32_t* cand_ids, float* cand_logit,
-                       float* cand_logprob, float* lse, hipStream_t stream);
+                       float* cand_logprob, float* lse, void* workspace, size_t ws_bytes, hipStream_t stream);
+// Few rows are cut over several workgroups when the workspace (256-byte aligned) holds at
+// least this many bytes; 0: the rows are not cut.
+size_t topk_workspace_bytes(int B, int gamma, int64_t V, int K, int dtype);
 
 // ---- selector scores ------------------------------------------------------------------
 struct Scales {

@@ -313,3 +313,23 @@ def test_tree_attention_split_workspace_alignment():
     bad = ctypes.c_void_p(0x10010)
     assert ubt.lib().ubt_tree_attention_split(FAKE, FAKE, FAKE, FAKE, 1000, FAKE, FAKE, FAKE, FAKE, 2, 17, 4, 2, 64,
                                               ctypes.c_float(0.1), FAKE, 1, None, bad, 1 << 30, None) == 5
+
+
+def test_cut_sweep_workspace_bytes():
+    """Nothing for more than 32 rows and for short rows; the full step query adds it to the
+    plain one."""
+    L = ubt.lib()
+    f = L.ubt_topk_workspace_bytes
+    assert f(1, 15, 151936, 64, 1) >= 15 * 8 * (64 * 8 + 8)
+    assert f(4, 15, 151936, 64, 1) == 0 and f(1, 15, 50000, 8, 1) == 0
+    assert f(1, 15, 63, 64, 1) == 0 and f(1, 65, 151936, 64, 1) == 0
+    for B, K in ((1, 64), (1, 8), (32, 8)):
+        plain = L.ubt_draft_step_workspace_bytes(B, 15, 151936, K, 1)
+        assert L.ubt_draft_step_full_workspace_bytes(B, 15, 151936, K, 1) == plain + f(B, 15, 151936, K, 1)
+    assert L.ubt_draft_step_full_workspace_bytes(0, 15, 151936, 8, 1) == 0
+
+
+def test_topk_split_workspace_alignment():
+    """A misaligned workspace is refused before any launch."""
+    assert ubt.lib().ubt_topk_split(FAKE, 1, 1, 3, 100000, 300000, 100000, 8, FAKE, FAKE, None, None,
+                                    ctypes.c_void_p(0x10010), 1 << 20, None) == 5

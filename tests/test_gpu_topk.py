@@ -214,3 +214,46 @@ def test_rows_off_the_16_byte_boundary(dt, off, V, K):
     x[:, :, off:off + V] = rows
     g = _run(synth.store(x, dt), K, view=lambda t: t[:, :, off:off + V])
     parity.check_topk(g, oracle.topk(synth.store(rows, dt), K))
+
+
+@pytest.mark.parametrize("B,gamma,V,K,dt", [
+    # the shortest rows that are cut, 32 rows, remainders of 63 and 64 elements past whole chunks,
+    # unaligned rows, fp32
+    (1, 1, 129025, 1, "bf16"), (1, 15, 151936, 64, "bf16"), (2, 3, 16384 * 8 + 63, 64, "bf16"),
+    (2, 3, 16384 * 8 + 64, 64, "bf16"), (1, 7, 64513, 4, "f32"), (3, 5, 150257, 17, "bf16"), (1, 2, 100003, 8, "f32"),
+    (4, 8, 140001, 33, "bf16"),
+])
+def test_rows_cut_over_workgroups(B, gamma, V, K, dt):
+    """Few rows, each cut into chunks that are merged: against the oracle, and the same
+    candidates as the whole-row kernel gives (ubt_topk without a workspace).  The workspace
+    starts out filled with a pattern.  One row is constant (ties in every chunk), one holds
+    finite values in its last chunk only."""
+    import ctypes
+
+    import torch
+
+    import paper_2609_39972_amd as ubt
+    from gpu_util import dev_values, say, to_np
+
+    say(f"topk cut B={B} gamma={gamma} V={V} K={K} {dt}")
+    rng = np.random.default_rng(V + K)
+    x = rng.normal(0, 2.5, (B, gamma, V))
+    x[-1, -1] = 0.5
+    if B * gamma > 1:
+        x[0, 0, :-2] = -np.inf
+    x = synth.store(x, dt)
+    t = dev_values(x)
+    ws = ubt.topk_workspace(B, gamma, V, K, t.dtype)
+    assert ws is not None
+    ws.fill_(0x7F)
+    g = to_np(ubt.topk(t, K, workspace=ws))
+    torch.cuda.synchronize()
+    parity.check_topk(g, oracle.topk(x, K))
+    whole = dict(cand_ids=torch.empty(B, gamma, K, dtype=torch.int32, device="cuda"),
+                 cand_logit=torch.empty(B, gamma, K, device="cuda"))
+    p = lambda v: ctypes.c_void_p(v.data_ptr())
+    assert ubt.lib().ubt_topk(p(t), ubt._dtype_code(t), B, gamma, V, t.stride(0), t.stride(1), K,
+                              p(whole["cand_ids"]), p(whole["cand_logit"]), None, None, None) == 0
+    torch.cuda.synchronize()
+    for k, v in to_np(whole).items():
+        assert np.array_equal(g[k], v), f"{k} differs from the whole-row kernel"
