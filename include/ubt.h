@@ -138,12 +138,12 @@ ubt_status_t ubt_topk_split(const void* logits, ubt_dtype_t dt, int B, int gamma
  * workspace, ws_bytes : device scratch of at least ubt_lm_head_topk_workspace_bytes(M, d,
  *            V, K) bytes, 256-byte aligned, owned by the caller; no state is kept in it
  *            between calls, and calls that share it must not overlap.
- * M <= 16: one pass over the head, bound by the bandwidth of reading w_lm.  M > 16: with
- * a workspace of ubt_lm_head_topk_full_workspace_bytes(M, d, V, K) bytes (which adds room
- * for the fp32 logits of up to 512 rows, about 4 * min(M, 512) * V bytes; never less than
- * the plain query) the projection is one matrix product; with less, the head is read once
- * per 16 rows of h.  Inputs must be finite; non-finite logits
- * give unspecified candidates.  Returns UBT_ERR_WORKSPACE for a missing, small or
+ * M <= 16: one pass over the head, bound by the bandwidth of reading w_lm.  M > 16, or d no
+ * multiple of 512: with a workspace of ubt_lm_head_topk_full_workspace_bytes(M, d, V, K)
+ * bytes (room for the fp32 logits of up to 512 rows, about 4 * min(M, 512) * V bytes; never
+ * less than the plain query) the projection is one matrix product; with less, the head is
+ * read once per 16 rows of h.  Inputs must be finite; non-finite logits give unspecified
+ * candidates.  Returns UBT_ERR_WORKSPACE for a missing, small or
  * misaligned workspace, UBT_ERR_UNSUPPORTED for shapes the workspace query rejects
  * (it returns 0 for them: very large V at large K).
  * ------------------------------------------------------------------------------------ */

@@ -129,13 +129,15 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError(f"unsupported dtype {t.dtype}: use torch.bfloat16 or torch.float32")
 
 
-def _ptr(t: torch.Tensor | None):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+# Addresses go to ctypes as plain integers (the argument types are void pointers): building a
+# c_void_p per pointer cost a call of 30 arguments several microseconds.
+def _ptr(t: torch.Tensor | None) -> int | None:
+    return None if t is None else t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
+def _stream(stream) -> int:
     s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    return s.cuda_stream
 
 
 def _scratch(n: int, device, stream) -> torch.Tensor | None:
@@ -184,7 +186,7 @@ def topk(logits: torch.Tensor, K: int, out: dict | None = None, with_logprob: bo
                    cand_logit=torch.empty(B, gamma, K, dtype=torch.float32, device=dev),
                    cand_logprob=torch.empty(B, gamma, K, dtype=torch.float32, device=dev) if with_logprob else None,
                    lse=torch.empty(B, gamma, dtype=torch.float32, device=dev))
-    if workspace is None:
+    if workspace is None and B * gamma <= 32:  # the library cuts no more rows than that
         workspace = _scratch(lib().ubt_topk_workspace_bytes(B, gamma, V, K, code), dev, stream)
     st = lib().ubt_topk_split(_ptr(logits), code, B, gamma, V, logits.stride(0), logits.stride(1), K,
                               _ptr(out["cand_ids"]), _ptr(out["cand_logit"]), _ptr(out.get("cand_logprob")),
@@ -238,8 +240,14 @@ def lm_head_topk(h: torch.Tensor, w_lm: torch.Tensor, K: int, out: dict | None =
     return out
 
 
+def _host_vals(x):
+    """The values as a list or tuple that ctypes converts to C floats by itself."""
+    vals = x.tolist() if hasattr(x, "tolist") else x
+    return vals if type(vals) in (list, tuple) else list(vals)
+
+
 def _host_f32(x, n: int) -> ctypes.Array:
-    vals = [float(v) for v in (x.tolist() if hasattr(x, "tolist") else x)]
+    vals = _host_vals(x)
     if len(vals) != n:
         raise ValueError(f"expected {n} values, got {len(vals)}")
     return (ctypes.c_float * n)(*vals)
@@ -564,8 +572,8 @@ def tree_kl_loss(logits: torch.Tensor, cand: dict, target_logits: torch.Tensor, 
         raise ValueError("logits and target_logits must be [B, gamma, V] with unit stride along V")
     if target_logits.dtype != logits.dtype:
         raise TypeError("target_logits must have the logits' dtype")
-    a = (ctypes.c_float * gamma)(*[float(x) for x in alpha])
-    l = (ctypes.c_float * gamma)(*[float(x) for x in lam])
+    a = (ctypes.c_float * gamma)(*_host_vals(alpha))
+    l = (ctypes.c_float * gamma)(*_host_vals(lam))
     if out is None:
         f32 = dict(dtype=torch.float32, device=logits.device)
         out = dict(loss=torch.empty(B, gamma, **f32), kl=torch.empty(B, gamma, **f32),

@@ -17,6 +17,7 @@
 // the row's K-th logit from below, so only the columns of about K groups are looked at.
 #include "bigram_tile.h"
 #include "search.h"
+#include "ubt_launch.h"
 
 namespace ubt {
 namespace {
@@ -537,9 +538,10 @@ int gm_grid() {
 }  // namespace
 
 size_t lm_gemm_workspace_bytes(int M, int d, int64_t V, int K) {
-  (void)d;
-  // Fewer rows fit one tile of the stream kernel, which reads the head once.
-  if (M <= 16 || V > (int64_t(1) << 24)) return 0;
+  // Up to 16 rows fit one tile of the row-group kernels, which read the head once: the one that
+  // splits d streams it as fast (15 rows, d = 2560: 132 us), the other one (d no multiple of 512)
+  // at less than half the rate.
+  if ((M <= 16 && lm_head_split_fits(d)) || V > (int64_t(1) << 24)) return 0;
   const GemmPlan p = gm_plan(M < kGmMaxRows ? M : kGmMaxRows, V, gm_grid());
   // The last rows of a longer call: fewer rows, so never more bytes.
   const GemmPlan q = M > kGmMaxRows ? gm_plan((M - 1) % kGmMaxRows + 1, V, gm_grid()) : p;

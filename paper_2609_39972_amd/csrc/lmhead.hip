@@ -705,6 +705,8 @@ constexpr size_t kLmMaxLds = 160 * 1024;
 
 }  // namespace
 
+bool lm_head_split_fits(int d) { return split_fits(d); }
+
 size_t lm_head_workspace_bytes(int M, int d, int64_t V, int K) {
   const int G = lm_grid(static_cast<int>((V + 15) / 16), d);
   if (G > 16 * kWave || merge_layout(G, K).total > kLmMaxLds) return 0;

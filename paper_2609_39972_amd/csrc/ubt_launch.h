@@ -25,8 +25,8 @@ size_t lm_head_workspace_bytes(int M, int d, int64_t V, int K);
 hipError_t launch_lm_head_topk(const void* h, const void* w_lm, int M, int d, int64_t V, int K, int32_t* cand_ids,
                                float* cand_logit, float* cand_logprob, float* lse, void* workspace,
                                hipStream_t stream);
-// The projection as a matrix product with reduced statistics (M > 16 rows); 0 bytes: the
-// shape is not taken.
+bool lm_head_split_fits(int d);  // whether the kernel that splits d over a workgroup's waves takes d
+// The projection as a matrix product with reduced statistics; 0 bytes: the shape is not taken.
 size_t lm_gemm_workspace_bytes(int M, int d, int64_t V, int K);
 hipError_t launch_lm_gemm_topk(const void* h, const void* w_lm, int M, int d, int64_t V, int K, int32_t* cand_ids,
                                float* cand_logit, float* cand_logprob, float* lse, void* workspace,

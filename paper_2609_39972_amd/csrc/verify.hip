@@ -380,7 +380,9 @@ __device__ __forceinline__ void score_block(AttnLds<D>& lds, int blk, const uint
   mx_next[TW - 1] = next_max(TW - 1);
 }
 
-template <int D, int TW>
+// kSplit: the keys of a (sequence, head) may be cut into parts (kept out of the whole-range
+// kernel: its first instructions and registers cost a full batch 1 to 2%).
+template <int D, int TW, bool kSplit>
 __global__ __launch_bounds__(kAttnThreads) void tree_attention_kernel(AttnArgs p) {
   constexpr int DS = D / 32;
   constexpr int DT = D / 16;
@@ -392,13 +394,17 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attention_kernel(AttnArgs p
   // Workgroup -> (part, sequence, key/value head, row group).  Consecutive workgroups go to
   // different XCDs; the remap puts the row groups of one (sequence, head) on one XCD, so
   // they share its key/value blocks through that XCD's L2.
-  const int total = p.B * p.Hkv * p.groups * p.splits;
+  const int total = p.B * p.Hkv * p.groups * (kSplit ? p.splits : 1);
   const int L = static_cast<int>(blockIdx.x);
   const int T8 = total - total % 8;
-  const int id = L < T8 ? (L % 8) * (T8 / 8) + L / 8 : L;
+  int id = L < T8 ? (L % 8) * (T8 / 8) + L / 8 : L;
+  int part = 0;
+  if (kSplit) {
+    part = id / (p.B * p.Hkv * p.groups);
+    id -= part * (p.B * p.Hkv * p.groups);
+  }
   const int grp = id % p.groups;
-  const int part = id / (p.B * p.Hkv * p.groups);
-  const int bh = (id / p.groups) % (p.B * p.Hkv);
+  const int bh = id / p.groups;
   const int h = bh % p.Hkv;
   const int b = bh / p.Hkv;
 
@@ -417,10 +423,14 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attention_kernel(AttnArgs p
   const int words = (p.N + 31) / 32;
   // This workgroup's blocks: nblk from block lo on.  Block numbers below count from lo.
   const int n_all = npb + (nn + kKB - 1) / kKB;
-  const int parts = part_count(npb, p.splits);
+  const int parts = kSplit ? part_count(npb, p.splits) : 1;
   if (part >= parts) return;
-  const int lo = static_cast<int>(static_cast<int64_t>(part) * n_all / parts);
-  const int hi = static_cast<int>(static_cast<int64_t>(part + 1) * n_all / parts);
+  int lo = 0, hi = n_all;
+  if (parts > 1) {  // part < 64 and n_all < 2^26 + 8 blocks: no overflow
+    lo = static_cast<int>(static_cast<uint32_t>(part) * static_cast<uint32_t>(n_all) / static_cast<uint32_t>(parts));
+    if (part + 1 < parts)
+      hi = static_cast<int>(static_cast<uint32_t>(part + 1) * static_cast<uint32_t>(n_all) / static_cast<uint32_t>(parts));
+  }
   const int nblk = hi - lo;
   const int Pl = P - lo * kKB, npl = npb - lo;
 
@@ -444,6 +454,10 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attention_kernel(AttnArgs p
 
   if (scorer) {
     // ---------------- score wave ----------------
+    // The score wave has the longer step: it wins the issue arbitration of its SIMD (one
+    // request over 16,384 keys 56.0 -> 54.9 us, the output wave first instead 59.7 us; a full
+    // batch 190 us either way, 205 us with the output wave first).
+    if (kSplit) __builtin_amdgcn_s_setprio(1);
     ScoreState<D, TW> S;
     int ml[TW];
 #pragma unroll
@@ -827,16 +841,24 @@ hipError_t launch_tree_attention(const TreeAttnArgs& a, void* workspace, size_t 
   // Tiles per pair: enough for the group's rows (1, 3 or 5; rows past R are empty tiles).
   const int tiles = (min(p.R, kAttnRows) + 15) / 16;
   const int tw = (tiles + kPairs - 1) / kPairs;
+#define UBT_ATTN(D, TW)                                                                                    \
+  do {                                                                                                    \
+    if (p.splits > 1)                                                                                     \
+      hipLaunchKernelGGL((tree_attention_kernel<D, TW, true>), grid, dim3(kAttnThreads), 0, stream, p);   \
+    else                                                                                                  \
+      hipLaunchKernelGGL((tree_attention_kernel<D, TW, false>), grid, dim3(kAttnThreads), 0, stream, p);  \
+  } while (0)
   if (a.D == 128) {
     if (tw <= 1)
-      hipLaunchKernelGGL((tree_attention_kernel<128, 1>), grid, dim3(kAttnThreads), 0, stream, p);
+      UBT_ATTN(128, 1);
     else if (tw <= 3)
-      hipLaunchKernelGGL((tree_attention_kernel<128, 3>), grid, dim3(kAttnThreads), 0, stream, p);
+      UBT_ATTN(128, 3);
     else
-      hipLaunchKernelGGL((tree_attention_kernel<128, kMaxTiles>), grid, dim3(kAttnThreads), 0, stream, p);
+      UBT_ATTN(128, kMaxTiles);
   } else {
-    hipLaunchKernelGGL((tree_attention_kernel<64, kMaxTiles>), grid, dim3(kAttnThreads), 0, stream, p);
+    UBT_ATTN(64, kMaxTiles);
   }
+#undef UBT_ATTN
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.splits == 1) return e;
   const int64_t rows = static_cast<int64_t>(p.B) * p.Hkv * p.R;

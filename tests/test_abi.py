@@ -283,12 +283,12 @@ def test_lm_head_workspace_bytes():
 
 
 def test_lm_head_full_workspace_bytes():
-    """The full query is the plain one up to 16 rows, adds room for the logits of up to 512
-    rows past that, and rejects what the plain one rejects."""
+    """The full query is the plain one up to 16 rows where the d-split kernel takes them, adds
+    room for the logits of up to 512 rows past that, and rejects what the plain one rejects."""
     L = ubt.lib()
     plain, full = L.ubt_lm_head_topk_workspace_bytes, L.ubt_lm_head_topk_full_workspace_bytes
     for d, V, K in ((2560, 151936, 64), (96, 1000, 4), (2880, 50257, 8)):
-        assert full(16, d, V, K) == plain(16, d, V, K)
+        assert full(16, d, V, K) == plain(16, d, V, K) if d % 512 == 0 else full(16, d, V, K) >= 16 * V * 4
         assert full(17, d, V, K) >= 17 * V * 4
         assert full(480, d, V, K) >= max(480 * V * 4, plain(480, d, V, K))
         assert full(5000, d, V, K) >= 512 * V * 4

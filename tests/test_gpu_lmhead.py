@@ -140,9 +140,11 @@ def test_lm_head_workspace_reuse_across_shapes():
     (257, 64, 3000, 8), (480, 160, 70001, 8), (530, 64, 5000, 64), (1030, 32, 300, 8),
     # Ranges of several tiles per workgroup, the last tile of one to four 64-row passes
     (17, 64, 151936, 8), (40, 64, 100003, 16), (20, 32, 262145, 4),
+    # Up to 16 rows where d is no multiple of 512
+    (1, 96, 5000, 8), (15, 2880, 3001, 64), (16, 160, 40001, 16),
 ])
 def test_lm_head_product_integer_inputs_exact(M, d, V, K):
-    """The matrix product of calls with more than 16 rows (full workspace): integer-valued
+    """The matrix product (more than 16 rows, or d no multiple of 512): integer-valued
     inputs, so every logit is exact in fp32 and ids, ties included, must match bit for bit.
     The workspace starts out filled with a pattern: nothing in it is read unwritten."""
     import paper_2609_39972_amd as ubt
