@@ -7,8 +7,8 @@
 // A call with M rows does 2 M d V flops on V d weights.  Streaming the head once per 16
 // rows (the drafting block of one sequence) reads it M / 16 times; from a few row groups
 // on, the weights have to be reused on chip.  Here a workgroup of 8 waves computes a tile
-// of 256 vocabulary rows x up to 256 rows of h with v_mfma_f32_16x16x32_bf16, both
-// operands staged in LDS by direct loads, so each weight byte is read once per 256 rows.
+// of 256 vocabulary rows x up to 160 rows of h with v_mfma_f32_16x16x32_bf16, both
+// operands staged in LDS by direct loads, so each weight byte is staged once per 160 rows.
 //
 // The fp32 logits go to the workspace (16-byte stores that overlap the next tile's
 // loads; 292 MB at 480 x 151,936, a fraction of the memory time that the product leaves
@@ -27,6 +27,7 @@ constexpr int kGmThreads = kGmWaves * kWave;
 constexpr int kGmBN = 256;             // vocabulary rows per tile
 constexpr int kGmBK = 64;              // k per stage: 128-byte rows, whole cache lines
 constexpr int kGmRowBytes = kGmBK * 2;
+constexpr int kGmBM = 160;             // most rows of h per tile
 constexpr int kGmGroup = 64;           // columns per statistics entry (one wave's columns)
 constexpr int kGmMaxGroups = 8192;     // statistics entries per row that the select kernel holds in LDS
 
@@ -35,7 +36,8 @@ struct GemmArgs {
   const uint16_t* w;  // [V, d] bf16
   int M, d;
   int64_t V;
-  int row_blocks, bm;  // 1 or 2 blocks of bm rows of h (bm a multiple of 32)
+  int row_blocks, bm;  // blocks of bm rows of h (bm a multiple of 32, at most kGmBM)
+  int fold;            // stages per partial sum
   int ranges, cpr;     // column ranges of cpr columns (a multiple of 16), one per workgroup and row block
   int gpr;             // statistics groups per range: ceil(cpr / 64)
   int64_t ls;          // logits per row
@@ -135,10 +137,13 @@ __global__ __launch_bounds__(kGmThreads, 2) void lm_gemm_kernel(GemmArgs a) {
   const int sw = gm_swz(lr);
   const int wrow = (vw * 64 + lr) * kGmRowBytes;
   const int hrow = kGmBN * kGmRowBytes + (hw * 16 * TH + lr) * kGmRowBytes;
-  f32x4 acc[TH][4];
-  // One stage.  The matrix cores do not round their running sum to nearest, so a sum
-  // carried through all of d drifts; each stage's 64 products per logit start from zero
-  // instead and join the running sum by an ordinary fp32 add.
+  f32x4 acc[TH][4], sum[TH][4];
+  // One stage.  The matrix cores do not round their running sum to nearest, so a sum carried
+  // through all of d drifts (error of 480 rows, d = 4096 against 64 bits 9.8e-7), and fp32
+  // adds of many short partial sums each round at the running sum's size (one add per 64
+  // products 3.6e-7).  `fold` cuts d into up to 8 partial sums, as the row-group kernels do
+  // (2.0e-7 for both).  The two accumulators bound the tile to 160 rows: 480 x 4096 x
+  // 151,936 takes 767 us, 709 us with 256 rows and one add per 64 products.
   auto compute = [&](int slot, auto both_tag) {
     constexpr bool both = decltype(both_tag)::value;
     const unsigned char* st0 = smem_raw + slot * kStage + ((kg ^ sw) << 4);
@@ -151,35 +156,36 @@ __global__ __launch_bounds__(kGmThreads, 2) void lm_gemm_kernel(GemmArgs a) {
     }
     u32x4 fh0 = *reinterpret_cast<const u32x4*>(st0 + hrow);
     u32x4 fh1 = *reinterpret_cast<const u32x4*>(st1 + hrow);
-    f32x4 t[4];
 #pragma unroll
     for (int i = 0; i < TH; ++i) {
-      // The fragments of row tile i + 1 load and the sums of row tile i - 1 are added
-      // while tile i is on the matrix cores; the barrier keeps the compiler from hoisting
-      // more loads than there are registers for.
+      // The fragments of row tile i + 1 load while tile i is on the matrix cores; the barrier
+      // keeps the compiler from hoisting more loads than there are registers for.
       u32x4 n0 = fh0, n1 = fh1;
       if (i + 1 < TH) {
         n0 = *reinterpret_cast<const u32x4*>(st0 + hrow + (i + 1) * 16 * kGmRowBytes);
         n1 = *reinterpret_cast<const u32x4*>(st1 + hrow + (i + 1) * 16 * kGmRowBytes);
       }
-      f32x4 u[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        u[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(fw0[j]), as_bf16x8(fh0), f32x4{0.f, 0.f, 0.f, 0.f}, 0,
-                                                       0, 0);
-      if (i > 0) {
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(fw0[j]), as_bf16x8(fh0), acc[i][j], 0, 0, 0);
+      if (both) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i - 1][j] += t[j];
+        for (int j = 0; j < 4; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(fw1[j]), as_bf16x8(fh1), acc[i][j], 0, 0, 0);
       }
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        t[j] = both ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(fw1[j]), as_bf16x8(fh1), u[j], 0, 0, 0) : u[j];
       fh0 = n0;
       fh1 = n1;
       __builtin_amdgcn_sched_barrier(0);
     }
+  };
+  auto fold = [&]() {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[TH - 1][j] += t[j];
+    for (int i = 0; i < TH; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        sum[i][j] += acc[i][j];
+        acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
   };
 
   // The stages of all of this workgroup's tiles form one sequence; S - 1 of them are in
@@ -207,7 +213,7 @@ __global__ __launch_bounds__(kGmThreads, 2) void lm_gemm_kernel(GemmArgs a) {
 #pragma unroll
     for (int i = 0; i < TH; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < 4; ++j) acc[i][j] = sum[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int nq = min((width - tile * kGmBN + 63) / 64, kWLoads);  // weight loads per wave and stage
     auto step = [&](int kt) {
       // Wait for this step's stage: all but the loads of the S - 2 stages after it.  Stores
@@ -237,17 +243,23 @@ __global__ __launch_bounds__(kGmThreads, 2) void lm_gemm_kernel(GemmArgs a) {
       }
       continue;
     }
+    int left = a.fold;
     for (int kt = 0; kt < nk_full; ++kt) {
       step(kt);
       compute(slot, BoolTag<true>{});
       next_slot();
+      if (--left == 0) {
+        fold();
+        left = a.fold;
+      }
     }
     if (nk_full < nk) {
       step(nk_full);
       compute(slot, BoolTag<false>{});
       next_slot();
     }
-    // Epilogue: acc[i][j][e] = u(row m, column c0 + 16 j + 4 kg + e).
+    fold();
+    // Epilogue: sum[i][j][e] = u(row m, column c0 + 16 j + 4 kg + e).
     const int64_t c0 = c_lo + tile * kGmBN + vw * kGmGroup;
     const int64_t ss = static_cast<int64_t>(a.ranges) * a.gpr;
     const int64_t group = static_cast<int64_t>(range) * a.gpr + tile * 4 + vw;
@@ -263,13 +275,13 @@ __global__ __launch_bounds__(kGmThreads, 2) void lm_gemm_kernel(GemmArgs a) {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) mx = fmaxf(mx, acc[i][j][e]);
+          for (int e = 0; e < 4; ++e) mx = fmaxf(mx, sum[i][j][e]);
       } else {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            mx = 16 * j + 4 * kg + e < cols ? fmaxf(mx, acc[i][j][e]) : mx;
+            mx = 16 * j + 4 * kg + e < cols ? fmaxf(mx, sum[i][j][e]) : mx;
       }
       mx = fmaxf(mx, __shfl_xor(mx, 16));
       mx = fmaxf(mx, __shfl_xor(mx, 32));
@@ -279,7 +291,7 @@ __global__ __launch_bounds__(kGmThreads, 2) void lm_gemm_kernel(GemmArgs a) {
         float t[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          t[e] = __builtin_amdgcn_exp2f((acc[i][j][e] - mx) * kLog2e);
+          t[e] = __builtin_amdgcn_exp2f((sum[i][j][e] - mx) * kLog2e);
           if (cols != kGmGroup) t[e] = 16 * j + 4 * kg + e < cols ? t[e] : 0.f;
         }
         se += (t[0] + t[1]) + (t[2] + t[3]);
@@ -292,7 +304,7 @@ __global__ __launch_bounds__(kGmThreads, 2) void lm_gemm_kernel(GemmArgs a) {
         // the row is padded to a multiple of 16.
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          if (16 * j < cols) *reinterpret_cast<f32x4*>(lp + 16 * j) = acc[i][j];
+          if (16 * j < cols) *reinterpret_cast<f32x4*>(lp + 16 * j) = sum[i][j];
         if (kg == 0) a.stats[m * ss + group] = make_float2(mx, se);
       }
     }
@@ -505,7 +517,7 @@ int gm_cu_count() {
   return cus;
 }
 
-constexpr int kGmMaxRows = 512;  // rows of h per product: two row blocks (bounds the workspace)
+constexpr int kGmMaxRows = 512;  // rows of h per product (bounds the workspace)
 
 size_t gm_up(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
@@ -518,7 +530,7 @@ struct GemmPlan {
 // The split of `rows` x V over G workgroups.
 GemmPlan gm_plan(int rows, int64_t V, int G) {
   GemmPlan p{};
-  p.row_blocks = (rows + 255) / 256;
+  p.row_blocks = (rows + kGmBM - 1) / kGmBM;
   p.th = ((rows + p.row_blocks - 1) / p.row_blocks + 31) / 32;
   const int64_t most = G / p.row_blocks > 0 ? G / p.row_blocks : 1;
   p.cpr = static_cast<int>(((V + most - 1) / most + 15) / 16 * 16);
@@ -565,6 +577,7 @@ hipError_t launch_lm_gemm_topk(const void* h, const void* w_lm, int M, int d, in
     a.V = V;
     a.row_blocks = p.row_blocks;
     a.bm = 32 * p.th;
+    a.fold = ((d + kGmBK - 1) / kGmBK + 7) / 8;
     a.ranges = p.ranges;
     a.cpr = p.cpr;
     a.gpr = p.gpr;
@@ -595,10 +608,7 @@ hipError_t launch_lm_gemm_topk(const void* h, const void* w_lm, int M, int d, in
       case 2: UBT_GEMM(2, 4); break;
       case 3: UBT_GEMM(3, 3); break;
       case 4: UBT_GEMM(4, 3); break;
-      case 5: UBT_GEMM(5, 3); break;
-      case 6: UBT_GEMM(6, 2); break;
-      case 7: UBT_GEMM(7, 2); break;
-      default: UBT_GEMM(8, 2); break;
+      default: UBT_GEMM(5, 3); break;
     }
 #undef UBT_GEMM1
 #undef UBT_GEMM

@@ -135,9 +135,12 @@ def test_lm_head_workspace_reuse_across_shapes():
 @pytest.mark.parametrize("M,d,V,K", [
     # One row block of every height (32 rows per step), d / 32 odd and even, one k stage and many
     (32, 32, 700, 8), (48, 96, 4099, 64), (65, 128, 2000, 16), (128, 224, 4097, 10), (130, 64, 5003, 64),
-    (161, 320, 1000, 8), (193, 96, 3333, 4), (256, 256, 2049, 64),
-    # Two row blocks (the last rows of the second past M), several products per call
-    (257, 64, 3000, 8), (480, 160, 70001, 8), (530, 64, 5000, 64), (1030, 32, 300, 8),
+    (160, 1024, 2049, 64),
+    # Two to four row blocks (the last rows of the last past M), several products per call
+    (161, 320, 1000, 8), (193, 96, 3333, 4), (257, 64, 3000, 8), (320, 544, 3000, 8), (321, 96, 1500, 16),
+    (480, 160, 70001, 8), (512, 1120, 1000, 64), (530, 64, 5000, 64), (1030, 32, 300, 8),
+    # One stage per partial sum, several, and a last one that is shorter
+    (33, 512, 2000, 8), (33, 576, 2000, 8), (33, 1088, 2000, 8), (33, 2880, 2000, 8),
     # Ranges of several tiles per workgroup, the last tile of one to four 64-row passes
     (17, 64, 151936, 8), (40, 64, 100003, 16), (20, 32, 262145, 4),
     # Up to 16 rows where d is no multiple of 512
