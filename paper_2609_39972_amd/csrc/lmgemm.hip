@@ -142,8 +142,9 @@ __global__ __launch_bounds__(kGmThreads, 2) void lm_gemm_kernel(GemmArgs a) {
   // through all of d drifts (error of 480 rows, d = 4096 against 64 bits 9.8e-7), and fp32
   // adds of many short partial sums each round at the running sum's size (one add per 64
   // products 3.6e-7).  `fold` cuts d into up to 8 partial sums, as the row-group kernels do
-  // (2.0e-7 for both).  The two accumulators bound the tile to 160 rows: 480 x 4096 x
-  // 151,936 takes 767 us, 709 us with 256 rows and one add per 64 products.
+  // (2.0e-7 for both).  The two accumulators bound the tile to 160 rows, which leaves room
+  // for a third stage: 480 x 4096 x 151,936 takes 705 us, 709 us with 256 rows, two stages
+  // and one add per 64 products.
   auto compute = [&](int slot, auto both_tag) {
     constexpr bool both = decltype(both_tag)::value;
     const unsigned char* st0 = smem_raw + slot * kStage + ((kg ^ sw) << 4);
