@@ -3,6 +3,7 @@
 // ubtree-frontier), global pruning (Eq. ubtree-pruning) and the ancestor mask.
 #pragma once
 
+#include "frontier.h"
 #include "ubt_device.h"
 #include "ubt_launch.h"
 
@@ -627,17 +628,13 @@ __device__ __forceinline__ void expand_depths_wide(const TreeArgs& a, const Fast
     }
     const float* slab = sm.slab + ((d - 1) & 1) * KK;
     // F_{d-1}: entry r on lane r (depth 1: the root, score 0, extends through row 0).
-    uint32_t pkey = f32_key(0.f), pinfo = 0u;
-    if (d > 1 && lane < W) {
-      pkey = sm.s_key[(d - 2) * W + lane];
-      pinfo = sm.s_info[(d - 2) * W + lane];
-    }
+    const FrontierSlot parent = frontier_slot(sm.s_key, sm.s_info, d, W, np, lane, f32_key(0.f));
     uint32_t key[RW];
 #pragma unroll
     for (int i = 0; i < RW; ++i) {
       const int r = i * kK64Waves + w;
-      const float base = f32_key_value(__builtin_amdgcn_readlane(pkey, r));
-      const int row = static_cast<int>(__builtin_amdgcn_readlane(pinfo, r) >> 16);
+      const float base = f32_key_value(__builtin_amdgcn_readlane(parent.key, r));
+      const int row = static_cast<int>(__builtin_amdgcn_readlane(parent.info, r) >> 16);
       float v = base + slab[row * K + (kExact || lane < K ? lane : 0)];
       if (with_zeta) v += zeta;
       key[i] = r < np && (kExact || lane < K) ? f32_key(v) : 0u;
