@@ -24,6 +24,7 @@ one stream (graph-capturable).
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 
@@ -140,14 +141,21 @@ def _stream(stream) -> int:
     return s.cuda_stream
 
 
+def _on(stream, device):
+    """A context in which allocations and fills belong to the call's stream: the memory comes
+    from that stream's pool, which hands it out again only to work ordered after the call."""
+    if stream is None:
+        return contextlib.nullcontext()
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream, device=device)
+    return torch.cuda.stream(stream)
+
+
 def _scratch(n: int, device, stream) -> torch.Tensor | None:
-    """Scratch memory for one call on ``stream``, from that stream's pool: the allocator hands
-    it out again only to work that is ordered after the call."""
+    """Scratch memory for one call on ``stream``."""
     if n == 0:
         return None
-    if stream is None:
-        return torch.empty(n, dtype=torch.uint8, device=device)
-    with torch.cuda.stream(stream):
+    with _on(stream, device):
         return torch.empty(n, dtype=torch.uint8, device=device)
 
 
@@ -232,7 +240,8 @@ def lm_head_topk(h: torch.Tensor, w_lm: torch.Tensor, K: int, out: dict | None =
                    cand_logprob=torch.empty(*lead, K, dtype=torch.float32, device=dev) if with_logprob else None,
                    lse=torch.empty(*lead, dtype=torch.float32, device=dev))
     if workspace is None:
-        workspace = lm_head_workspace(M, d, V, K, dev)
+        with _on(stream, dev):
+            workspace = lm_head_workspace(M, d, V, K, dev)
     st = lib().ubt_lm_head_topk(_ptr(h), _ptr(w_lm), M, d, V, K, _ptr(out["cand_ids"]), _ptr(out["cand_logit"]),
                                 _ptr(out.get("cand_logprob")), _ptr(out.get("lse")), _ptr(workspace),
                                 workspace.numel(), _stream(stream))
@@ -402,7 +411,8 @@ def tree_mask(parent: torch.Tensor, n_nodes: torch.Tensor, out: torch.Tensor | N
 def draft_step_workspace(B: int, gamma: int, V: int, K: int, dtype=torch.bfloat16, device="cuda") -> torch.Tensor:
     """A zero-filled workspace for :func:`draft_step` (uint8, 256-byte aligned).  Each
     call resets the counters it uses, so one workspace serves consecutive calls on one
-    stream."""
+    stream.  The fill runs on the current stream; a first use on another one has to be
+    ordered after it."""
     code = UBT_BF16 if dtype == torch.bfloat16 else UBT_F32
     n = lib().ubt_draft_step_full_workspace_bytes(B, gamma, V, K, code)
     if n == 0:
@@ -448,7 +458,8 @@ def draft_step(logits: torch.Tensor, phi: torch.Tensor, psi: torch.Tensor, gate:
     if out is None:
         out = tree_outputs(B, gamma, W, budget, dev, with_mask)
     if workspace is None:
-        workspace = draft_step_workspace(B, gamma, V, K, logits.dtype, dev)
+        with _on(stream, dev):  # the fill must be ordered before the launch
+            workspace = draft_step_workspace(B, gamma, V, K, logits.dtype, dev)
     a, l = _host_f32(alpha, gamma), _host_f32(lam, gamma)
     # The workspace is zero-filled and serves one stream, whatever the shape.
     st = lib().ubt_draft_step_full(_ptr(logits), _dtype_code(logits), B, gamma, V, logits.stride(0), logits.stride(1),
@@ -618,6 +629,8 @@ class DraftStep:
         self.fused = fused and not with_delta and not debug
         self.one_call = one_call and self.fused
         self.workspace = draft_step_workspace(B, gamma, V, K, logit_dtype, dev) if self.one_call else None
+        if self.one_call and not torch.cuda.is_current_stream_capturing():
+            torch.cuda.current_stream(dev).synchronize()  # run() may be given any stream: the fill is done
         self.topk_workspace = None if self.one_call else topk_workspace(B, gamma, V, K, logit_dtype, dev)
         self.logit_dtype_code = UBT_BF16 if logit_dtype == torch.bfloat16 else UBT_F32
 

@@ -1,0 +1,92 @@
+"""The binding's own memory and library calls, without a GPU: the library and the streams are
+stand-ins that record what is asked of them."""
+from __future__ import annotations
+
+import contextlib
+
+import pytest
+import torch
+
+import paper_2609_39972_amd as ubt
+
+
+class Lib:
+    """Every function returns 0, a size query what `sizes` says."""
+
+    def __init__(self, sizes):
+        self.sizes, self.calls = sizes, []
+
+    def __getattr__(self, name):
+        if not name.startswith("ubt_"):
+            raise AttributeError(name)
+
+        def call(*args):
+            self.calls.append((name, args))
+            return self.sizes.get(name, 0)
+        return call
+
+    def names(self):
+        return [n for n, _ in self.calls]
+
+
+class Side:
+    """A stream of the caller's, known by its handle only."""
+    cuda_stream = 77
+
+
+@pytest.fixture
+def fake(monkeypatch):
+    """(library, allocations): allocations holds (bytes, stream handle) of every scratch tensor."""
+    lib, made, on = Lib({}), [], [0]
+
+    @contextlib.contextmanager
+    def stream(s):
+        on.append(s.cuda_stream)
+        yield
+        on.pop()
+
+    class External:
+        def __init__(self, handle, device=None):
+            self.cuda_stream = handle
+
+    def workspace(*shape, **kw):
+        made.append((shape, on[-1]))
+        return torch.zeros(512, dtype=torch.uint8)
+
+    real = torch.empty
+
+    def empty(*a, **kw):
+        if kw.get("dtype") == torch.uint8:
+            made.append((a, on[-1]))
+        return real(*a, **kw)
+
+    monkeypatch.setattr(ubt, "lib", lambda: lib)
+    monkeypatch.setattr(ubt, "_need_gpu", lambda *t: None)
+    monkeypatch.setattr(ubt, "_stream", lambda s: 0 if s is None else s.cuda_stream)
+    monkeypatch.setattr(torch.cuda, "stream", stream)
+    monkeypatch.setattr(torch.cuda, "ExternalStream", External)
+    monkeypatch.setattr(ubt, "draft_step_workspace", workspace)
+    monkeypatch.setattr(ubt, "lm_head_workspace", workspace)
+    monkeypatch.setattr(torch, "empty", empty)
+    return lib, made
+
+
+def _bf16(*shape):
+    return torch.zeros(*shape, dtype=torch.bfloat16)
+
+
+@pytest.mark.parametrize("stream,handle", [(None, 0), (Side(), 77)])
+def test_draft_step_makes_its_workspace_on_the_calls_stream(fake, stream, handle):
+    lib, made = fake
+    ubt.draft_step(_bf16(2, 3, 100), _bf16(100, 16), _bf16(100, 16), _bf16(2, 3, 16), torch.zeros(2, dtype=torch.int32),
+                   [1.0] * 3, [1.0] * 3, 4, 2, 6, stream=stream)
+    assert [s for _, s in made] == [handle]
+    assert lib.calls[-1][1][-1] == handle
+
+
+@pytest.mark.parametrize("stream,handle", [(None, 0), (Side(), 77)])
+def test_lm_head_makes_its_workspace_on_the_calls_stream(fake, stream, handle):
+    lib, made = fake
+    ubt.lm_head_topk(_bf16(20, 64), _bf16(500, 64), 8, stream=stream)
+    assert [s for _, s in made] == [handle]
+    assert lib.calls[-1][1][-1] == handle

@@ -292,3 +292,39 @@ def test_step_unaligned_rows_one_launch(kw):
     torch.cuda.synchronize()
     for k in EXACT_KEYS:
         assert np.array_equal(a[k], b[k]), f"{k} differs without a workspace"
+
+
+@pytest.mark.parametrize("kw", [
+    dict(B=3, L=6, V=12287, K=8, W=5, budget=20),             # rows between 16-byte boundaries
+    dict(B=2, L=9, V=6000, K=64, W=21, r=32, budget=90),      # K = 64 with W > 16
+])
+def test_step_on_a_side_stream_without_a_workspace(kw):
+    """The call makes and fills its workspace in the order of its own stream: the current stream
+    is kept busy, and the side stream's pool hands out memory that holds a pattern."""
+    import torch
+
+    import paper_2609_39972_amd as ubt
+    from gpu_util import to_np
+
+    w = _custom(305, **kw)
+    d = synth.inputs(w, 0)
+    logits = _logits_tensor(w, d)
+    a = _args(w, d, w.W)
+    args = (a[6], a[7], a[8], a[9], a[10], a[11], w.K, w.W, w.budget, w.zeta)
+    ref = to_np(ubt.draft_step(logits, *args))
+    side = torch.cuda.Stream()
+    n = ubt.draft_step_workspace(w.B, w.gamma, w.V, w.K).numel()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        torch.full((n,), 0x7F, dtype=torch.uint8, device="cuda")
+    one = ubt.DraftStep(*a, one_call=True)  # for its outputs only
+    big = torch.ones(4096, 4096, device="cuda")
+    torch.cuda.synchronize()
+    for _ in range(20):
+        big = big @ big * 1e-4
+    for _ in range(2):
+        got = ubt.draft_step(logits, *args, cand=one.cand, logq=one.sel["logq"], out=one.tree, stream=side)
+    torch.cuda.synchronize()
+    got = to_np(got)
+    for k in EXACT_KEYS:
+        assert np.array_equal(ref[k], got[k]), f"{k} differs on a side stream"
