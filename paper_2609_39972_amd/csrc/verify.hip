@@ -83,6 +83,31 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f{lo, hi}), v2bf));
 }
 
+// From `at[i]` key blocks on, a sequence is cut into `parts[i]` parts (the last entry that
+// applies); below at[0] it stays whole.
+constexpr int kMaxCuts = 8;
+struct CutRule {
+  int n;
+  int at[kMaxCuts], parts[kMaxCuts];
+};
+
+// n / d by a multiplication, for n * d < 2^32.
+struct FastDiv {
+  int d;
+  uint64_t magic;  // ceil(2^32 / d)
+  __device__ __forceinline__ int operator()(int n) const {
+    return static_cast<int>((static_cast<uint64_t>(static_cast<uint32_t>(n)) * magic) >> 32);
+  }
+};
+
+// The numbering of a cut launch's workgroups, in units of `wgs`.  There are at most kMaxCuts
+// workgroups per compute unit, so the numbers divided here stay far below 2^16.
+struct SplitGrid {
+  int heads;  // heads per unit
+  int dealt;  // workgroups of the units that are dealt out over the XCDs, a multiple of 8
+  FastDiv wgs, seqs, groups;  // workgroups per unit, units per part, row groups
+};
+
 struct AttnArgs {
   const uint16_t* q;
   const uint16_t* kc;
@@ -98,19 +123,24 @@ struct AttnArgs {
   void* out;
   int out_f32;
   float* lse;
-  int splits;     // most parts a key/value range is cut into; 1: no partial results
+  CutRule cuts;
+  SplitGrid split;
+  int splits;     // most parts of `cuts`; 1: no partial results
   float* part_o;  // [B * Hkv][splits][R][D] unnormalised outputs of the parts
   float2* part_ml;  // [B * Hkv][splits][R] (running maximum in log2 units, sum of weights)
 };
 
-// The parts a sequence's blocks are cut into: one per kMinPart context blocks, at most
-// `splits`.  Part s holds blocks [s T / n, (s + 1) T / n) of the T = npb + tree blocks; with
-// kMinPart >= 8 >= the tree's blocks every part starts with a context block, of which every
-// query sees a key, so its running maximum is finite.
+// The parts a sequence's blocks are cut into: by its own length, at most one per kMinPart
+// context blocks.  Part s holds blocks [s T / n, (s + 1) T / n) of the T = npb + tree blocks;
+// with kMinPart >= 8 >= the tree's blocks every part starts with a context block, of which
+// every query sees a key, so its running maximum is finite.
 constexpr int kMinPart = 8;
-__device__ __forceinline__ int part_count(int npb, int splits) {
-  const int n = (npb + kMinPart - 1) / kMinPart;
-  return n < 1 ? 1 : (n < splits ? n : splits);
+__device__ __forceinline__ int part_count(const CutRule& c, int npb, int n_all) {
+  int n = 1;
+#pragma unroll
+  for (int i = 0; i < kMaxCuts; ++i)
+    if (i < c.n && n_all >= c.at[i]) n = c.parts[i];
+  return max(1, min(n, (npb + kMinPart - 1) / kMinPart));
 }
 
 // Where the keys and values of block `blk` of sequence b, head h live: the context for
@@ -392,19 +422,33 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attention_kernel(AttnArgs p
   __shared__ __attribute__((aligned(16))) uint16_t v_ring[kRing][kKB * D];
 
   // Workgroup -> (part, sequence, key/value head, row group).  Consecutive workgroups go to
-  // different XCDs; the remap puts the row groups of one (sequence, head) on one XCD, so
+  // different XCDs; the row groups of one (sequence, head) or part of it go to one XCD, so
   // they share its key/value blocks through that XCD's L2.
-  const int total = p.B * p.Hkv * p.groups * (kSplit ? p.splits : 1);
   const int L = static_cast<int>(blockIdx.x);
-  const int T8 = total - total % 8;
-  int id = L < T8 ? (L % 8) * (T8 / 8) + L / 8 : L;
-  int part = 0;
+  int grp, bh, part = 0;
   if (kSplit) {
-    part = id / (p.B * p.Hkv * p.groups);
-    id -= part * (p.B * p.Hkv * p.groups);
+    // A unit is up to 8 heads of one part of a sequence: they read the same rows of the cache,
+    // which lie next to each other, and go to one XCD (one request over 16,384 keys 54.5 us, with
+    // its heads on different XCDs 56.2).  Units are dealt out over the XCDs one at a time, part 0
+    // of all sequences first: a sequence shorter than the cache has fewer parts than the grid,
+    // and consecutive units on one XCD would leave the others idle (12 sequences, 512 of 32,768
+    // keys: 100 us, whole 40).
+    const int dealt = p.split.dealt;
+    const int i = L < dealt ? L / 8 : L - dealt;
+    const int at = p.split.wgs(i);
+    const int u = L < dealt ? at * 8 + L % 8 : dealt / p.split.wgs.d + at;
+    part = p.split.seqs(u);
+    const int in = i - at * p.split.wgs.d;
+    const int head = p.split.groups(in);
+    bh = (u - part * p.split.seqs.d) * p.split.heads + head;
+    grp = in - head * p.groups;
+  } else {
+    const int total = p.B * p.Hkv * p.groups;
+    const int T8 = total - total % 8;
+    const int id = L < T8 ? (L % 8) * (T8 / 8) + L / 8 : L;
+    grp = id % p.groups;
+    bh = id / p.groups;
   }
-  const int grp = id % p.groups;
-  const int bh = id / p.groups;
   const int h = bh % p.Hkv;
   const int b = bh / p.Hkv;
 
@@ -423,7 +467,7 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attention_kernel(AttnArgs p
   const int words = (p.N + 31) / 32;
   // This workgroup's blocks: nblk from block lo on.  Block numbers below count from lo.
   const int n_all = npb + (nn + kKB - 1) / kKB;
-  const int parts = kSplit ? part_count(npb, p.splits) : 1;
+  const int parts = kSplit ? part_count(p.cuts, npb, n_all) : 1;
   if (part >= parts) return;
   int lo = 0, hi = n_all;
   if (parts > 1) {  // part < 64 and n_all < 2^26 + 8 blocks: no overflow
@@ -632,20 +676,18 @@ constexpr int kCombineBatch = 8;
 constexpr int kCombineThreads = 256;
 
 template <int D>
-__global__ __launch_bounds__(kCombineThreads) void attention_combine_kernel(AttnArgs p) {
+__device__ __forceinline__ void combine_row(const AttnArgs& p, int row, int l32) {
   constexpr int E = D / 32;  // 2 or 4 dims per lane
   typedef float vef __attribute__((ext_vector_type(E)));
-  const int64_t row = (static_cast<int64_t>(blockIdx.x) * kCombineThreads + threadIdx.x) / 32;
-  const int l32 = static_cast<int>(threadIdx.x) % 32;
-  const int64_t bh = row / p.R;
-  if (bh >= static_cast<int64_t>(p.B) * p.Hkv) return;
-  const int r = static_cast<int>(row - bh * p.R);
-  const int b = static_cast<int>(bh / p.Hkv), h = static_cast<int>(bh % p.Hkv);
+  const int bh = row / p.R;
+  const int r = row - bh * p.R;
+  const int b = bh / p.Hkv, h = bh - b * p.Hkv;
   const int P = min(max(p.prefix_len[b], 0), static_cast<int>(p.Pmax));
   const int nn = min(max(p.n_nodes[b], 0), p.N);
-  const int parts = part_count((P + kKB - 1) / kKB, p.splits);
+  const int npb = (P + kKB - 1) / kKB;
+  const int parts = part_count(p.cuts, npb, npb + (nn + kKB - 1) / kKB);
   if (parts == 1) return;  // stored by the attention kernel
-  const int64_t at = bh * p.splits * p.R + r;
+  const int64_t at = static_cast<int64_t>(bh) * p.splits * p.R + r;
   float M = neg_inf(), L = 0.f;
   vef o = 0.f;
   for (int s0 = 0; s0 < parts; s0 += kCombineBatch) {
@@ -684,6 +726,18 @@ __global__ __launch_bounds__(kCombineThreads) void attention_combine_kernel(Attn
     for (int i = 0; i < E / 2; ++i) op[i] = pack_bf16(y[2 * i], y[2 * i + 1]);
   }
   if (p.lse && l32 == 0) p.lse[orow] = has ? (M + __builtin_amdgcn_logf(L)) * kLn2 : neg_inf();
+}
+
+// At most eight workgroups per compute unit: with one per 8 rows, 40 sequences whose contexts
+// are too short to be cut paid 6 us for workgroups that leave at once.
+constexpr int kCombineGrid = 2048;
+template <int D>
+__global__ __launch_bounds__(kCombineThreads) void attention_combine_kernel(AttnArgs p) {
+  constexpr int kRows = kCombineThreads / 32;
+  const int rows = p.B * p.Hkv * p.R;  // fewer than 2^20: kMaxPartBytes
+  for (int row = static_cast<int>(blockIdx.x) * kRows + static_cast<int>(threadIdx.x) / 32; row < rows;
+       row += static_cast<int>(gridDim.x) * kRows)
+    combine_row<D>(p, row, static_cast<int>(threadIdx.x) % 32);
 }
 
 // ---- acceptance walk: one wave per sequence ----------------------------------------------
@@ -762,30 +816,77 @@ __global__ __launch_bounds__(256) void commit_kv_kernel(const uint16_t* __restri
 
 namespace {
 
-// Parts per (sequence, head).  One workgroup runs on a compute unit, so `base` = B * Hkv *
-// groups workgroups leave the chip idle when they are few (one sequence of 8 heads: 8 of
-// 256 units) or when their last round is.  The lengths are on the device: the host picks
-// the cut that is best for a full cache, priced in key blocks with about 6 per workgroup for its
-// start and end and 8 for the second kernel; short sequences are cut less (part_count).
-int attention_splits(int64_t base, int64_t Pmax, int N) {
+// How many parts a (sequence, head) is cut into, by its number of key blocks.  One workgroup
+// runs on a compute unit, so `base` = B * Hkv * groups workgroups leave the chip idle when they
+// are few (one sequence of 8 heads: 8 of 256 units) or when their last round is.  The lengths
+// are on the device: the host prices each cut as a line over the blocks per sequence (all
+// sequences alike), the kernels look up the cheapest line for each sequence's own length.
+//
+// Prices in key blocks of one workgroup (1.15 us at D = 128, 260 query rows): a workgroup
+// starts and ends in 14; with every unit busy a block takes 1.23 (D = 128: the caches deliver
+// 2.95 TB/s); the second kernel takes 8, and 4 more per chip's worth of parts whose fp32 results
+// are written and read again.  Over 100 measured shapes (1 to 64 sequences, 128 to 32,768 keys)
+// the price is within 10% of the time from 40 us on.  One sequence over 4,096 keys 170 us whole,
+// 37 cut; 16 sequences 171 and 121; 24 sequences 176 and 200: not cut.  A cut has to promise a
+// tenth in a full cache, because a context that turns out too short for it still pays for the
+// second launch and the workgroups that leave at once (one sequence, 128 of 32,768 keys: 25 and
+// 28 us; 33 sequences, 2,048 keys: 192 and 201).
+constexpr int64_t kMaxPartBytes = int64_t(256) << 20;  // scratch of one call
+
+CutRule attention_cuts(int64_t base, int64_t Pmax, int N, int D, int64_t bytes_per_part) {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
     cus = 256;
   const int64_t ctx = (Pmax + kKB - 1) / kKB, all = ctx + (N + kKB - 1) / kKB;
-  int best = 1;
-  int64_t best_cost = (base + cus - 1) / cus * (all + 6);
-  for (int s = 2; s <= 64 && static_cast<int64_t>(s - 1) * kMinPart < ctx; ++s) {
-    const int64_t cost = (base * s + cus - 1) / cus * ((all + s - 1) / s + 6) + 8;
-    if (cost < best_cost) {
-      best_cost = cost;
-      best = s;
+  const float busy = D == 128 ? 1.23f : 1.f;
+  struct Line {
+    int parts;
+    float slope, start;
+  };
+  auto price = [&](int s) {
+    const int64_t n = base * s, full = n / cus, rem = n % cus;
+    const float last = busy * static_cast<float>(rem) / static_cast<float>(cus);
+    Line l{s, (static_cast<float>(full) * busy + (rem ? (last > 1.f ? last : 1.f) : 0.f)) / static_cast<float>(s),
+           14.f * static_cast<float>(full + (rem ? 1 : 0))};
+    if (s > 1) {
+      l.slope *= 1.1f;
+      l.start = 1.1f * (l.start + 8.f + 4.f * static_cast<float>(n) / static_cast<float>(cus));
     }
+    return l;
+  };
+  CutRule rule{};
+  Line line[kMaxCuts];
+  int lines = 0;
+  const int64_t most = (ctx + kMinPart - 1) / kMinPart;
+  for (int rounds = 1; rounds <= kMaxCuts; ++rounds) {  // the most parts that fit these rounds of the chip
+    int64_t s = rounds * cus / base;
+    s = s < most ? s : most;
+    s = s < 64 ? s : 64;
+    if (s < 2 || s * bytes_per_part > kMaxPartBytes || (lines > 0 && line[lines - 1].parts == s)) continue;
+    line[lines++] = price(static_cast<int>(s));
   }
-  return best;
+  Line cur = price(1);
+  for (;;) {  // the next line to cross below the current one
+    float x = static_cast<float>(all);
+    int next = -1;
+    for (int i = 0; i < lines; ++i) {
+      if (line[i].slope >= cur.slope) continue;
+      const float cross = (line[i].start - cur.start) / (cur.slope - line[i].slope);
+      if (cross <= x) {
+        x = cross;
+        next = i;
+      }
+    }
+    if (next < 0) return rule;
+    cur = line[next];
+    rule.at[rule.n] = x > 0.f ? static_cast<int>(x) + 1 : 0;
+    rule.parts[rule.n++] = cur.parts;
+  }
 }
 
 struct AttnWorkspace {
+  CutRule cuts;
   int splits;
   size_t ml, total;  // (m, l) pairs first, then the outputs
 };
@@ -793,12 +894,14 @@ struct AttnWorkspace {
 AttnWorkspace attention_workspace(int B, int N, int H, int Hkv, int D, int64_t Pmax) {
   const int64_t R = static_cast<int64_t>(N) * (H / Hkv);
   const int64_t base = static_cast<int64_t>(B) * Hkv * ((R + kAttnRows - 1) / kAttnRows);
+  const int64_t rows = static_cast<int64_t>(B) * Hkv * R;
   AttnWorkspace w{};
-  w.splits = attention_splits(base, Pmax, N);
-  if (w.splits == 1 || base * w.splits >= (int64_t(1) << 31)) return AttnWorkspace{1, 0, 0};
-  const size_t rows = static_cast<size_t>(B) * Hkv * w.splits * R;
-  w.ml = (rows * sizeof(float2) + 255) & ~static_cast<size_t>(255);
-  w.total = w.ml + rows * D * sizeof(float);
+  w.cuts = attention_cuts(base, Pmax, N, D, rows * (D * sizeof(float) + sizeof(float2)));
+  w.splits = 1;
+  for (int i = 0; i < w.cuts.n; ++i) w.splits = w.cuts.parts[i] > w.splits ? w.cuts.parts[i] : w.splits;
+  if (w.splits == 1) return w;
+  w.ml = (static_cast<size_t>(rows) * w.splits * sizeof(float2) + 255) & ~static_cast<size_t>(255);
+  w.total = w.ml + static_cast<size_t>(rows) * w.splits * D * sizeof(float);
   return w;
 }
 
@@ -834,6 +937,14 @@ hipError_t launch_tree_attention(const TreeAttnArgs& a, void* workspace, size_t 
   const AttnWorkspace ws = attention_workspace(a.B, a.N, a.H, a.Hkv, a.D, a.Pmax);
   if (workspace && ws.total != 0 && ws_bytes >= ws.total) {
     p.splits = ws.splits;
+    p.cuts = ws.cuts;
+    const int heads = a.Hkv % 8 == 0 ? 8 : a.Hkv % 4 == 0 ? 4 : a.Hkv % 2 == 0 ? 2 : 1;
+    auto by = [](int d) { return FastDiv{d, ((uint64_t(1) << 32) + d - 1) / d}; };
+    p.split.heads = heads;
+    p.split.wgs = by(heads * p.groups);
+    p.split.seqs = by(a.B * (a.Hkv / heads));
+    p.split.groups = by(p.groups);
+    p.split.dealt = a.B * (a.Hkv / heads) * p.splits / 8 * 8 * heads * p.groups;
     p.part_ml = static_cast<float2*>(workspace);
     p.part_o = reinterpret_cast<float*>(static_cast<char*>(workspace) + ws.ml);
   }
@@ -862,7 +973,8 @@ hipError_t launch_tree_attention(const TreeAttnArgs& a, void* workspace, size_t 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.splits == 1) return e;
   const int64_t rows = static_cast<int64_t>(p.B) * p.Hkv * p.R;
-  const dim3 cgrid(static_cast<unsigned>((rows * 32 + kCombineThreads - 1) / kCombineThreads));
+  const int64_t blocks = (rows * 32 + kCombineThreads - 1) / kCombineThreads;
+  const dim3 cgrid(static_cast<unsigned>(blocks < kCombineGrid ? blocks : kCombineGrid));
   if (a.D == 128)
     hipLaunchKernelGGL((attention_combine_kernel<128>), cgrid, dim3(kCombineThreads), 0, stream, p);
   else

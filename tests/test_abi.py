@@ -308,6 +308,21 @@ def test_tree_attention_workspace_bytes():
     assert f(1, 65, 30, 8, 128, 16384) == 0 and f(1, 300, 32, 8, 128, 16384) == 0 and f(1, 65, 32, 8, 96, 16384) == 0
 
 
+def test_tree_attention_cut_is_priced():
+    """Shapes whose cut measured slower than the whole ranges stay whole (24 and 48 sequences over
+    4,096 keys: 176 -> 200 and 343 -> 359 us), and no call asks for more than 256 MiB of scratch,
+    however large the cache."""
+    f = ubt.lib().ubt_tree_attention_workspace_bytes
+    for B, P in ((20, 4096), (24, 4096), (28, 32768), (32, 32768), (48, 4096)):
+        assert f(B, 65, 32, 8, 128, P) == 0, (B, P)
+    assert f(24, 100, 16, 2, 128, 2048) == 0  # 101 -> 108 us
+    for B in (1, 2, 7, 25, 33, 64, 200):
+        for N, H, Hkv, D in ((65, 32, 8, 128), (256, 64, 4, 128), (129, 40, 8, 128), (17, 16, 2, 64)):
+            for P in (300, 5000, 32768, 131072, 2 ** 31 - 1):
+                assert f(B, N, H, Hkv, D, P) <= 257 << 20, (B, N, H, Hkv, D, P)
+    assert f(8, 65, 32, 8, 128, 4096) > 0 and f(16, 65, 32, 8, 128, 4096) > 0  # 171 -> 74, 171 -> 121 us
+
+
 def test_tree_attention_split_workspace_alignment():
     """A misaligned workspace is refused before any launch."""
     bad = ctypes.c_void_p(0x10010)

@@ -108,6 +108,10 @@ def test_tree_attention_small(B, N, H, Hkv, D, Pmax, plen, nn, out_dtype):
     (2, 256, 4, 1, 128, 600, (257, 600), (256, 130)),   # the shortest cut context with 8 tree blocks behind it
     (4, 129, 8, 2, 128, 700, (700, 256, 288, 31), (129, 1, 0, 64)),  # two row groups; an empty tree
     (1, 17, 4, 4, 64, 9000, (8500,), (17,)),            # a cache larger than the context
+    # a cache much larger than most contexts: sequences on both sides of every cut, and an odd
+    # number of (sequence, head, part) units
+    (3, 65, 20, 5, 128, 4000, (4000, 200, 700), (65, 65, 65)),
+    (12, 33, 8, 8, 128, 5000, (5000, 290, 620, 650, 800, 257, 0, 31, 4000, 640, 660, 1500), (33,) * 11 + (1,)),
 ])
 @pytest.mark.parametrize("out_dtype", ["f32", "bf16"])
 def test_tree_attention_split_keys(B, N, H, Hkv, D, Pmax, plen, nn, out_dtype):
