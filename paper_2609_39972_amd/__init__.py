@@ -159,6 +159,15 @@ def _scratch(n: int, device, stream) -> torch.Tensor | None:
         return torch.empty(n, dtype=torch.uint8, device=device)
 
 
+def _bytes(workspace: torch.Tensor | None) -> int:
+    """The size a workspace argument is passed with."""
+    if workspace is None:
+        return 0
+    if not workspace.is_contiguous():
+        raise ValueError("workspace must be contiguous")
+    return workspace.numel() * workspace.element_size()
+
+
 def _need_gpu(*ts: torch.Tensor) -> None:
     for t in ts:
         if t is not None and not t.is_cuda:
@@ -509,15 +518,29 @@ def draft_step_noalloc(logits: torch.Tensor, phi: torch.Tensor, psi: torch.Tenso
     return {**cand, "logq": logq, **out}
 
 
+def tree_attention_workspace(B: int, N: int, H: int, Hkv: int, D: int, Pmax: int,
+                             device="cuda") -> torch.Tensor | None:
+    """A workspace for :func:`tree_attention` (its contents are never read before they are
+    written), or None when the shape needs none."""
+    n = lib().ubt_tree_attention_workspace_bytes(B, N, H, Hkv, D, Pmax)
+    return torch.empty(n, dtype=torch.uint8, device=device) if n else None
+
+
 def tree_attention(q: torch.Tensor, k_cache: torch.Tensor | None, v_cache: torch.Tensor | None,
                    prefix_len: torch.Tensor, k_tree: torch.Tensor, v_tree: torch.Tensor, mask: torch.Tensor,
                    n_nodes: torch.Tensor, scale: float | None = None, out: torch.Tensor | None = None,
-                   lse: torch.Tensor | None = None, out_dtype=torch.bfloat16, stream=None):
+                   lse: torch.Tensor | None = None, out_dtype=torch.bfloat16, stream=None,
+                   workspace: torch.Tensor | None = None):
     """``ubt_tree_attention``: every tree node attends to the committed context and to
     its ancestors.  q ``[B, N, H, D]`` bf16; caches ``[B, P_max, H_kv, D]`` bf16 (or None
     with no context); k_tree / v_tree ``[B, N, H_kv, D]`` bf16; mask ``[B, N, words]``
-    int32 (uint32 bits); prefix_len, n_nodes int32 ``[B]``.  Returns (out, lse)."""
-    _need_gpu(q, k_cache, v_cache, prefix_len, k_tree, v_tree, mask, n_nodes)
+    int32 (uint32 bits); prefix_len, n_nodes int32 ``[B]``.  Returns (out, lse).
+
+    Shapes that would leave the chip idle run with their keys cut over several workgroups,
+    with scratch memory: ``workspace`` (from :func:`tree_attention_workspace`), or memory of
+    this call's own.  With ``out`` and ``lse`` given the call allocates nothing: without a
+    workspace the keys then stay whole."""
+    _need_gpu(q, k_cache, v_cache, prefix_len, k_tree, v_tree, mask, n_nodes, workspace)
     B, N, H, D = q.shape
     Hkv = k_tree.shape[2]
     Pmax = 0 if k_cache is None else k_cache.shape[1]
@@ -528,15 +551,16 @@ def tree_attention(q: torch.Tensor, k_cache: torch.Tensor | None, v_cache: torch
                 raise TypeError(f"{name} must be bfloat16")
     if scale is None:
         scale = D ** -0.5
+    if workspace is None and (out is None or lse is None):
+        workspace = _scratch(lib().ubt_tree_attention_workspace_bytes(B, N, H, Hkv, D, Pmax), q.device, stream)
     if out is None:
         out = torch.empty(B, N, H, D, dtype=out_dtype, device=q.device)
     if lse is None:
         lse = torch.empty(B, N, H, dtype=torch.float32, device=q.device)
-    n = lib().ubt_tree_attention_workspace_bytes(B, N, H, Hkv, D, Pmax)
-    workspace = _scratch(n, q.device, stream)
     st = lib().ubt_tree_attention_split(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(prefix_len), Pmax, _ptr(k_tree),
                                         _ptr(v_tree), _ptr(mask), _ptr(n_nodes), B, N, H, Hkv, D, float(scale),
-                                        _ptr(out), _dtype_code(out), _ptr(lse), _ptr(workspace), n, _stream(stream))
+                                        _ptr(out), _dtype_code(out), _ptr(lse), _ptr(workspace), _bytes(workspace),
+                                        _stream(stream))
     _check("ubt_tree_attention", st)
     return out, lse
 
@@ -605,7 +629,9 @@ class DraftStep:
     """One draft step (top-K -> selector -> tree + mask) with every buffer preallocated.
 
     ``run(logits)`` issues the library calls on the current stream and allocates nothing,
-    so it can be captured into a HIP graph.  By default it is ``ubt_topk``, then the
+    so it can be captured into a HIP graph.  Its buffers are made on the stream that is current
+    then (the one-call workspace is filled there): a first run on another stream has to be
+    ordered after that.  By default it is ``ubt_topk``, then the
     selector and the search through ``ubt_draft_tree``; ``one_call=True`` makes the whole
     step one ``ubt_draft_step`` call; ``fused=False``, ``with_delta`` or ``debug`` use the
     separate ``ubt_topk``, ``ubt_bigram_scores`` and ``ubt_build_tree`` calls."""
@@ -629,8 +655,6 @@ class DraftStep:
         self.fused = fused and not with_delta and not debug
         self.one_call = one_call and self.fused
         self.workspace = draft_step_workspace(B, gamma, V, K, logit_dtype, dev) if self.one_call else None
-        if self.one_call and not torch.cuda.is_current_stream_capturing():
-            torch.cuda.current_stream(dev).synchronize()  # run() may be given any stream: the fill is done
         self.topk_workspace = None if self.one_call else topk_workspace(B, gamma, V, K, logit_dtype, dev)
         self.logit_dtype_code = UBT_BF16 if logit_dtype == torch.bfloat16 else UBT_F32
 

@@ -90,3 +90,30 @@ def test_lm_head_makes_its_workspace_on_the_calls_stream(fake, stream, handle):
     ubt.lm_head_topk(_bf16(20, 64), _bf16(500, 64), 8, stream=stream)
     assert [s for _, s in made] == [handle]
     assert lib.calls[-1][1][-1] == handle
+
+
+def _attention(**kw):
+    B, N, H, Hkv, D, P = 1, 5, 4, 2, 64, 100
+    i32 = dict(dtype=torch.int32)
+    return ubt.tree_attention(_bf16(B, N, H, D), _bf16(B, P, Hkv, D), _bf16(B, P, Hkv, D), torch.zeros(B, **i32),
+                              _bf16(B, N, Hkv, D), _bf16(B, N, Hkv, D), torch.zeros(B, N, 1, **i32),
+                              torch.zeros(B, **i32), **kw)
+
+
+def test_attention_scratch(fake):
+    """Scratch of its own only where the call allocates anyway; a workspace is passed on."""
+    lib, made = fake
+    lib.sizes["ubt_tree_attention_workspace_bytes"] = 4096
+    _attention()
+    assert [a for a, _ in made] == [(4096,)] and lib.calls[-1][1][-2] == 4096
+    _attention(stream=Side())
+    assert made[-1] == ((4096,), 77)
+    n = len(made)
+    given = dict(out=_bf16(1, 5, 4, 64), lse=torch.zeros(1, 5, 4))
+    _attention(**given)
+    assert len(made) == n and lib.calls[-1][1][-3:-1] == (None, 0)
+    ws = torch.zeros(8192, dtype=torch.uint8)
+    _attention(workspace=ws, **given)
+    assert len(made) == n and lib.calls[-1][1][-3:-1] == (ws.data_ptr(), 8192)
+    with pytest.raises(ValueError):
+        _attention(workspace=ws[::2], **given)
