@@ -79,10 +79,14 @@ __host__ __device__ inline bool fast_tree_fits(int gamma, int K, int W) {
   return (K == 4 || K == 8 || K == 16) && W * K <= 512 && W <= kFastMaxW && gamma * W <= kFastMaxGW;
 }
 
-// The four-wave search: every other shape of up to 64 parents and 1024 supertree nodes.  Its
-// depth costs about 1.9 us whatever K is, the general kernel's 3.5 us (K = 10, W = 10) to
-// 16 us (K = 64, W = 20); the one-wave search above stays the faster one where it applies.
+// The four-wave search: every other shape of up to 64 parents and 1024 supertree nodes.  15
+// positions, one sequence, this against the general kernel: K = 10 21.1 / 26.7 us at W = 2,
+// 29.0 / 53.1 at W = 10, 43.4 / 89.6 at W = 24; K = 24, W = 24 50.6 / 142; K = 64, W = 20
+// 49.9 / 218.  With one parent there is nothing to share out: K = 48 26.9 / 23.5, K = 3 22.4 /
+// 21.7, K = 24 still 22.6 / 26.2.  The one-wave search above is the faster one wherever it
+// applies: K = 16 24.5 / 25.7 us at W = 8, 37.2 / 47.4 at W = 24; K = 4 17.4 / 21.6 at W = 4.
 __host__ __device__ inline bool wide_tree_fits(int gamma, int K, int W) {
+  if (W == 1 && K != 64 && (K <= 3 || K > 32)) return false;
   return K <= 64 && W <= kWideMaxW && gamma * W <= kFastMaxGW;
 }
 

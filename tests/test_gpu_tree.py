@@ -122,6 +122,8 @@ def test_tree_mask_matches_fused_and_oracle():
     (2, 1, 10, 10, 20), (3, 5, 1, 4, 8), (2, 9, 2, 5, 30), (2, 11, 10, 10, 48), (2, 7, 15, 13, 60),
     (2, 6, 17, 17, 100), (2, 15, 24, 24, 128), (2, 5, 31, 25, 128), (2, 32, 32, 32, 255), (2, 8, 33, 9, 40),
     (1, 16, 63, 64, 255), (2, 16, 64, 64, 255), (3, 7, 64, 33, 100), (2, 20, 64, 20, 100), (2, 6, 16, 33, 200),
+    # one parent: the general kernel for K <= 3 and K > 32, this one between
+    (2, 9, 3, 1, 9), (2, 9, 5, 1, 9), (2, 9, 32, 1, 9), (2, 9, 33, 1, 9),
 ])
 def test_four_wave_search(B, gamma, K, W, budget, tie_frac, levels):
     _compare(B, gamma, K, W, budget, seed=K * 100 + W, tie_frac=tie_frac, levels=levels)
