@@ -543,9 +543,11 @@ __device__ __forceinline__ void expand_depths(const TreeArgs& a, const FastSmem&
 // Selection: each parent's best child is a wave maximum over its register, and the
 // smallest of these W maxima is a lower bound of the W-th best entry (they are W distinct
 // entries).  The entries at or above that bound (the survivors, typically a few dozen)
-// hold F_d; they are compacted to the survivors' stage and each survivor's rank among
-// them (score desc, then index) is counted, so the survivors of rank < W are F_d, already
-// ranked.  All waves return with the same `total`.
+// hold F_d; a wave with very many of them keeps its W best, so at most 256 are left (equal
+// scores everywhere, K = 64, W = 24, 15 positions: 1,703 us without that cut, 65 with it).
+// They are compacted to the survivors' stage and each survivor's rank among them (score
+// desc, then index) is counted, so the survivors of rank < W are F_d, already ranked.  All
+// waves return with the same `total`.
 constexpr int kK64Waves = 4;
 
 // KC: K = 64 exactly (KC = 64 and kExact), else K <= KC in {16, 32, 64}.  RW: registers of
@@ -663,6 +665,17 @@ __device__ __forceinline__ void expand_depths_wide(const TreeArgs& a, const Fast
     for (int i = 0; i < RW; ++i) {
       sel[i] = ballot(key[i] >= kbound);
       cnt += popc(sel[i]);
+    }
+    // F_d takes at most w_d entries of one wave, its best by (score, index): with many tied
+    // scores far more reach the bound, and ranking them all is quadratic in their number.  Up
+    // to 64 per wave, one round of ranking is as quick as the selection (W = 17, K = 64: 46.2 us,
+    // with a selection whenever cnt > w_d 51.7).
+    if (__builtin_expect(cnt > max(w_d, min(2 * w_d + 16, kWave)), 0)) {
+      uint32_t best = 0u;
+#pragma unroll
+      for (int i = 0; i < RW; ++i) best = max(best, key[i]);
+      select_best<RW>(key, cnt, w_d, sel, wave_umax(best), kbound);
+      cnt = w_d;
     }
     if (lane == 0) s_cnt[w] = static_cast<uint32_t>(cnt);
     lds_barrier();

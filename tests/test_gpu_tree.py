@@ -114,7 +114,7 @@ def test_tree_mask_matches_fused_and_oracle():
     del to_np
 
 
-@pytest.mark.parametrize("tie_frac,levels", [(0.0, 64), (0.8, 4)])
+@pytest.mark.parametrize("tie_frac,levels", [(0.0, 64), (0.8, 4), (0.0, 1)])
 @pytest.mark.parametrize("B,gamma,K,W,budget", [
     # The four-wave search: each class of K at its edges (1, 2, 15, 17, 31 .. 33, 63, 64), W at
     # the edges of the register counts (4, 5, 8, 9, 12, 13, 16, 17, 24, 25, 32, 33, 64),
@@ -127,3 +127,37 @@ def test_tree_mask_matches_fused_and_oracle():
 ])
 def test_four_wave_search(B, gamma, K, W, budget, tie_frac, levels):
     _compare(B, gamma, K, W, budget, seed=K * 100 + W, tie_frac=tie_frac, levels=levels)
+
+
+@pytest.mark.parametrize("K,W", [(24, 24), (64, 12), (64, 32)])
+def test_tied_scores_take_no_longer(K, W):
+    """A frontier of equal scores is ranked in about the time of distinct ones (every entry of
+    the W best's bound was ranked against every other: 5 to 30 times the time).  The bound of
+    three times leaves room for noise; 1.1 to 1.3 times were measured."""
+    import torch
+
+    import paper_2609_39972_amd as ubt
+
+    B, gamma = 4, 15
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K)
+    ids = torch.arange(K, device="cuda", dtype=torch.int32).expand(B, gamma, K).contiguous()
+    anchor = torch.zeros(B, dtype=torch.int32, device="cuda")
+
+    def us(q):
+        out = ubt.build_tree(anchor, ids, q, W, 64)
+        best = float("inf")
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                ubt.build_tree(anchor, ids, q, W, 64, out=out)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 50.0)
+        return best
+
+    distinct = us(torch.randn(B, gamma, K, K, generator=g, device="cuda").log_softmax(3))
+    tied = us(torch.full((B, gamma, K, K), -1.0, device="cuda"))
+    print(f"K={K} W={W}: distinct {distinct:.1f} us, tied {tied:.1f} us", flush=True)
+    assert tied < 3 * distinct
