@@ -117,3 +117,32 @@ def test_attention_scratch(fake):
     assert len(made) == n and lib.calls[-1][1][-3:-1] == (ws.data_ptr(), 8192)
     with pytest.raises(ValueError):
         _attention(workspace=ws[::2], **given)
+
+
+@pytest.mark.parametrize("rows,dtype", [(1, torch.bfloat16), (15, torch.bfloat16), (15, torch.float32)])
+def test_topk_makes_one_call_and_no_scratch(fake, rows, dtype):
+    """Few long rows cost the host no size query, allocation or second launch unless the caller
+    keeps a workspace, with and without outputs given."""
+    lib, made = fake
+    lib.sizes["ubt_topk_workspace_bytes"] = 4096
+    x = torch.zeros(1, rows, 140000, dtype=dtype)
+    out = ubt.topk(x, 64)
+    ubt.topk(x, 64, out=out)
+    assert lib.names() == ["ubt_topk_split"] * 2 and made == []
+    assert lib.calls[-1][1][-3:-1] == (None, 0)
+    ws = torch.zeros(4096, dtype=torch.uint8)
+    ubt.topk(x, 64, out=out, workspace=ws)
+    assert lib.calls[-1][1][-3:-1] == (ws.data_ptr(), 4096) and made == []
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_draft_step_run_allocates_nothing(fake, dtype):
+    """Whatever dtype the logits have, and whatever dtype the step was made for."""
+    lib, made = fake
+    lib.sizes["ubt_topk_workspace_bytes"] = 0
+    step = ubt.DraftStep(1, 3, 70000, 8, 4, 8, _bf16(70000, 16), _bf16(70000, 16), _bf16(1, 3, 16),
+                         torch.zeros(1, dtype=torch.int32), [1.0] * 3, [1.0] * 3)
+    lib.sizes["ubt_topk_workspace_bytes"] = 4096
+    n = len(made)
+    step.run(torch.zeros(1, 3, 70000, dtype=dtype))
+    assert len(made) == n
