@@ -420,8 +420,8 @@ def tree_mask(parent: torch.Tensor, n_nodes: torch.Tensor, out: torch.Tensor | N
 
 def draft_step_workspace(B: int, gamma: int, V: int, K: int, dtype=torch.bfloat16, device="cuda") -> torch.Tensor:
     """A zero-filled workspace for :func:`draft_step` (uint8, 256-byte aligned).  Each
-    call resets the counters it uses, so one workspace serves consecutive calls on one
-    stream.  The fill runs on the current stream; a first use on another one has to be
+    call resets the counters it uses, so one workspace serves consecutive calls of this shape
+    on one stream.  The fill runs on the current stream; a first use on another one has to be
     ordered after it."""
     code = UBT_BF16 if dtype == torch.bfloat16 else UBT_F32
     n = lib().ubt_draft_step_full_workspace_bytes(B, gamma, V, K, code)
@@ -449,8 +449,20 @@ def draft_step(logits: torch.Tensor, phi: torch.Tensor, psi: torch.Tensor, gate:
                cand: dict | None = None, logq: torch.Tensor | None = None, out: dict | None = None,
                with_mask: bool = True, stream=None) -> dict:
     """The whole draft step (``topk`` then ``draft_tree``) in one library call; returns the
-    candidates, ``logq`` and the tree outputs."""
-    _need_gpu(logits, phi, psi, gate, anchor)
+    candidates, ``logq`` and the tree outputs.
+
+    A given ``workspace`` is used by the shapes that need one (rows on 16-byte boundaries in
+    one launch, K = 64 with W <= 16) and left alone by all others.  With none the call makes
+    one for its shape, as :class:`DraftStep` does once: then every shape may use it
+    (``ubt_draft_step_full``), so a program that makes many calls is faster with a DraftStep."""
+    return _draft_step(logits, phi, psi, gate, anchor, alpha, lam, K, W, budget, zeta, workspace, workspace is None,
+                       cand, logq, out, with_mask, stream)
+
+
+def _draft_step(logits, phi, psi, gate, anchor, alpha, lam, K, W, budget, zeta, workspace, full, cand, logq, out,
+                with_mask, stream) -> dict:
+    """``full``: the workspace is made here, or was made for this shape and serves no other."""
+    _need_gpu(logits, phi, psi, gate, anchor, workspace)
     if logits.dim() != 3 or logits.stride(2) != 1:
         raise ValueError("logits must be [B, gamma, V] with unit stride along V")
     for n, t in (("phi", phi), ("psi", psi), ("gate", gate), ("anchor", anchor)):
@@ -471,14 +483,13 @@ def draft_step(logits: torch.Tensor, phi: torch.Tensor, psi: torch.Tensor, gate:
         with _on(stream, dev):  # the fill must be ordered before the launch
             workspace = draft_step_workspace(B, gamma, V, K, logits.dtype, dev)
     a, l = _host_f32(alpha, gamma), _host_f32(lam, gamma)
-    # The workspace is zero-filled and serves one stream, whatever the shape.
-    st = lib().ubt_draft_step_full(_ptr(logits), _dtype_code(logits), B, gamma, V, logits.stride(0), logits.stride(1),
-                                   K, _ptr(phi), _ptr(psi), _ptr(gate), _dtype_code(phi), r, _ptr(anchor), a, l, W,
-                                   budget, float(zeta), _ptr(cand["cand_ids"]), _ptr(cand["cand_logit"]),
-                                   _ptr(cand.get("cand_logprob")), _ptr(cand.get("lse")), _ptr(logq),
-                                   _ptr(out["n_nodes"]), _ptr(out["token"]), _ptr(out["parent"]), _ptr(out["depth"]),
-                                   _ptr(out["cand_rank"]), _ptr(out["score"]), _ptr(out.get("mask")),
-                                   _ptr(workspace), workspace.numel(), _stream(stream))
+    call = lib().ubt_draft_step_full if full else lib().ubt_draft_step
+    st = call(_ptr(logits), _dtype_code(logits), B, gamma, V, logits.stride(0), logits.stride(1), K, _ptr(phi),
+              _ptr(psi), _ptr(gate), _dtype_code(phi), r, _ptr(anchor), a, l, W, budget, float(zeta),
+              _ptr(cand["cand_ids"]), _ptr(cand["cand_logit"]), _ptr(cand.get("cand_logprob")), _ptr(cand.get("lse")),
+              _ptr(logq), _ptr(out["n_nodes"]), _ptr(out["token"]), _ptr(out["parent"]), _ptr(out["depth"]),
+              _ptr(out["cand_rank"]), _ptr(out["score"]), _ptr(out.get("mask")), _ptr(workspace), _bytes(workspace),
+              _stream(stream))
     _check("ubt_draft_step", st)
     return {**cand, "logq": logq, **out}
 
@@ -679,8 +690,9 @@ class DraftStep:
 
     def run(self, logits: torch.Tensor, stream=None) -> dict:
         if self.one_call:
-            draft_step(logits, self.phi, self.psi, self.gate, self.anchor, self.alpha, self.lam, self.K, self.W,
-                       self.budget, self.zeta, self.workspace, self.cand, self.sel["logq"], self.tree, stream=stream)
+            _draft_step(logits, self.phi, self.psi, self.gate, self.anchor, self.alpha, self.lam, self.K, self.W,
+                        self.budget, self.zeta, self.workspace, True, self.cand, self.sel["logq"], self.tree, True,
+                        stream)
             return {**self.cand, **self.sel, **self.tree}
         topk(logits, self.K, self.cand, stream=stream, workspace=self.topk_workspace)
         if self.fused:

@@ -146,3 +146,21 @@ def test_draft_step_run_allocates_nothing(fake, dtype):
     n = len(made)
     step.run(torch.zeros(1, 3, 70000, dtype=dtype))
     assert len(made) == n
+
+
+def test_a_given_step_workspace_keeps_its_old_contract(fake):
+    """A caller's workspace may serve calls of other shapes, which leave it alone in ubt_draft_step
+    (their counters would lie in another shape's partial results); only a workspace made for the
+    call or by DraftStep goes to ubt_draft_step_full."""
+    lib, made = fake
+    args = (_bf16(2, 3, 100), _bf16(100, 16), _bf16(100, 16), _bf16(2, 3, 16), torch.zeros(2, dtype=torch.int32),
+            [1.0] * 3, [1.0] * 3)
+    ws = torch.zeros(1024, dtype=torch.uint8)
+    ubt.draft_step(*args, 4, 2, 6, workspace=ws)
+    assert lib.calls[-1][0] == "ubt_draft_step" and lib.calls[-1][1][-3:-1] == (ws.data_ptr(), 1024)
+    assert made == []
+    ubt.draft_step(*args, 4, 2, 6)
+    assert lib.calls[-1][0] == "ubt_draft_step_full" and len(made) == 1
+    step = ubt.DraftStep(2, 3, 100, 4, 2, 6, *args[1:], one_call=True)
+    step.run(args[0])
+    assert lib.calls[-1][0] == "ubt_draft_step_full" and lib.calls[-1][1][-3] == step.workspace.data_ptr()

@@ -328,3 +328,30 @@ def test_step_on_a_side_stream_without_a_workspace(kw):
     got = to_np(got)
     for k in EXACT_KEYS:
         assert np.array_equal(ref[k], got[k]), f"{k} differs on a side stream"
+
+
+def test_one_workspace_between_shapes():
+    """A caller's workspace used by a 16-byte aligned shape, with calls of unaligned rows and of
+    K = 64, W = 21 in between: these leave it alone, and every call gives what it gives with a
+    workspace of its own."""
+    import torch
+
+    import paper_2609_39972_amd as ubt
+    from gpu_util import say, to_np
+
+    say("draft_step: one workspace between shapes")
+    ws = None
+    shapes = [_custom(306, B=8, L=9, V=20000), _custom(307, B=2, L=3, V=12287), _custom(306, B=8, L=9, V=20000),
+              _custom(308, B=2, L=9, V=6000, K=64, W=21, r=32, budget=90), _custom(306, B=8, L=9, V=20000)]
+    ws = torch.zeros(max(ubt.draft_step_workspace(w.B, w.gamma, w.V, w.K).numel() for w in shapes),
+                     dtype=torch.uint8, device="cuda")
+    for w in shapes:
+        d = synth.inputs(w, 0)
+        a = _args(w, d, w.W)
+        args = (_logits_tensor(w, d), a[6], a[7], a[8], a[9], a[10], a[11], w.K, w.W, w.budget, w.zeta)
+        own = to_np(ubt.draft_step(*args))
+        got = to_np(ubt.draft_step(*args, workspace=ws))
+        for k in EXACT_KEYS:
+            assert np.array_equal(own[k], got[k]), f"{w.describe()}: {k} differs"
+        assert ubt.draft_step_error(ws) == 0
+        assert not ws.cpu().numpy()[:256 + 4 * w.B * w.gamma].any()
