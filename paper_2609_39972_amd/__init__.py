@@ -259,17 +259,22 @@ def lm_head_topk(h: torch.Tensor, w_lm: torch.Tensor, K: int, out: dict | None =
     return out
 
 
-def _host_vals(x):
-    """The values as a list or tuple that ctypes converts to C floats by itself."""
+def _c_floats(x, n: int) -> ctypes.Array:
+    """The values of ``x`` as n C floats: ctypes converts numbers by itself, anything else that
+    float() takes (one-element tensors, text) is converted here."""
     vals = x.tolist() if hasattr(x, "tolist") else x
-    return vals if type(vals) in (list, tuple) else list(vals)
+    vals = vals if type(vals) in (list, tuple) else list(vals)
+    try:
+        return (ctypes.c_float * n)(*vals)
+    except TypeError:
+        return (ctypes.c_float * n)(*[float(v) for v in (x if hasattr(x, "tolist") else vals)])
 
 
 def _host_f32(x, n: int) -> ctypes.Array:
-    vals = _host_vals(x)
-    if len(vals) != n:
-        raise ValueError(f"expected {n} values, got {len(vals)}")
-    return (ctypes.c_float * n)(*vals)
+    x = x if hasattr(x, "__len__") else list(x)
+    if len(x) != n:
+        raise ValueError(f"expected {n} values, got {len(x)}")
+    return _c_floats(x, n)
 
 
 def bigram_scores(phi: torch.Tensor, psi: torch.Tensor, gate: torch.Tensor, anchor: torch.Tensor,
@@ -619,8 +624,7 @@ def tree_kl_loss(logits: torch.Tensor, cand: dict, target_logits: torch.Tensor, 
         raise ValueError("logits and target_logits must be [B, gamma, V] with unit stride along V")
     if target_logits.dtype != logits.dtype:
         raise TypeError("target_logits must have the logits' dtype")
-    a = (ctypes.c_float * gamma)(*_host_vals(alpha))
-    l = (ctypes.c_float * gamma)(*_host_vals(lam))
+    a, l = _c_floats(alpha, gamma), _c_floats(lam, gamma)
     if out is None:
         f32 = dict(dtype=torch.float32, device=logits.device)
         out = dict(loss=torch.empty(B, gamma, **f32), kl=torch.empty(B, gamma, **f32),

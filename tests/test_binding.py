@@ -164,3 +164,35 @@ def test_a_given_step_workspace_keeps_its_old_contract(fake):
     step = ubt.DraftStep(2, 3, 100, 4, 2, 6, *args[1:], one_call=True)
     step.run(args[0])
     assert lib.calls[-1][0] == "ubt_draft_step_full" and lib.calls[-1][1][-3] == step.workspace.data_ptr()
+
+
+def _loss(scales):
+    B, gamma, V, K, r = 1, 3, 100, 4, 16
+    cand = dict(cand_ids=torch.zeros(B, gamma, K, dtype=torch.int32), cand_logit=torch.zeros(B, gamma, K),
+                lse=torch.zeros(B, gamma))
+    return ubt.tree_kl_loss(_bf16(B, gamma, V), cand, _bf16(B, gamma, V), torch.zeros(B, gamma, dtype=torch.int32),
+                            torch.zeros(B, dtype=torch.int32), _bf16(V, r), _bf16(V, r), _bf16(B, gamma, r), scales,
+                            scales)
+
+
+@pytest.mark.parametrize("scales", [
+    [1.0, 0.5, 2.0], (1, 0.5, 2), torch.tensor([1.0, 0.5, 2.0]), torch.tensor([[1.0], [0.5], [2.0]]),
+    torch.tensor([1.0, 0.5, 2.0]).numpy(), [torch.tensor(1.0), torch.tensor([0.5]), 2.0], ["1", "0.5", "2"],
+], ids=["list", "tuple", "tensor", "column", "numpy", "tensors", "text"])
+def test_objective_takes_any_scales(fake, scales):
+    """Depth scales in every form that float() converts one by one."""
+    lib, _ = fake
+    _loss(scales)
+    args = lib.calls[-1][1]
+    assert [list(a) for a in args if hasattr(a, "_length_")] == [[1.0, 0.5, 2.0]] * 2
+
+
+@pytest.mark.parametrize("scales", [[1.0, 0.5, 2.0], torch.tensor([1.0, 0.5, 2.0]), ["1", "0.5", "2"]],
+                         ids=["list", "tensor", "text"])
+def test_step_takes_any_scales(fake, scales):
+    lib, _ = fake
+    args = (_bf16(2, 3, 100), _bf16(100, 16), _bf16(100, 16), _bf16(2, 3, 16), torch.zeros(2, dtype=torch.int32))
+    ubt.draft_step(*args, scales, iter([1.0, 0.5, 2.0]), 4, 2, 6)
+    assert [list(a) for a in lib.calls[-1][1] if hasattr(a, "_length_")] == [[1.0, 0.5, 2.0]] * 2
+    with pytest.raises(ValueError):
+        ubt.draft_step(*args, [1.0, 0.5], scales, 4, 2, 6)
