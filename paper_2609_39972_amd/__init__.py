@@ -214,10 +214,16 @@ def topk(logits: torch.Tensor, K: int, out: dict | None = None, with_logprob: bo
     return out
 
 
-def lm_head_workspace(M: int, d: int, V: int, K: int, device="cuda") -> torch.Tensor:
+def lm_head_workspace(M: int, d: int, V: int, K: int, device="cuda", full: bool = True) -> torch.Tensor:
     """A workspace for :func:`lm_head_topk` (uint8, 256-byte aligned; its contents are
-    never read before they are written, so it serves calls of any shape in turn)."""
-    n = lib().ubt_lm_head_topk_full_workspace_bytes(M, d, V, K)
+    never read before they are written, so it serves calls of any shape in turn).
+
+    Calls that run as a matrix product (more than 16 rows, or a d that the kernel for 16 rows
+    does not take) keep the logits of up to 512 rows in it: about 4 min(M, 512) V bytes.
+    ``full=False`` leaves that room out (a few MB): such calls then read the head once per 16
+    rows of h."""
+    size = lib().ubt_lm_head_topk_full_workspace_bytes if full else lib().ubt_lm_head_topk_workspace_bytes
+    n = size(M, d, V, K)
     if n == 0:
         raise ValueError("invalid shape for ubt_lm_head_topk")
     ws = torch.empty(n, dtype=torch.uint8, device=device)
@@ -231,7 +237,7 @@ def lm_head_topk(h: torch.Tensor, w_lm: torch.Tensor, K: int, out: dict | None =
     """Candidates and softmax statistics of the logits ``h @ w_lm.T`` without forming them:
     ``h [..., d]`` and ``w_lm [V, d]``, both contiguous bf16.  Outputs have h's leading
     shape: ``cand_ids``/``cand_logit``/``cand_logprob`` [..., K] and ``lse`` [...]."""
-    _need_gpu(h, w_lm)
+    _need_gpu(h, w_lm, workspace)
     _contig(h, "h")
     _contig(w_lm, "w_lm")
     if h.dtype != torch.bfloat16 or w_lm.dtype != torch.bfloat16:
@@ -254,7 +260,7 @@ def lm_head_topk(h: torch.Tensor, w_lm: torch.Tensor, K: int, out: dict | None =
             workspace = lm_head_workspace(M, d, V, K, dev)
     st = lib().ubt_lm_head_topk(_ptr(h), _ptr(w_lm), M, d, V, K, _ptr(out["cand_ids"]), _ptr(out["cand_logit"]),
                                 _ptr(out.get("cand_logprob")), _ptr(out.get("lse")), _ptr(workspace),
-                                workspace.numel(), _stream(stream))
+                                _bytes(workspace), _stream(stream))
     _check("ubt_lm_head_topk", st)
     return out
 

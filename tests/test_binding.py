@@ -196,3 +196,45 @@ def test_step_takes_any_scales(fake, scales):
     assert [list(a) for a in lib.calls[-1][1] if hasattr(a, "_length_")] == [[1.0, 0.5, 2.0]] * 2
     with pytest.raises(ValueError):
         ubt.draft_step(*args, [1.0, 0.5], scales, 4, 2, 6)
+
+
+def test_lm_head_workspace_sizes(monkeypatch):
+    """The full size by default, the plain one on request."""
+    lib = Lib({"ubt_lm_head_topk_full_workspace_bytes": 1 << 20, "ubt_lm_head_topk_workspace_bytes": 1 << 12})
+    monkeypatch.setattr(ubt, "lib", lambda: lib)
+    real = torch.empty
+    made = []
+
+    def empty(n, **kw):
+        made.append(n)
+        buf = real(n + 256, **kw)
+        return buf[-buf.data_ptr() % 256:][:n]
+
+    monkeypatch.setattr(torch, "empty", empty)
+    assert ubt.lm_head_workspace(40, 512, 30000, 8, device="cpu").numel() == 1 << 20
+    assert ubt.lm_head_workspace(40, 512, 30000, 8, device="cpu", full=False).numel() == 1 << 12
+    assert made == [1 << 20, 1 << 12]
+
+
+@pytest.mark.parametrize("call", ["topk", "lm_head", "step", "attention"])
+def test_only_the_workspace_on_the_host(fake, monkeypatch, call):
+    """The workspace is looked at, not only the inputs."""
+    lib, _ = fake
+    ws = torch.zeros(4096, dtype=torch.uint8)
+
+    def need(*ts):
+        if any(t is ws for t in ts):
+            raise ValueError("host")
+
+    monkeypatch.setattr(ubt, "_need_gpu", need)
+    with pytest.raises(ValueError, match="host"):
+        if call == "topk":
+            ubt.topk(_bf16(1, 2, 100), 4, workspace=ws)
+        elif call == "lm_head":
+            ubt.lm_head_topk(_bf16(20, 64), _bf16(500, 64), 8, workspace=ws)
+        elif call == "step":
+            ubt.draft_step(_bf16(2, 3, 100), _bf16(100, 16), _bf16(100, 16), _bf16(2, 3, 16),
+                           torch.zeros(2, dtype=torch.int32), [1.0] * 3, [1.0] * 3, 4, 2, 6, workspace=ws)
+        else:
+            _attention(workspace=ws)
+    assert lib.calls == []
