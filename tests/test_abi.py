@@ -283,8 +283,9 @@ def test_lm_head_workspace_bytes():
 
 
 def test_lm_head_full_workspace_bytes():
-    """The full query is the plain one up to 16 rows where the d-split kernel takes them, adds
-    room for the logits of up to 512 rows past that, and rejects what the plain one rejects."""
+    """The full query is the plain one up to 16 rows where the d-split kernel takes them (d = 512 n
+    for n = 2 .. 8 and 10), adds room for the logits of up to 512 rows past that, and rejects what the
+    plain one rejects."""
     L = ubt.lib()
     plain, full = L.ubt_lm_head_topk_workspace_bytes, L.ubt_lm_head_topk_full_workspace_bytes
     for d, V, K in ((2560, 151936, 64), (96, 1000, 4), (2880, 50257, 8)):
@@ -292,6 +293,11 @@ def test_lm_head_full_workspace_bytes():
         assert full(17, d, V, K) >= 17 * V * 4
         assert full(480, d, V, K) >= max(480 * V * 4, plain(480, d, V, K))
         assert full(5000, d, V, K) >= 512 * V * 4
+    V, K = 151936, 8
+    for d in range(32, 8193, 32):
+        split = d % 512 == 0 and d // 512 in (2, 3, 4, 5, 6, 7, 8, 10)
+        assert (full(16, d, V, K) == plain(16, d, V, K)) == split, d
+        assert split or full(16, d, V, K) >= 16 * V * 4, d
     assert full(0, 2560, 1000, 8) == 0
     assert full(40, 48, 1000, 8) == 0
     assert full(40, 2560, 2 ** 31 - 1, 64) == 0

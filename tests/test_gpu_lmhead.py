@@ -3,9 +3,11 @@ against the fp64 oracle, through the C ABI.
 
 * Integer-valued hidden states and head rows: every logit is an exact integer in fp32,
   whatever the accumulation order, so ids and logits must match bit for bit, and the many
-  equal logits test the tie order (id asc) across tiles, waves and workgroups.  Hidden
-  sizes cover both kernels: the one that splits d over a workgroup's waves (d a multiple
-  of 512, every slice width) and the one that does not.
+  equal logits test the tie order (id asc) across tiles, waves and workgroups.  With the
+  binding's full workspace, calls of up to 16 rows run the kernel that splits d over a
+  workgroup's waves where it takes d (every slice width) and all others run the matrix
+  product; with a workspace of the plain query's size, calls of several row groups run the
+  split kernel or the one that does not split d.
 * Gaussian operands at the drafting block of the paper's latency breakdown (16 rows of a
   2560-wide hidden state against a 151,936-token head), at d = 4096, and at small and
   ragged shapes (M not a multiple of 16, V not a multiple of 16, d/32 odd): logits within
@@ -155,7 +157,7 @@ def test_lm_head_product_integer_inputs_exact(M, d, V, K):
     print(f"lm_head product M={M} d={d} V={V} K={K}", flush=True)
     hb, wb = _int_bits(M, d, V, seed=M * 1000 + d + V, lo=-3, hi=3)
     ws = ubt.lm_head_workspace(M, d, V, K)
-    assert ws.numel() >= ubt.lib().ubt_lm_head_topk_workspace_bytes(M, d, V, K)
+    assert ws.numel() >= min(M, 512) * V * 4  # room for the logits: the product runs
     ws.fill_(0x7F)  # as fp32: 3.4e38, above every logit
     parity.check_lm_head(_run(hb, wb, K, workspace=ws), hb, wb, K, exact=True)
 
@@ -186,3 +188,22 @@ def test_lm_head_product_and_row_groups_agree():
     for k in ("cand_ids", "cand_logit"):
         np.testing.assert_array_equal(a[k], b[k])
     np.testing.assert_allclose(a["lse"], b["lse"], rtol=1e-6)
+
+
+@pytest.mark.parametrize("M,d,V,K", [
+    # d split over the waves, two and three row groups (the last of 1, 4 and 16 rows)
+    (17, 2048, 30000, 16), (20, 2560, 70001, 64), (48, 1024, 20000, 8),
+    # the kernel that does not split d: up to 16 rows and several groups, d / 32 odd and even, d = 512
+    (5, 96, 40001, 8), (16, 2880, 40001, 8), (33, 96, 60001, 16), (17, 2880, 20001, 8), (33, 512, 40000, 8),
+])
+def test_lm_head_row_groups_integer_inputs_exact(M, d, V, K):
+    """A workspace of the plain size, too small for the product, keeps the call on the kernels
+    that read the head once per 16 rows."""
+    import paper_2609_39972_amd as ubt
+
+    print(f"lm_head row groups M={M} d={d} V={V} K={K}", flush=True)
+    hb, wb = _int_bits(M, d, V, seed=M * 1000 + d + V, lo=-3, hi=3)
+    ws = ubt.lm_head_workspace(M, d, V, K, full=False)
+    assert ws.numel() < min(M, 512) * V * 4  # no room for the logits
+    ws.fill_(0x7F)
+    parity.check_lm_head(_run(hb, wb, K, workspace=ws), hb, wb, K, exact=True)

@@ -287,6 +287,8 @@ def test_step_unaligned_rows_one_launch(kw):
                         logit_dtype=torch.bfloat16 if w.dtype == "bf16" else torch.float32)
     a = to_np(one.run(_logits_tensor(w, d)))
     one.check()
+    words = 256 + (w.B * w.gamma * 4 + 255) // 256 * 256
+    assert one.workspace[words:].any(), "no partial results: the separate kernels ran"
     one.workspace = torch.zeros(16, dtype=torch.uint8, device="cuda")
     b = to_np(one.run(_logits_tensor(w, d)))
     torch.cuda.synchronize()
@@ -355,3 +357,65 @@ def test_one_workspace_between_shapes():
             assert np.array_equal(own[k], got[k]), f"{w.describe()}: {k} differs"
         assert ubt.draft_step_error(ws) == 0
         assert not ws.cpu().numpy()[:256 + 4 * w.B * w.gamma].any()
+
+
+@pytest.mark.parametrize("kw", [
+    dict(B=1, L=16, V=151936, K=64, W=12, r=64, budget=64),                 # then selector + search in one launch
+    dict(B=2, L=5, V=131081, K=64, W=20, r=32, budget=60),                  # unaligned rows, W > 16
+    dict(B=1, L=9, V=140000, K=8, W=6, feat_dtype="f32"),                   # fp32 features: separate kernels
+    dict(B=3, L=6, V=100001, K=10, W=7, r=32, dtype="f32", budget=30),      # fp32 rows, the four-wave search
+])
+def test_step_with_the_cut_sweep(kw):
+    """Few long rows: the sweep inside the step is cut over several workgroups, with its lists at
+    the workspace's end, next to the words that must stay zero.  Twice on one workspace."""
+    import torch
+
+    import paper_2609_39972_amd as ubt
+    from gpu_util import to_np
+
+    w = _custom(309, **kw)
+    d = synth.inputs(w, 0)
+    code = 1 if w.dtype == "bf16" else 0
+    lists = ubt.lib().ubt_topk_workspace_bytes(w.B, w.gamma, w.V, w.K, code)
+    assert lists > 0
+    _check(w, w.W, d=d)
+    one = ubt.DraftStep(*_args(w, d, w.W), one_call=True,
+                        logit_dtype=torch.bfloat16 if w.dtype == "bf16" else torch.float32)
+    logits = _logits_tensor(w, d)
+    a = to_np(one.run(logits))
+    one.check()
+    assert one.workspace[-lists:].any(), "the sweep was not cut"
+    assert not one.workspace[:256 + 4 * w.B * w.gamma].any(), "words that must stay zero"
+    b = to_np(one.run(logits))
+    torch.cuda.synchronize()
+    for k in EXACT_KEYS:
+        assert np.array_equal(a[k], b[k]), f"{k} differs between identical calls"
+
+
+@pytest.mark.parametrize("kw", [
+    dict(B=3, L=6, V=12288, K=8, W=5),                          # aligned: one launch
+    dict(B=3, L=6, V=12287, K=4, W=3, budget=12),               # unaligned: the separate kernels
+    dict(B=2, L=9, V=6000, K=64, W=16, r=32, budget=60),        # selector + search in one launch
+    dict(B=2, L=9, V=6000, K=64, W=21, r=32, budget=90),        # W > 16: the separate kernels
+    dict(B=1, L=6, V=151936, K=64, W=12, r=32, budget=40),      # long rows, never cut in ubt_draft_step
+])
+def test_plain_draft_step(kw):
+    """ubt_draft_step (a workspace given to draft_step) against the separate calls: the shapes it
+    promises to leave the workspace alone for do so."""
+    import torch
+
+    import paper_2609_39972_amd as ubt
+    from gpu_util import say, to_np
+
+    w = _custom(310, **kw)
+    say(f"ubt_draft_step: {w.describe()}")
+    d = synth.inputs(w, 0)
+    a = _args(w, d, w.W)
+    logits = _logits_tensor(w, d)
+    sep = to_np(ubt.DraftStep(*a, fused=False).run(logits))
+    ws = ubt.draft_step_workspace(w.B, w.gamma, w.V, w.K)
+    got = to_np(ubt.draft_step(logits, a[6], a[7], a[8], a[9], a[10], a[11], w.K, w.W, w.budget, w.zeta, workspace=ws))
+    for k in EXACT_KEYS:
+        assert np.array_equal(sep[k], got[k]), f"{k} differs"
+    assert ws.any().item() == (w.V == 12288), "partial results"
+    assert ubt.draft_step_error(ws) == 0

@@ -44,7 +44,7 @@ def _tree(rng, B: int, N: int, nn):
     return parent, token, mask
 
 
-def _run_attention(d, plen, mask, nn, scale, out_dtype, D):
+def _run_attention(d, plen, mask, nn, scale, out_dtype, D, given=False):
     import torch
 
     import paper_2609_39972_amd as ubt
@@ -52,9 +52,14 @@ def _run_attention(d, plen, mask, nn, scale, out_dtype, D):
 
     kc = dev_values(d["k_cache"]) if d["k_cache"].shape[1] > 0 else None
     vc = dev_values(d["v_cache"]) if d["v_cache"].shape[1] > 0 else None
-    out, lse = ubt.tree_attention(dev_values(d["q"]), kc, vc, dev_i32(plen), dev_values(d["k_tree"]),
+    q = dev_values(d["q"])
+    outs = {}
+    if given:  # nothing left to allocate: no scratch either
+        outs = dict(out=torch.full(q.shape, 7.0, dtype=out_dtype, device="cuda"),
+                    lse=torch.full(q.shape[:3], 7.0, device="cuda"))
+    out, lse = ubt.tree_attention(q, kc, vc, dev_i32(plen), dev_values(d["k_tree"]),
                                   dev_values(d["v_tree"]), dev_i32(mask.view(np.int32)), dev_i32(nn), scale=scale,
-                                  out_dtype=out_dtype)
+                                  out_dtype=out_dtype, **outs)
     torch.cuda.synchronize()
     return out.float().cpu().numpy().astype(np.float64), lse.cpu().numpy().astype(np.float64)
 
@@ -126,6 +131,30 @@ def test_tree_attention_split_keys(B, N, H, Hkv, D, Pmax, plen, nn, out_dtype):
     say(f"tree_attention split B={B} N={N} H={H} Hkv={Hkv} D={D} P={plen} nn={nn} out={out_dtype}")
     assert ubt.lib().ubt_tree_attention_workspace_bytes(B, N, H, Hkv, D, Pmax) > 0
     test_tree_attention_small(B, N, H, Hkv, D, Pmax, plen, nn, out_dtype)
+
+
+@pytest.mark.parametrize("B,N,H,Hkv,D,Pmax,plen,nn", [
+    (1, 65, 32, 8, 128, 3001, (3001,), (65,)), (3, 33, 16, 2, 64, 2000, (2000, 257, 0), (33, 20, 5)),
+    (2, 256, 4, 1, 128, 600, (257, 600), (256, 130)),
+])
+def test_tree_attention_whole_keys(B, N, H, Hkv, D, Pmax, plen, nn):
+    """The same shapes without scratch (out and lse given, no workspace): the keys stay whole."""
+    import torch
+
+    import paper_2609_39972_amd as ubt
+    from gpu_util import say
+
+    say(f"tree_attention whole B={B} N={N} H={H} Hkv={Hkv} D={D} P={plen} nn={nn}")
+    assert ubt.lib().ubt_tree_attention_workspace_bytes(B, N, H, Hkv, D, Pmax) > 0
+    rng = np.random.default_rng(1000 + N + D)
+    plen, nn = np.array(plen, np.int32), np.array(nn, np.int32)
+    _, _, mask = _tree(rng, B, N, nn)
+    d = synth.verify_inputs(N * 7 + D, B, N, H, Hkv, D, Pmax)
+    scale = 1.0 / math.sqrt(D)
+    out, lse = _run_attention(d, plen, mask, nn, scale, torch.float32, D, given=True)
+    ref, ref_lse = V.tree_attention_fast(d["q"], d["k_cache"], d["v_cache"], plen, d["k_tree"], d["v_tree"], mask, nn,
+                                         scale)
+    _check_attention(out, lse, ref, ref_lse, d, False)
 
 
 def test_tree_attention_on_draft_trees():
