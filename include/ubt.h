@@ -120,8 +120,9 @@ ubt_status_t ubt_topk_split(const void* logits, ubt_dtype_t dt, int B, int gamma
                             size_t ws_bytes, hipStream_t stream);
 
 /* ------------------------------------------------------------------------------------
- * ubt_lm_head_topk -- the LM-head projection followed by ubt_topk's outputs, without
- * writing the logits.  Background, "DFlash & DFlash 2": the proposer's hidden state h_i
+ * ubt_lm_head_topk -- the LM-head projection followed by ubt_topk's outputs; no logits
+ * are handed out (up to 16 rows never leave the chip, the matrix product for more rows
+ * keeps them in the workspace).  Background, "DFlash & DFlash 2": the proposer's hidden state h_i
  * is mapped to its logits by the frozen target LM head, u_i = W_lm h_i.  Method /
  * Unigram Proposer, Eq. (ubtree-unigram) and "Candidate Sets": LSE_i and C_i as for
  * ubt_topk.
@@ -138,11 +139,12 @@ ubt_status_t ubt_topk_split(const void* logits, ubt_dtype_t dt, int B, int gamma
  * workspace, ws_bytes : device scratch of at least ubt_lm_head_topk_workspace_bytes(M, d,
  *            V, K) bytes, 256-byte aligned, owned by the caller; no state is kept in it
  *            between calls, and calls that share it must not overlap.
- * M <= 16: one pass over the head, bound by the bandwidth of reading w_lm.  M > 16, or d no
- * multiple of 512: with a workspace of ubt_lm_head_topk_full_workspace_bytes(M, d, V, K)
- * bytes (room for the fp32 logits of up to 512 rows, about 4 * min(M, 512) * V bytes; never
- * less than the plain query) the projection is one matrix product; with less, the head is
- * read once per 16 rows of h.  Inputs must be finite; non-finite logits give unspecified
+ * M <= 16 and d = 512 n with n in {2, .., 8, 10}: one pass over the head, bound by the
+ * bandwidth of reading w_lm.  M > 16, or any other d: with a workspace of
+ * ubt_lm_head_topk_full_workspace_bytes(M, d, V, K) bytes (room for the fp32 logits of up to
+ * 512 rows, about 4 * min(M, 512) * V bytes; never less than the plain query) the projection
+ * is one matrix product that writes the logits there; with less, the head is read once per
+ * 16 rows of h.  Inputs must be finite; non-finite logits give unspecified
  * candidates.  Returns UBT_ERR_WORKSPACE for a missing, small or
  * misaligned workspace, UBT_ERR_UNSUPPORTED for shapes the workspace query rejects
  * (it returns 0 for them: very large V at large K).
@@ -268,10 +270,11 @@ ubt_status_t ubt_draft_tree(const void* phi_tab, const void* psi_tab, const void
  * runs the search.  That launch needs `workspace`: device memory of at least
  * ubt_draft_step_workspace_bytes(B, gamma, V, K, dt) bytes (about
  * 256 + B * gamma * (4 + 2 * (8K + 4))), 256-byte aligned, owned by the caller and
- * ZERO-FILLED before its first use.  It holds an error word (the first 4 bytes), one
+ * ZERO-FILLED before its first use by a shape (where the counters end depends on B * gamma,
+ * and partial results of another shape may lie among them).  It holds an error word (the first 4 bytes), one
  * chunk counter per row (from byte 256) and the chunks' partial results; each call
  * resets the counters it raised, so one workspace serves any number of consecutive calls
- * on one stream; calls that may overlap need separate workspaces.  A chunk's results are
+ * of that shape on one stream; calls that may overlap need separate workspaces.  A chunk's results are
  * exchanged through agent-scope atomic stores and loads, and its row counter is raised
  * only after those stores have completed.  Every wait inside the launch is bounded (1 s).
  * If one runs out of time (a
@@ -305,7 +308,8 @@ ubt_status_t ubt_draft_step(const void* logits, ubt_dtype_t dt, int B, int gamma
                             hipStream_t stream);
 
 /* ubt_draft_step_full -- ubt_draft_step for callers whose workspace is zero-filled before
- * its first use and never shared by overlapping calls, for every shape: rows that are not
+ * its first use, never shared by overlapping calls, and used by calls of this shape alone, for
+ * every shape: rows that are not
  * 16-byte aligned then take the one launch too (with at least
  * ubt_draft_step_workspace_bytes(...) bytes), and so does K = 64 with 16 < W <= 32 its
  * selector + search launch.  With a missing, short or misaligned workspace those shapes run
@@ -465,9 +469,9 @@ ubt_status_t ubt_tree_attention(const void* q, const void* k_cache, const void* 
 /* ubt_tree_attention_split -- the same call with a workspace (256-byte aligned device
  * memory, contents never read before they are written; calls that share it must not
  * overlap).  With at least ubt_tree_attention_workspace_bytes(...) bytes (0: the shape has
- * nothing to gain) the keys of a (sequence, head) are cut into parts that run on their own
- * compute units, and a second kernel combines them in a fixed order; with NULL or less it
- * is ubt_tree_attention.  The two agree within the rounding of the weights to bf16 (each
+ * nothing to gain; at most 257 MiB) the keys of a (sequence, head) are cut into parts that run
+ * on their own compute units, as many as the sequence's own length is worth, and a second
+ * kernel combines them in a fixed order; with NULL or less it is ubt_tree_attention.  The two agree within the rounding of the weights to bf16 (each
  * part rounds relative to its own running maximum).  UBT_ERR_WORKSPACE: misaligned. */
 size_t ubt_tree_attention_workspace_bytes(int B, int N, int H, int H_kv, int D, int64_t P_max);
 ubt_status_t ubt_tree_attention_split(const void* q, const void* k_cache, const void* v_cache,

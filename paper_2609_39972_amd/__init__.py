@@ -234,7 +234,7 @@ def lm_head_workspace(M: int, d: int, V: int, K: int, device="cuda", full: bool 
 
 def lm_head_topk(h: torch.Tensor, w_lm: torch.Tensor, K: int, out: dict | None = None,
                  workspace: torch.Tensor | None = None, with_logprob: bool = True, stream=None) -> dict:
-    """Candidates and softmax statistics of the logits ``h @ w_lm.T`` without forming them:
+    """Candidates and softmax statistics of the logits ``h @ w_lm.T``, which are not handed out:
     ``h [..., d]`` and ``w_lm [V, d]``, both contiguous bf16.  Outputs have h's leading
     shape: ``cand_ids``/``cand_logit``/``cand_logprob`` [..., K] and ``lse`` [...]."""
     _need_gpu(h, w_lm, workspace)

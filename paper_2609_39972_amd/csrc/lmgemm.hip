@@ -552,11 +552,12 @@ int gm_grid() {
 
 size_t lm_gemm_workspace_bytes(int M, int d, int64_t V, int K) {
   // Up to 16 rows fit one tile of the row-group kernels, which read the head once: the one that
-  // splits d streams it as fast (15 rows, d = 2560: 132 us), the other one (d no multiple of 512)
-  // at less than half the rate.
+  // splits d (512 n, n in {2, .., 8, 10}) streams it as fast (15 rows, d = 2560: 132 us), the other
+  // one at less than half the rate (15 rows, d = 2880: 317 us, here 156).
   if ((M <= 16 && lm_head_split_fits(d)) || V > (int64_t(1) << 24)) return 0;
   const GemmPlan p = gm_plan(M < kGmMaxRows ? M : kGmMaxRows, V, gm_grid());
-  // The last rows of a longer call: fewer rows, so never more bytes.
+  // The last rows of a longer call: fewer row blocks cut V into more ranges, so at a small V their
+  // statistics may take more room than those of 512 rows.
   const GemmPlan q = M > kGmMaxRows ? gm_plan((M - 1) % kGmMaxRows + 1, V, gm_grid()) : p;
   if (static_cast<int64_t>(p.ranges) * p.gpr > kGmMaxGroups || static_cast<int64_t>(q.ranges) * q.gpr > kGmMaxGroups)
     return 0;

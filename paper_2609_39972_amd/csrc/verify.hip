@@ -27,8 +27,9 @@
 // the softmax on the vector ALU the other keeps the matrix core busy; each needs at most
 // 256 registers.  The output wave runs one block behind.  A score wave computes the next
 // block's scores tile by tile right after the tile's weights, so its own MFMAs overlap its
-// vector work too.  K and V are staged through registers two steps ahead of their LDS
-// stores, the output waves on even steps and the score waves on odd ones.  The running
+// vector work too.  K and V go straight from global memory into rings of four blocks in LDS:
+// the output waves load the K block of four steps ahead, the score waves the V block of three
+// steps ahead, which the output waves transpose within LDS.  The running
 // maximum is raised only when a score exceeds it by more than 2^8 (weights then stay
 // below 256, exact enough in fp32 and bf16); it is checked on each block's scores as soon
 // as they exist, and the factor by which the output must be rescaled goes to the output
