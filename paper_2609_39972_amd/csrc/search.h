@@ -668,9 +668,10 @@ __device__ __forceinline__ void expand_depths_wide(const TreeArgs& a, const Fast
     }
     // F_d takes at most w_d entries of one wave, its best by (score, index): with many tied
     // scores far more reach the bound, and ranking them all is quadratic in their number.  Up
-    // to 64 per wave, one round of ranking is as quick as the selection (W = 17, K = 64: 46.2 us,
-    // with a selection whenever cnt > w_d 51.7).
-    if (__builtin_expect(cnt > max(w_d, min(2 * w_d + 16, kWave)), 0)) {
+    // to 64 per wave (w_d is no larger), the one round of ranking that they take is quicker than
+    // the selection: W = 17, K = 64 46.2 us, with a selection whenever cnt > w_d 51.7; W = 6, K = 32
+    // 46.4 us per step, with one from 2 w_d + 16 on 48.3.
+    if (__builtin_expect(cnt > kWave, 0)) {
       uint32_t best = 0u;
 #pragma unroll
       for (int i = 0; i < RW; ++i) best = max(best, key[i]);

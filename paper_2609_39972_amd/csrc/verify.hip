@@ -87,6 +87,7 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 // From `at[i]` key blocks on, a sequence is cut into `parts[i]` parts (the last entry that
 // applies); below at[0] it stays whole.
 constexpr int kMaxCuts = 8;
+constexpr int kMaxRounds = 8;  // most workgroups of a cut launch per compute unit
 struct CutRule {
   int n;
   int at[kMaxCuts], parts[kMaxCuts];
@@ -101,11 +102,11 @@ struct FastDiv {
   }
 };
 
-// The numbering of a cut launch's workgroups, in units of `wgs`.  There are at most kMaxCuts
+// The numbering of a cut launch's workgroups, in units of `wgs`.  There are at most kMaxRounds
 // workgroups per compute unit, so the numbers divided here stay far below 2^16.
 struct SplitGrid {
   int heads;  // heads per unit
-  int dealt;  // workgroups of the units that are dealt out over the XCDs, a multiple of 8
+  int dealt;  // workgroups of the units that are dealt out over the XCDs, a multiple of 8 units
   FastDiv wgs, seqs, groups;  // workgroups per unit, units per part, row groups
 };
 
@@ -433,11 +434,12 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attention_kernel(AttnArgs p
     // its heads on different XCDs 56.2).  Units are dealt out over the XCDs one at a time, part 0
     // of all sequences first: a sequence shorter than the cache has fewer parts than the grid,
     // and consecutive units on one XCD would leave the others idle (12 sequences, 512 of 32,768
-    // keys: 100 us, whole 40).
+    // keys: 100 us, whole 40).  Each round of 8 starts one XCD further, so that a long sequence's
+    // parts do not all meet on one.
     const int dealt = p.split.dealt;
     const int i = L < dealt ? L / 8 : L - dealt;
     const int at = p.split.wgs(i);
-    const int u = L < dealt ? at * 8 + L % 8 : dealt / p.split.wgs.d + at;
+    const int u = L < dealt ? at * 8 + (L + at) % 8 : dealt / p.split.wgs.d + at;
     part = p.split.seqs(u);
     const int in = i - at * p.split.wgs.d;
     const int head = p.split.groups(in);
@@ -823,67 +825,97 @@ namespace {
 // are on the device: the host prices each cut as a line over the blocks per sequence (all
 // sequences alike), the kernels look up the cheapest line for each sequence's own length.
 //
-// Prices in key blocks of one workgroup (1.15 us at D = 128, 260 query rows): a workgroup
-// starts and ends in 14; with every unit busy a block takes 1.23 (D = 128: the caches deliver
-// 2.95 TB/s); the second kernel takes 8, and 4 more per chip's worth of parts whose fp32 results
-// are written and read again.  Over 100 measured shapes (1 to 64 sequences, 128 to 32,768 keys)
-// the price is within 10% of the time from 40 us on.  One sequence over 4,096 keys 170 us whole,
-// 37 cut; 16 sequences 171 and 121; 24 sequences 176 and 200: not cut.  A cut has to promise a
-// tenth in a full cache, because a context that turns out too short for it still pays for the
-// second launch and the workgroups that leave at once (one sequence, 128 of 32,768 keys: 25 and
-// 28 us; 33 sequences, 2,048 keys: 192 and 201).
+// Prices in microseconds, by the kernel's tiles per pair (1, 3, 5).  A workgroup takes 0.72, 0.98
+// or 1.16 per block (D = 64: 0.945) and, to start and end, 4, 11 or 15 (D = 64: 0.045 per query
+// row).  Those of several rounds run one after the other; with more than four fifths of the units
+// busy all of them slow down, by a fifth when the chip is full (D = 64: not at all).  The second
+// kernel takes 5 to 9, and up to 6 per chip's worth of parts whose fp32 results are written and
+// read again.  Over 150 measured shapes (1 to 64 sequences, 128 to 32,768 keys, 37 to 516 query
+// rows) that is within 15% of the time from 40 us on.  At 260 rows, one sequence over 4,096 keys
+// 170 us whole, 37 cut; 16 sequences 171 and 121; 24 sequences 176 and 200, 48 sequences 343 and
+// 359: not cut.
+//
+// A call is cut only if that promises 5% in a full cache: a context that turns out too short for
+// it still pays for the second launch and the workgroups that leave at once (one sequence, 128 of
+// 32,768 keys: 25 and 28 us; 33 sequences, 2,048 keys: 192 and 201).  Inside a cut call most of
+// the second kernel is paid anyway, and the longest workgroup counts: its sequences are cut from
+// shorter lengths on (5 sequences of 354 to 709 keys: 45 us, whole below 19 blocks 55).
 constexpr int64_t kMaxPartBytes = int64_t(256) << 20;  // scratch of one call
 
-CutRule attention_cuts(int64_t base, int64_t Pmax, int N, int D, int64_t bytes_per_part) {
+// Tiles per pair: enough for the group's rows (the kernel's instances: 1, 3 or 5; rows past R
+// are empty tiles).
+int tiles_per_pair(int64_t R) {
+  const int tiles = static_cast<int>(((R < kAttnRows ? R : kAttnRows) + 15) / 16);
+  return (tiles + kPairs - 1) / kPairs;
+}
+
+CutRule attention_cuts(int64_t base, int64_t R, int64_t Pmax, int N, int D, int64_t bytes_per_part) {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
     cus = 256;
   const int64_t ctx = (Pmax + kKB - 1) / kKB, all = ctx + (N + kKB - 1) / kKB;
-  const float busy = D == 128 ? 1.23f : 1.f;
+  const int tw = tiles_per_pair(R);
+  const float in_group = static_cast<float>(R < kAttnRows ? R : kAttnRows);
+  const float block_us = D == 64 ? 0.945f : tw <= 1 ? 0.72f : tw <= 3 ? 0.98f : 1.16f;
+  const float ends_us = D == 64 ? 0.045f * in_group : tw <= 1 ? 4.f : tw <= 3 ? 11.f : 15.f;
+  const float busy = D == 64 ? 1.f : 1.23f;
+  const float rows = in_group / 260.f;
+  const float second_us = 5.f + 4.f * rows;
   struct Line {
-    int parts;
+    int parts, fewest;  // given out; what a length needs room for
     float slope, start;
   };
   auto price = [&](int s) {
-    const int64_t n = base * s, full = n / cus, rem = n % cus;
-    const float last = busy * static_cast<float>(rem) / static_cast<float>(cus);
-    Line l{s, (static_cast<float>(full) * busy + (rem ? (last > 1.f ? last : 1.f) : 0.f)) / static_cast<float>(s),
-           14.f * static_cast<float>(full + (rem ? 1 : 0))};
-    if (s > 1) {
-      l.slope *= 1.1f;
-      l.start = 1.1f * (l.start + 8.f + 4.f * static_cast<float>(n) / static_cast<float>(cus));
-    }
+    const float load = static_cast<float>(base * s) / static_cast<float>(cus);
+    const float rounds = static_cast<float>((base * s + cus - 1) / cus);
+    const float steps = rounds > busy * load ? rounds : busy * load;
+    Line l{s, s, block_us * steps / static_cast<float>(s), 3.f + ends_us * rounds};
+    if (s > 1) l.start += second_us + 6.f * rows * static_cast<float>(D) / 128.f * load;
     return l;
   };
   CutRule rule{};
-  Line line[kMaxCuts];
+  Line line[1 + kMaxRounds];
   int lines = 0;
-  const int64_t most = (ctx + kMinPart - 1) / kMinPart;
-  for (int rounds = 1; rounds <= kMaxCuts; ++rounds) {  // the most parts that fit these rounds of the chip
-    int64_t s = rounds * cus / base;
-    s = s < most ? s : most;
-    s = s < 64 ? s : 64;
-    if (s < 2 || s * bytes_per_part > kMaxPartBytes || (lines > 0 && line[lines - 1].parts == s)) continue;
-    line[lines++] = price(static_cast<int>(s));
+  int64_t most = (ctx + kMinPart - 1) / kMinPart;
+  most = most < 64 ? most : 64;
+  auto add = [&](int64_t s) {
+    if (s >= 2 && s <= most && s * bytes_per_part <= kMaxPartBytes && (lines == 0 || line[lines - 1].parts < s))
+      line[lines++] = price(static_cast<int>(s));
+  };
+  // The most parts that fit 1, 2, ... rounds of the chip.  Within one round the lengths that give
+  // fewer parts than that are cut as often as they can be: from where two parts pay on.
+  add(cus / base > 2 ? 2 : 0);
+  for (int rounds = 1; rounds <= kMaxRounds; ++rounds) {
+    const int64_t s = rounds * cus / base;
+    add(s < most ? s : most);
   }
-  Line cur = price(1);
-  for (;;) {  // the next line to cross below the current one
+  if (lines > 1 && cus / base > 2) line[0].parts = line[1].parts;
+  const Line whole = price(1);
+  Line cur = whole;
+  cur.start += second_us - 3.f;
+  while (rule.n < kMaxCuts) {  // the next line to cross below the current one
     float x = static_cast<float>(all);
     int next = -1;
     for (int i = 0; i < lines; ++i) {
       if (line[i].slope >= cur.slope) continue;
-      const float cross = (line[i].start - cur.start) / (cur.slope - line[i].slope);
+      // Not below the length that has blocks for as many parts.
+      const float least = static_cast<float>((line[i].fewest - 1) * kMinPart + 1 + all - ctx);
+      const float at = (line[i].start - cur.start) / (cur.slope - line[i].slope);
+      const float cross = at > least ? at : least;
       if (cross <= x) {
         x = cross;
         next = i;
       }
     }
-    if (next < 0) return rule;
+    if (next < 0) break;
     cur = line[next];
-    rule.at[rule.n] = x > 0.f ? static_cast<int>(x) + 1 : 0;
+    rule.at[rule.n] = static_cast<int>(x) + 1;
     rule.parts[rule.n++] = cur.parts;
   }
+  const float full = static_cast<float>(all);
+  if (rule.n == 0 || 1.05f * (cur.slope * full + cur.start) > whole.slope * full + whole.start) rule.n = 0;
+  return rule;
 }
 
 struct AttnWorkspace {
@@ -897,7 +929,7 @@ AttnWorkspace attention_workspace(int B, int N, int H, int Hkv, int D, int64_t P
   const int64_t base = static_cast<int64_t>(B) * Hkv * ((R + kAttnRows - 1) / kAttnRows);
   const int64_t rows = static_cast<int64_t>(B) * Hkv * R;
   AttnWorkspace w{};
-  w.cuts = attention_cuts(base, Pmax, N, D, rows * (D * sizeof(float) + sizeof(float2)));
+  w.cuts = attention_cuts(base, R, Pmax, N, D, rows * (D * sizeof(float) + sizeof(float2)));
   w.splits = 1;
   for (int i = 0; i < w.cuts.n; ++i) w.splits = w.cuts.parts[i] > w.splits ? w.cuts.parts[i] : w.splits;
   if (w.splits == 1) return w;
@@ -945,14 +977,18 @@ hipError_t launch_tree_attention(const TreeAttnArgs& a, void* workspace, size_t 
     p.split.wgs = by(heads * p.groups);
     p.split.seqs = by(a.B * (a.Hkv / heads));
     p.split.groups = by(p.groups);
-    p.split.dealt = a.B * (a.Hkv / heads) * p.splits / 8 * 8 * heads * p.groups;
+    // An XCD has 32 compute units: units that fill them evenly are all dealt out whole (the last
+    // round may hold numbers past the last unit, which leave at once), else the rest goes one
+    // workgroup at a time.
+    const int units = a.B * (a.Hkv / heads) * p.splits;
+    const int rest = 32 % (heads * p.groups) == 0 ? 7 : 0;
+    p.split.dealt = (units + rest) / 8 * 8 * heads * p.groups;
     p.part_ml = static_cast<float2*>(workspace);
     p.part_o = reinterpret_cast<float*>(static_cast<char*>(workspace) + ws.ml);
   }
-  const dim3 grid(static_cast<unsigned>(p.B * p.Hkv * p.groups * p.splits));
-  // Tiles per pair: enough for the group's rows (1, 3 or 5; rows past R are empty tiles).
-  const int tiles = (min(p.R, kAttnRows) + 15) / 16;
-  const int tw = (tiles + kPairs - 1) / kPairs;
+  const int all = p.B * p.Hkv * p.groups * p.splits;
+  const dim3 grid(static_cast<unsigned>(all > p.split.dealt ? all : p.split.dealt));
+  const int tw = tiles_per_pair(p.R);
 #define UBT_ATTN(D, TW)                                                                                    \
   do {                                                                                                    \
     if (p.splits > 1)                                                                                     \
