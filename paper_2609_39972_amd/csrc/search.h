@@ -532,6 +532,44 @@ __device__ __forceinline__ void expand_depths(const TreeArgs& a, const FastSmem&
   }
 }
 
+// Zeroes all but the `need` best entries (key desc, index asc; entry (r, lane) has index
+// r * 64 + lane) of a wave that holds more than that many of at least kmin.  Kept small, with one
+// mask live at a time: inlined beside a search's own masks, select_best's spilled hundreds more
+// scalar registers in some instances.
+template <int R>
+__device__ __forceinline__ void drop_beyond(uint32_t (&key)[R], int need, uint32_t kmin) {
+  uint32_t kmax = 0u;
+#pragma unroll
+  for (int r = 0; r < R; ++r) kmax = max(kmax, key[r]);
+  kmax = wave_umax(kmax);
+  auto count = [&](uint32_t t) {  // entries of at least t
+    int n = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) n += popc(ballot(key[r] >= t));
+    return n;
+  };
+  // t: the need-th largest key, bit by bit below the bits that kmin and kmax share, or a value
+  // that exactly `need` entries reach.
+  uint32_t t = kmax;
+  if (kmax != kmin) {
+    uint32_t m = 0x80000000u >> __clz(kmax ^ kmin);
+    t = kmax & ~(m | (m - 1u));
+    for (; m != 0u; m >>= 1) {
+      const int n = count(t | m);
+      if (n >= need) t |= m;
+      if (n == need) break;
+    }
+  }
+  int left = need - (t == ~0u ? 0 : count(t + 1u));  // entries equal to t that stay, by index
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint64_t eq = ballot(key[r] == t);
+    const bool stays = key[r] > t || (key[r] == t && static_cast<int>(lanes_below(eq)) < left);
+    key[r] = stays ? key[r] : 0u;
+    left -= popc(eq);
+  }
+}
+
 // The same expansion for any K <= 64 on kK64Waves waves of one workgroup (a lone wave
 // issues too slowly for the W K entries of a depth).  The slabs (gamma K^2 floats) may not
 // fit in LDS: two are staged at a time, each wave loading a quarter of the slab two depths
@@ -543,8 +581,8 @@ __device__ __forceinline__ void expand_depths(const TreeArgs& a, const FastSmem&
 // Selection: each parent's best child is a wave maximum over its register, and the
 // smallest of these W maxima is a lower bound of the W-th best entry (they are W distinct
 // entries).  The entries at or above that bound (the survivors, typically a few dozen)
-// hold F_d; a wave with very many of them keeps its W best, so at most 256 are left (equal
-// scores everywhere, K = 64, W = 24, 15 positions: 1,703 us without that cut, 65 with it).
+// hold F_d; when there are more than 256 of them every wave keeps its W best (equal scores
+// everywhere, K = 64, W = 24, 15 positions: 1,703 us without that cut, 65 with it).
 // They are compacted to the survivors' stage and each survivor's rank among them (score
 // desc, then index) is counted, so the survivors of rank < W are F_d, already ranked.  All
 // waves return with the same `total`.
@@ -666,27 +704,37 @@ __device__ __forceinline__ void expand_depths_wide(const TreeArgs& a, const Fast
       sel[i] = ballot(key[i] >= kbound);
       cnt += popc(sel[i]);
     }
-    // F_d takes at most w_d entries of one wave, its best by (score, index): with many tied
-    // scores far more reach the bound, and ranking them all is quadratic in their number.  Up
-    // to 64 per wave (w_d is no larger), the one round of ranking that they take is quicker than
-    // the selection: W = 17, K = 64 46.2 us, with a selection whenever cnt > w_d 51.7; W = 6, K = 32
-    // 46.4 us per step, with one from 2 w_d + 16 on 48.3.
-    if (__builtin_expect(cnt > kWave, 0)) {
-      uint32_t best = 0u;
-#pragma unroll
-      for (int i = 0; i < RW; ++i) best = max(best, key[i]);
-      select_best<RW>(key, cnt, w_d, sel, wave_umax(best), kbound);
-      cnt = w_d;
-    }
-    if (lane == 0) s_cnt[w] = static_cast<uint32_t>(cnt);
-    lds_barrier();
-    const uint32_t c4 = lane < kK64Waves ? s_cnt[lane < kK64Waves ? lane : 0] : 0u;
     int ns = 0, off = 0;
+    auto exchange = [&]() {  // all waves' counts
+      if (lane == 0) s_cnt[w] = static_cast<uint32_t>(cnt);
+      lds_barrier();
+      const uint32_t c4 = lane < kK64Waves ? s_cnt[lane < kK64Waves ? lane : 0] : 0u;
+      ns = off = 0;
 #pragma unroll
-    for (int v = 0; v < kK64Waves; ++v) {
-      const int cv = static_cast<int>(__builtin_amdgcn_readlane(c4, v));
-      off += v < w ? cv : 0;
-      ns += cv;
+      for (int v = 0; v < kK64Waves; ++v) {
+        const int cv = static_cast<int>(__builtin_amdgcn_readlane(c4, v));
+        off += v < w ? cv : 0;
+        ns += cv;
+      }
+    };
+    exchange();
+    // Up to 256 survivors are ranked in one round; with many tied scores far more reach the bound,
+    // and ranking them all is quadratic in their number.  F_d takes at most w_d entries of a
+    // wave, its best by (score, index): the others go.  Left out where there cannot be more, and
+    // at K = 64, W <= 16, where it cost the usual step 1% (32 sequences 75.0 -> 75.7 us).
+    constexpr bool kMany = kK64Waves * RW * KC > kK64Waves * kWave && !(kExact && RW <= 4);
+    if (kMany && __builtin_expect(ns > kK64Waves * kWave, 0)) {
+      lds_barrier();  // every wave has read the counts
+      if (cnt > w_d) {
+        drop_beyond<RW>(key, w_d, kbound);
+        cnt = 0;
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+          sel[i] = ballot(key[i] >= kbound);
+          cnt += popc(sel[i]);
+        }
+      }
+      exchange();
     }
     // Survivors to surv[0, ns) (each wave at its offset, in any order), then 16 zeros.
     int pos = off;

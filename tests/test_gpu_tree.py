@@ -129,7 +129,7 @@ def test_four_wave_search(B, gamma, K, W, budget, tie_frac, levels):
     _compare(B, gamma, K, W, budget, seed=K * 100 + W, tie_frac=tie_frac, levels=levels)
 
 
-@pytest.mark.parametrize("K,W", [(24, 24), (64, 12), (64, 32)])
+@pytest.mark.parametrize("K,W", [(24, 24), (48, 16), (64, 32)])
 def test_tied_scores_take_no_longer(K, W):
     """A frontier of equal scores is ranked in about the time of distinct ones (every entry of
     the W best's bound was ranked against every other: 5 to 30 times the time).  The bound of
