@@ -126,26 +126,40 @@ __device__ __forceinline__ void load_full(u32x4 (&buf)[kSubGroups], __amdgpu_buf
   }
 }
 
-// Sets the groups of a tile that lie at or past V to -inf (groups never straddle V when
-// V * sizeof(T) is a multiple of 16).
-template <typename T>
+// Sets the part of a tile that lies at or past V to -inf: whole groups, or with kElems, where
+// a group may straddle V, single elements.
+template <typename T, bool kElems>
 __device__ __forceinline__ void mask_tail(u32x4 (&buf)[kSubGroups], int64_t c0, int64_t V, int lane) {
   constexpr int EPG = Traits<T>::kPer;
   const int64_t lane_e = c0 + lane * EPG;
 #pragma unroll
-  for (int g = 0; g < kSubGroups; ++g)
-    if (lane_e >= V - g * kWave * EPG) Traits<T>::set_neg_inf(buf[g]);
+  for (int g = 0; g < kSubGroups; ++g) {
+    if (!kElems) {
+      if (lane_e >= V - g * kWave * EPG) Traits<T>::set_neg_inf(buf[g]);
+    } else if (lane_e + EPG > V - g * kWave * EPG) {
+#pragma unroll
+      for (int j = 0; j < EPG; ++j)
+        if (lane_e + j >= V - g * kWave * EPG) Traits<T>::set_elem(buf[g], j, Traits<T>::kNegInf);
+    }
+  }
 }
 
 // One row as the streaming pass sees it: whole 16-byte groups from the 16-byte boundary at
 // or below the row's first element on.
-//  * kAligned: the row starts on that boundary and V * sizeof(T) is a multiple of 16.
-//  * Otherwise the row's elements are [mis, Vp) of the stretch, and the elements before and
+//  * kWholeRows: the row starts on that boundary and V * sizeof(T) is a multiple of 16.
+//  * kAnyRows: the row's elements are [mis, Vp) of the stretch, and the elements before and
 //    after them that share its first and last groups are set to -inf once loaded.  They lie
 //    in the same 16-byte granules as elements of the row, so reading them is safe.  The same
 //    16-byte loads then serve every row: 66 rows of 50,257 bf16 take 11.5 us, with one load
 //    per element 55.6 us.
-template <typename T, bool kAligned>
+//  * kRaggedRows: the row starts on that boundary and ends anywhere, V * sizeof(T) <= 2^32 - 16:
+//    one descriptor for the row, and only its last tile is masked, at the cost of some scalar
+//    registers.  The sweep of K > 16 reads every row that starts there in this mode: as
+//    kAnyRows, whose masks and descriptors it has no vector registers left for, it spills (480
+//    rows of 151,933 bf16, K = 64: 41.3 us, so 34.2).  That of K <= 16, which has them, is as
+//    fast either way.
+constexpr int kAnyRows = 0, kWholeRows = 1, kRaggedRows = 2;
+template <typename T, int kRows>
 struct RowIn {
   static constexpr int EPG = Traits<T>::kPer;
   static constexpr int64_t SUB = static_cast<int64_t>(kSubGroups) * kWave * EPG;
@@ -155,18 +169,20 @@ struct RowIn {
   __amdgpu_buffer_rsrc_t rsrc;
 
   __device__ __forceinline__ RowIn(const T* row, int64_t n) : V(n) {
-    mis = kAligned ? 0 : static_cast<int>((reinterpret_cast<uintptr_t>(row) & 15u) / sizeof(T));
+    mis = kRows != kAnyRows ? 0 : static_cast<int>((reinterpret_cast<uintptr_t>(row) & 15u) / sizeof(T));
     first = row - mis;
-    if constexpr (kAligned) rsrc = row_resource(row, static_cast<uint32_t>(V * static_cast<int64_t>(sizeof(T))));
+    const int64_t len = kRows == kRaggedRows ? (V + EPG - 1) / EPG * EPG : V;
+    if constexpr (kRows != kAnyRows)
+      rsrc = row_resource(row, static_cast<uint32_t>(len * static_cast<int64_t>(sizeof(T))));
   }
-  __device__ __forceinline__ int64_t Vp() const { return V + (kAligned ? 0 : mis); }
+  __device__ __forceinline__ int64_t Vp() const { return V + (kRows != kAnyRows ? 0 : mis); }
   __device__ __forceinline__ int64_t tiles() const { return (Vp() + SUB - 1) / SUB; }
   // First element of the tile that ends past the row (-1: none does).
   __device__ __forceinline__ int64_t last_c0() const { return Vp() % SUB != 0 ? (tiles() - 1) * SUB : -1; }
   // Loads the tile at c0 (wave-uniform).  A stretch's rounded-up length may not fit the 32 bits
   // of one descriptor, so unaligned rows take one per tile.
   __device__ __forceinline__ void load(u32x4 (&buf)[kSubGroups], int64_t c0, uint32_t lane_off) const {
-    if constexpr (kAligned) {
+    if constexpr (kRows != kAnyRows) {
       load_full<T>(buf, rsrc, c0, lane_off);
     } else {
       const int64_t rest = Vp() - c0 < SUB ? (Vp() - c0 + EPG - 1) / EPG * EPG : SUB;
@@ -176,8 +192,8 @@ struct RowIn {
   }
   // Masks the tile at c0, just loaded.
   __device__ __forceinline__ void mask(u32x4 (&buf)[kSubGroups], int64_t c0, int64_t last, int lane) const {
-    if constexpr (kAligned) {
-      if (c0 == last) mask_tail<T>(buf, c0, V, lane);
+    if constexpr (kRows != kAnyRows) {
+      if (c0 == last) mask_tail<T, kRows == kRaggedRows>(buf, c0, V, lane);
     } else {
       if (c0 != last && (c0 != 0 || mis == 0)) return;
 #pragma unroll
@@ -378,9 +394,9 @@ struct WaveState {
 // the running top K, the threshold tightened, and the rest re-filtered, until every
 // passing group is held.  Otherwise a group that does not fit sets `overflow` (exact
 // re-scan at the end).
-template <typename T, bool kAligned, bool kBig, class WL>
+template <typename T, int kRows, bool kBig, class WL>
 __device__ __forceinline__ void push_groups(const u32x4 (&buf)[kSubGroups], const float (&gmax)[kSubGroups],
-                                            uint32_t pending, int64_t c0, const RowIn<T, kAligned>& in, int K,
+                                            uint32_t pending, int64_t c0, const RowIn<T, kRows>& in, int K,
                                             int lane, WL& s, WaveState& st);
 
 // Max and exp-sum of one tile, folded into the lane's running (lm, ls): ls is the
@@ -499,8 +515,9 @@ __device__ __forceinline__ uint32_t buffer_groups(const u32x4 (&buf)[kSubGroups]
 // values): re-reads its tiles and keeps a running top-K, merging the buffer each
 // time it fills and tightening the threshold once K candidates are held (later groups
 // carry larger ids, so they must beat the K-th candidate strictly).
-template <typename T, bool kAligned, class WL>
-__device__ __forceinline__ uint2 rescan(const RowIn<T, kAligned>& in, int64_t first, int nw, uint32_t thr, int K, int lane, WL& s) {
+template <typename T, int kRows, class WL>
+__device__ __forceinline__ uint2 rescan(const RowIn<T, kRows>& in, int64_t first, int nw, uint32_t thr, int K, int lane,
+                                        WL& s) {
   constexpr int64_t SUB = static_cast<int64_t>(kSubGroups) * kWave * Traits<T>::kPer;
   const int64_t nsub = in.tiles(), last_c0 = in.last_c0();
   const uint32_t lane_off = static_cast<uint32_t>(lane * 16);
@@ -542,9 +559,9 @@ __device__ __forceinline__ uint2 rescan(const RowIn<T, kAligned>& in, int64_t fi
   return make_uint2(cur_key, cur_id);
 }
 
-template <typename T, bool kAligned, bool kBig, class WL>
+template <typename T, int kRows, bool kBig, class WL>
 __device__ __forceinline__ void push_groups(const u32x4 (&buf)[kSubGroups], const float (&gmax)[kSubGroups],
-                                            uint32_t pending, int64_t c0, const RowIn<T, kAligned>& in, int K,
+                                            uint32_t pending, int64_t c0, const RowIn<T, kRows>& in, int K,
                                             int lane, WL& s, WaveState& st) {
   pending = buffer_groups<T>(buf, pending, c0, in.mis, lane, s, st.nbuf);
   if (!ballot(pending != 0)) return;
@@ -602,8 +619,8 @@ struct RowOut {
 // wave's buffer s (with kBig, also a running top K).  lane_max (nw * 64 words of LDS)
 // receives the lane maxima of the first tiles; the threshold is agreed on after one
 // __syncthreads of the workgroup.
-template <typename T, bool kAligned, int MW, bool kBig, class WL>
-__device__ __forceinline__ void stream_row(WL& s, uint32_t* lane_max, const RowIn<T, kAligned>& in, int K, int nw,
+template <typename T, int kRows, int MW, bool kBig, class WL>
+__device__ __forceinline__ void stream_row(WL& s, uint32_t* lane_max, const RowIn<T, kRows>& in, int K, int nw,
                                            int w, int lane, WaveState& st) {
   constexpr int EPG = Traits<T>::kPer;
   constexpr int64_t SUB = static_cast<int64_t>(kSubGroups) * kWave * EPG;
@@ -666,7 +683,7 @@ __device__ __forceinline__ void stream_row(WL& s, uint32_t* lane_max, const RowI
   }
   if (sc < nfull) {
     const uint32_t p = passing_groups<T>(gmax, sc * SUB, in.Vp(), st.thr, false, lane);
-    if (ballot(p != 0)) push_groups<T, kAligned, kBig>(bufA, gmax, p, sc * SUB, in, K, lane, s, st);
+    if (ballot(p != 0)) push_groups<T, kRows, kBig>(bufA, gmax, p, sc * SUB, in, K, lane, s, st);
   }
   sc += nw;
 
@@ -675,7 +692,7 @@ __device__ __forceinline__ void stream_row(WL& s, uint32_t* lane_max, const RowI
     reduce_sub<T>(buf, gmax, st.lm, st.ls);
     if (!st.overflow && any_pass_full<T>(gmax, st.thr)) {
       const uint32_t p = passing_groups<T>(gmax, c0, in.Vp(), st.thr, st.strict, lane);
-      if (ballot(p != 0)) push_groups<T, kAligned, kBig>(buf, gmax, p, c0, in, K, lane, s, st);
+      if (ballot(p != 0)) push_groups<T, kRows, kBig>(buf, gmax, p, c0, in, K, lane, s, st);
     }
   };
   // The remaining tiles, the next one always in flight; the last tile issues no load.  Only
@@ -712,7 +729,7 @@ __device__ __forceinline__ void stream_row(WL& s, uint32_t* lane_max, const RowI
 
 // The row at rp (V elements) of global row index `row`; the workgroup has up to MW waves
 // and `lds` is its shared memory.  Writes cand_*[row * K, row * K + K) and lse[row].
-template <typename T, bool kAligned, int MW = kWaves, bool kBig = false>
+template <typename T, int kRows, int MW = kWaves, bool kBig = false>
 __device__ __forceinline__ void sweep_row(RowLdsT<MW>& lds, const T* __restrict__ rp, int64_t V, int K, int64_t row,
                                           const RowOut& out) {
   const int nw = blockDim.x / kWave;
@@ -720,11 +737,11 @@ __device__ __forceinline__ void sweep_row(RowLdsT<MW>& lds, const T* __restrict_
   // then live in scalar registers.
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int lane = threadIdx.x % kWave;
-  const RowIn<T, kAligned> in(rp, V);
+  const RowIn<T, kRows> in(rp, V);
   WaveLds& s = lds.wave[w];
   if (threadIdx.x == 0) lds.thr2 = 0;  // published by the barrier inside the pass
   WaveState st;
-  stream_row<T, kAligned, MW, kBig>(s, lds.lane_max, in, K, nw, w, lane, st);
+  stream_row<T, kRows, MW, kBig>(s, lds.lane_max, in, K, nw, w, lane, st);
 
   // This wave's live candidates (key >= the threshold) in s.cand: staged straight from
   // the buffer, or, when there are more than 64 of them or the buffer overflowed, the top
@@ -746,7 +763,7 @@ __device__ __forceinline__ void sweep_row(RowLdsT<MW>& lds, const T* __restrict_
       ck = c.x;
       ci = c.y;
     } else {
-      const uint2 c = rescan<T, kAligned>(in, w, nw, st.thr, K, lane, s);
+      const uint2 c = rescan<T, kRows>(in, w, nw, st.thr, K, lane, s);
       ck = c.x;
       ci = c.y;
     }

@@ -66,20 +66,20 @@ __device__ __forceinline__ uint32_t descend(const uint32_t* h, int need, int lan
 
 // The row at rp (V >= K elements) of global row index `row`, K <= 64.  Writes
 // cand_*[row * K, row * K + K) and lse[row].
-template <typename T, bool kAligned>
+template <typename T, int kRows>
 __device__ __forceinline__ void sweep_row_big(BigRowLds& lds, const T* __restrict__ rp, int64_t V, int K, int64_t row,
                                               const RowOut& out) {
   constexpr int EPG = Traits<T>::kPer;
   const int nw = blockDim.x / kWave;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int lane = threadIdx.x % kWave;
-  const RowIn<T, kAligned> in(rp, V);
+  const RowIn<T, kRows> in(rp, V);
   auto& s = lds.wave[w];
   for (int e = static_cast<int>(threadIdx.x); e < (kKeyPasses + kIdPasses) * 256; e += static_cast<int>(blockDim.x))
     (&lds.hist[0][0])[e] = 0u;
   if (threadIdx.x == 0) lds.nfin = 0u;  // published by the barrier inside the pass
   WaveState st;
-  stream_row<T, kAligned, kWaves, true>(s, lds.lane_max, in, K, nw, w, lane, st);
+  stream_row<T, kRows, kWaves, true>(s, lds.lane_max, in, K, nw, w, lane, st);
 
   // Candidates of this wave: the buffered elements that pass its threshold (strictly once
   // it holds a running top K: later elements carry larger ids) and, if it merged, its

@@ -13,7 +13,7 @@ namespace {
 
 // kBig: K > 16 (a tighter first threshold, a larger buffer with a running top K instead
 // of the re-scan, and the workgroup-wide selection of sweep_big.h).
-template <typename T, bool kAligned, bool kBig>
+template <typename T, int kRows, bool kBig>
 __global__ __launch_bounds__(kWave* kWaves, 4) void topk_row_kernel(const T* __restrict__ logits, int gamma,
                                                                     int64_t V, int64_t stride_b, int64_t stride_i,
                                                                     int K, int32_t* __restrict__ cand_ids,
@@ -25,10 +25,10 @@ __global__ __launch_bounds__(kWave* kWaves, 4) void topk_row_kernel(const T* __r
   const RowOut out{cand_ids, cand_logit, cand_logprob, lse, false};
   if constexpr (kBig) {
     __shared__ BigRowLds lds;
-    sweep_row_big<T, kAligned>(lds, logits + b * stride_b + i * stride_i, V, K, row, out);
+    sweep_row_big<T, kRows>(lds, logits + b * stride_b + i * stride_i, V, K, row, out);
   } else {
     __shared__ RowLds lds;
-    sweep_row<T, kAligned, kWaves, false>(lds, logits + b * stride_b + i * stride_i, V, K, row, out);
+    sweep_row<T, kRows, kWaves, false>(lds, logits + b * stride_b + i * stride_i, V, K, row, out);
   }
 }
 
@@ -54,7 +54,7 @@ __device__ __forceinline__ int64_t chunk_start(const SplitArgs& p, int c) {
   return static_cast<int64_t>(c) * p.tiles / kSplitChunks * SUB;
 }
 
-template <typename T, bool kAligned, bool kBig>
+template <typename T, int kRows, bool kBig>
 __global__ __launch_bounds__(kWave* kWaves, 4) void topk_chunk_kernel(const T* __restrict__ logits, int gamma,
                                                                       int64_t V, int64_t stride_b, int64_t stride_i,
                                                                       int K, SplitArgs p) {
@@ -68,10 +68,10 @@ __global__ __launch_bounds__(kWave* kWaves, 4) void topk_chunk_kernel(const T* _
   const RowOut out{p.ids, p.logit, nullptr, p.sum, false, p.row_max};
   if constexpr (kBig) {
     __shared__ BigRowLds lds;
-    sweep_row_big<T, kAligned>(lds, rp, len, K, rc, out);
+    sweep_row_big<T, kRows>(lds, rp, len, K, rc, out);
   } else {
     __shared__ RowLds lds;
-    sweep_row<T, kAligned, kWaves, false>(lds, rp, len, K, rc, out);
+    sweep_row<T, kRows, kWaves, false>(lds, rp, len, K, rc, out);
   }
 }
 
@@ -174,11 +174,11 @@ void launch_split(const void* logits, int B, int gamma, int64_t V, int64_t strid
   const int64_t rows = static_cast<int64_t>(B) * gamma;
   const dim3 grid(static_cast<unsigned>(rows * kSplitChunks)), block(kWave * kWaves);
   if (K > 16)
-    hipLaunchKernelGGL((topk_chunk_kernel<T, kAligned, true>), grid, block, 0, stream, static_cast<const T*>(logits),
-                       gamma, V, stride_b, stride_i, K, p);
+    hipLaunchKernelGGL((topk_chunk_kernel<T, kAligned ? kRaggedRows : kAnyRows, true>), grid, block, 0, stream,
+                       static_cast<const T*>(logits), gamma, V, stride_b, stride_i, K, p);
   else
-    hipLaunchKernelGGL((topk_chunk_kernel<T, kAligned, false>), grid, block, 0, stream, static_cast<const T*>(logits),
-                       gamma, V, stride_b, stride_i, K, p);
+    hipLaunchKernelGGL((topk_chunk_kernel<T, kAligned ? kWholeRows : kAnyRows, false>), grid, block, 0, stream,
+                       static_cast<const T*>(logits), gamma, V, stride_b, stride_i, K, p);
   const int threads = (kSplitChunks * K + kWave - 1) / kWave * kWave;
   hipLaunchKernelGGL((topk_merge_kernel<T>), dim3(static_cast<unsigned>(rows)), dim3(static_cast<unsigned>(threads)),
                      0, stream, p, K, cand_ids, cand_logit, cand_logprob, lse);
@@ -189,13 +189,13 @@ void launch_typed(const void* logits, int B, int gamma, int64_t V, int64_t strid
                   int32_t* cand_ids, float* cand_logit, float* cand_logprob, float* lse, hipStream_t stream) {
   const int64_t rows = static_cast<int64_t>(B) * gamma;
   if (K > 16)
-    hipLaunchKernelGGL((topk_row_kernel<T, kAligned, true>), dim3(static_cast<unsigned>(rows)), dim3(kWave * kWaves),
-                       0, stream, static_cast<const T*>(logits), gamma, V, stride_b, stride_i, K, cand_ids, cand_logit,
-                       cand_logprob, lse);
+    hipLaunchKernelGGL((topk_row_kernel<T, kAligned ? kRaggedRows : kAnyRows, true>), dim3(static_cast<unsigned>(rows)),
+                       dim3(kWave * kWaves), 0, stream, static_cast<const T*>(logits), gamma, V, stride_b, stride_i, K,
+                       cand_ids, cand_logit, cand_logprob, lse);
   else
-    hipLaunchKernelGGL((topk_row_kernel<T, kAligned, false>), dim3(static_cast<unsigned>(rows)), dim3(kWave * kWaves),
-                       0, stream, static_cast<const T*>(logits), gamma, V, stride_b, stride_i, K, cand_ids, cand_logit,
-                       cand_logprob, lse);
+    hipLaunchKernelGGL((topk_row_kernel<T, kAligned ? kWholeRows : kAnyRows, false>), dim3(static_cast<unsigned>(rows)),
+                       dim3(kWave * kWaves), 0, stream, static_cast<const T*>(logits), gamma, V, stride_b, stride_i, K,
+                       cand_ids, cand_logit, cand_logprob, lse);
 }
 
 }  // namespace
@@ -207,8 +207,11 @@ size_t topk_workspace_bytes(int B, int gamma, int64_t V, int K, int dtype) {
 hipError_t launch_topk(const void* logits, int dtype, bool aligned, int B, int gamma, int64_t V, int64_t stride_b,
                        int64_t stride_i, int K, int32_t* cand_ids, float* cand_logit, float* cand_logprob, float* lse,
                        void* workspace, size_t ws_bytes, hipStream_t stream) {
-  // Rows of whole 16-byte groups need no masks at their ends (RowIn).
-  aligned = aligned && (V * (dtype == 1 ? 2 : 4)) % 16 == 0;
+  // Rows that start on 16 bytes need no mask at their start, and those of whole 16-byte groups none
+  // inside a group either (RowIn); past K = 16 the kernel masks the end of any row, up to the
+  // longest whose 16-byte groups one descriptor can state.
+  const int64_t bytes = V * (dtype == 1 ? 2 : 4);
+  aligned = aligned && (K > 16 ? bytes <= (int64_t(1) << 32) - 16 : bytes % 16 == 0);
   if (workspace) {
     const SplitPlan sp = split_plan(static_cast<int64_t>(B) * gamma, V, K, dtype);
     if (sp.tiles != 0 && ws_bytes >= sp.total) {

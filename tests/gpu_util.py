@@ -51,3 +51,20 @@ def run_pipeline(w: synth.Workload, d: dict, W: int | None = None, debug: bool =
     out = step.run(logits)
     torch.cuda.synchronize()
     return to_np(out)
+
+
+def best_us(fn, calls: int = 20, reps: int = 7) -> float:
+    """The shortest mean time of `calls` calls of fn in microseconds."""
+    import torch
+
+    best = float("inf")
+    fn()
+    for _ in range(reps):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(calls):
+            fn()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / calls)
+    return best

@@ -288,3 +288,48 @@ def test_cut_rows_take_no_longer(V):
     whole_us, cut_us = us(none), us(cut)
     print(f"V={V}: whole {whole_us:.1f} us, cut {cut_us:.1f} us", flush=True)
     assert cut_us < whole_us
+
+
+@pytest.mark.parametrize("dt,per", [("bf16", 8), ("f32", 4)])
+@pytest.mark.parametrize("cut", [False, True])
+def test_aligned_rows_of_any_length_past_k16(dt, per, cut):
+    """K > 16, rows on 16-byte boundaries that end 0 .. per - 1 elements into a group, around the ends
+    of a tile and of eight tiles (and, cut, past the length from which rows are cut), with much larger
+    values behind the row's end: none of those leaks in."""
+    import torch
+
+    import paper_2609_39972_amd as ubt
+    from gpu_util import say, dev_values, to_np
+
+    tile = 256 * per
+    rng = np.random.default_rng(per + 100 * cut)
+    for base in ((tile * 96,) if cut else (64, tile, 8 * tile, 9 * tile + 40)):
+        for rest in range(per):
+            V = base + rest + (per if cut else 0)
+            say(f"topk V={V} dtype={dt} cut={cut}")
+            x = np.full((1, 2, base + 4 * per), 1e30)
+            rows = rng.normal(0, 2.5, (1, 2, V))
+            rows[0, 1, :-1] = -np.inf  # the last element alone
+            x[:, :, :V] = rows
+            t = dev_values(synth.store(x, dt))[:, :, :V]
+            ws = ubt.topk_workspace(1, 2, V, 33, t.dtype) if cut else None
+            assert not cut or ws is not None
+            out = ubt.topk(t, 33, workspace=ws)
+            torch.cuda.synchronize()
+            parity.check_topk(to_np(out), oracle.topk(synth.store(rows, dt), 33))
+
+
+def test_ragged_rows_take_no_longer_than_whole_groups():
+    """480 rows of 151,933 bf16 on 16-byte boundaries, K = 64, against 151,936: read as rows that may
+    start anywhere they took 41.3 us against 35.5, with a mask of the last tile alone 34.2."""
+    import torch
+
+    import paper_2609_39972_amd as ubt
+    from gpu_util import best_us
+
+    x = torch.randn(480, 1, 151936, device="cuda").bfloat16()
+    out = ubt.topk(x, 64)
+    whole = best_us(lambda: ubt.topk(x, 64, out))
+    ragged = best_us(lambda: ubt.topk(x[:, :, :151933], 64, out))
+    print(f"whole groups {whole:.1f} us, ragged {ragged:.1f} us", flush=True)
+    assert ragged < 1.1 * whole
