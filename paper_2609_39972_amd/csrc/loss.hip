@@ -42,25 +42,29 @@ __device__ __forceinline__ float logit_at<uint16_t>(const uint16_t* p, int64_t i
 __device__ __forceinline__ bool valid_token(int32_t y, int64_t V) { return y >= 0 && y < V; }
 
 // grad[row][v] = beta * exp(u[row][v] - lse[row]) for valid rows, 0 for invalid ones.
-// Grid: B * gamma rows x chunks of kDenseThreads * 8 * kDenseUnroll elements, the chunks of a
-// row next to each other: workgroups that run together then stream neighbouring memory (480
-// rows of 151,936 bf16: 89 us, 4.9 TB/s, the rate of a large copy; with the rows next to
-// each other 93-96 us; nontemporal loads and stores 104-115 us).
+// Grid: B * gamma rows x chunks of kDenseThreads * 8 * kDenseUnroll elements, in one of two orders.
+// Workgroup i takes (row, chunk) = (i / per, i % per) with by_row, the chunks of a row next to each
+// other: workgroups that run together then stream neighbouring memory (480 rows of 151,936 bf16:
+// 89 us, 4.9 TB/s, the rate of a large copy; with the rows next to each other 93-96 us; nontemporal
+// loads and stores 104-115 us).  The chunk then moves on by one every eight rows, so that a row's
+// short last chunk is not always with the same XCDs (1,984 rows of 24,584 bf16 81 us, so 70).
+// Otherwise (i % per, i / per), the rows next to each other: see the launch.
 template <typename T, bool kVec>
-__global__ __launch_bounds__(kDenseThreads) void kl_dense_kernel(const T* __restrict__ logits, int gamma, int chunks,
-                                                                 int64_t V,
+__global__ __launch_bounds__(kDenseThreads) void kl_dense_kernel(const T* __restrict__ logits, int gamma, uint32_t per,
+                                                                 bool by_row, int64_t V,
                                                                  int64_t stride_b, int64_t stride_i,
                                                                  const float* __restrict__ lse,
                                                                  const int32_t* __restrict__ y_star, float beta,
                                                                  float* __restrict__ grad) {
-  const int64_t row = blockIdx.x / chunks;
+  const uint32_t hi = blockIdx.x / per, lo = blockIdx.x - hi * per;
+  const int64_t row = by_row ? hi : lo;
   const int64_t b = row / gamma, i = row - b * gamma;
   const T* u = logits + b * stride_b + i * stride_i;
   float* g = grad + row * V;
   const bool valid = valid_token(y_star[row], V);
   const float shift = valid ? lse[row] * kLog2e : 0.f;
   constexpr int64_t kChunk = static_cast<int64_t>(kDenseThreads) * 8 * kDenseUnroll;
-  const int64_t c0 = (blockIdx.x - row * chunks) * kChunk;
+  const int64_t c0 = (by_row ? (lo + hi / 8) % per : hi) * kChunk;
   if (kVec) {
     // Whole 8-element groups (V % 8 == 0 and 16-byte aligned rows).
     float x[kDenseUnroll][8];
@@ -239,13 +243,21 @@ void launch_typed(const LossArgs& p, int rows, bool vec, hipStream_t stream) {
     constexpr int64_t kChunk = static_cast<int64_t>(kDenseThreads) * 8 * kDenseUnroll;
     const int chunks = static_cast<int>((p.V + kChunk - 1) / kChunk);
     const dim3 grid(static_cast<unsigned>(rows) * static_cast<unsigned>(chunks));
+    // The chunks of a row next to each other (kl_dense_kernel) pay where the pass is larger than the
+    // 256 MB last-level cache (1,984 rows of 32,000 bf16: the objective takes 89 us, in the other
+    // order 95).  A smaller pass loses: 480 rows of 24,584 fp32 22.8 us, in the other order 21.7.  So
+    // do rows of two or three chunks (1,984 rows of 8,200 bf16 32 us, 25), and rows read element by
+    // element (1,984 of 50,257 fp32 202 us, 194).
+    const int64_t moved = static_cast<int64_t>(rows) * p.V * static_cast<int64_t>(sizeof(T) + sizeof(float));
+    const bool by_row = vec && chunks > 3 && moved > (int64_t(256) << 20);
+    const uint32_t per = static_cast<uint32_t>(by_row ? chunks : rows);
     const T* u = static_cast<const T*>(p.logits);
     if (vec)
-      hipLaunchKernelGGL((kl_dense_kernel<T, true>), grid, dim3(kDenseThreads), 0, stream, u, p.gamma, chunks, p.V,
-                         p.stride_b, p.stride_i, p.lse, p.y_star, p.beta, p.grad);
+      hipLaunchKernelGGL((kl_dense_kernel<T, true>), grid, dim3(kDenseThreads), 0, stream, u, p.gamma, per, by_row,
+                         p.V, p.stride_b, p.stride_i, p.lse, p.y_star, p.beta, p.grad);
     else
-      hipLaunchKernelGGL((kl_dense_kernel<T, false>), grid, dim3(kDenseThreads), 0, stream, u, p.gamma, chunks, p.V,
-                         p.stride_b, p.stride_i, p.lse, p.y_star, p.beta, p.grad);
+      hipLaunchKernelGGL((kl_dense_kernel<T, false>), grid, dim3(kDenseThreads), 0, stream, u, p.gamma, per, by_row,
+                         p.V, p.stride_b, p.stride_i, p.lse, p.y_star, p.beta, p.grad);
   }
   hipLaunchKernelGGL((kl_position_kernel<T, F>), dim3(static_cast<unsigned>(rows)), dim3(kWave), 0, stream, p);
 }

@@ -108,3 +108,70 @@ def test_loss_headline_workload(T):
     d = synth.inputs(w, 0)
     li = synth.loss_inputs(w, 0)
     _check(w, d, li, T, 0.1, grad_rows=[0, 17, 233, 479])
+
+
+@pytest.mark.parametrize("rows,V,dt", [
+    # one to five chunks of 8,192 elements per row in a pass that the last-level cache holds, rows read
+    # element by element, and passes past the cache, whose workgroups run row by row
+    (3, 40, "bfloat16"), (5, 8192, "float32"), (5, 8200, "bfloat16"), (7, 16392, "float32"), (9, 33000, "bfloat16"),
+    (4, 24581, "bfloat16"), (1830, 24584, "bfloat16"), (1031, 32776, "float32"),
+])
+def test_dense_gradient_at_the_ends_of_chunks(rows, V, dt):
+    """beta exp(u - lse) at every element but the candidates', on the device against float64; invalid
+    rows are zero throughout."""
+    import torch
+
+    import paper_2609_39972_amd as ubt
+
+    print(f"dense gradient rows={rows} V={V} {dt}", flush=True)
+    torch.manual_seed(V)
+    u = (torch.randn(rows, 1, V, device="cuda") * 2).to(getattr(torch, dt))
+    cand = ubt.topk(u, 4)
+    f = torch.zeros(V, 16, device="cuda", dtype=torch.bfloat16)
+    gate = torch.zeros(rows, 1, 16, device="cuda", dtype=torch.bfloat16)
+    y = torch.randint(0, V, (rows, 1), device="cuda", dtype=torch.int32)
+    y[rows // 2] = -1
+    out = ubt.tree_kl_loss(u, cand, u, y, torch.zeros(rows, dtype=torch.int32, device="cuda"), f, f, gate, [1.0], [1.0],
+                           beta=0.1)
+    g = out["grad_logits"]
+    for r in range(0, rows, max(1, rows // 64)):
+        ref = 0.1 * torch.exp(u[r, 0].double() - torch.logsumexp(u[r, 0].double(), 0))
+        if y[r, 0] < 0:
+            ref.zero_()
+        skip = torch.cat([cand["cand_ids"][r, 0].long(), y[r].long().clamp(min=0)])
+        err = (g[r, 0].double() - ref).abs() - 1e-5 * ref - 1e-9
+        err[skip] = -1.0
+        assert float(err.max()) <= 0, (r, float(err.max()))
+
+
+def test_short_second_chunk_takes_little():
+    """1,984 rows of 8,200 bf16 against 8,192: the second chunk holds eight elements.  With the chunks
+    of a row next to each other every whole chunk fell on an XCD of even index: 32.3 us against 25.0;
+    with the rows next to each other 25.0 both."""
+    import torch
+
+    import paper_2609_39972_amd as ubt
+    from gpu_util import best_us
+
+    def us(V):
+        u = torch.randn(64, 31, V, device="cuda").bfloat16()
+        cand = ubt.topk(u, 8)
+        f = torch.zeros(V, 32, device="cuda", dtype=torch.bfloat16)
+        gate = torch.zeros(64, 31, 32, device="cuda", dtype=torch.bfloat16)
+        y = torch.zeros(64, 31, device="cuda", dtype=torch.int32)
+        an = torch.zeros(64, device="cuda", dtype=torch.int32)
+        one = [1.0] * 31
+        out = ubt.tree_kl_loss(u, cand, u, y, an, f, f, gate, one, one)
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            ubt.tree_kl_loss(u, cand, u, y, an, f, f, gate, one, one, out=out)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            for _ in range(10):
+                ubt.tree_kl_loss(u, cand, u, y, an, f, f, gate, one, one, out=out)
+        return best_us(graph.replay, calls=2) / 10
+
+    short, long = us(8192), us(8200)
+    print(f"8,192: {short:.1f} us, 8,200: {long:.1f} us", flush=True)
+    assert long < 1.15 * short
