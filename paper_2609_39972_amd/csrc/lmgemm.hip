@@ -368,7 +368,11 @@ __device__ __forceinline__ void sel_digit(const uint32_t* hist, uint32_t* misc, 
 //    the threads in order.
 //  * The bound: about the K-th largest of 256 maxima over the groups of a thread pair, by
 //    the ballot radix search.  At least K groups have a maximum at or above it, so the
-//    row's top K elements do; it lets about K + K / 8 + K^2 / 512 groups through.
+//    row's top K elements do; it lets about K + K / 8 + K^2 / 512 groups through.  Where fewer
+//    than K thread pairs hold a group (K = 64: up to 8,192 columns), or past K = 16 so few
+//    that the bound is the least of them, the pairs' maxima over the elements they read give a
+//    second one: without a bound every element was ranked or selected (d = 2880, 17 rows of
+//    1,500 columns: 91.9 us, so 37.4; 480 rows of 4,000: 82.2, so 51.3).
 //  * The elements at or above the bound lie in the groups whose maximum is; they are read,
 //    collected and ranked by counting.
 //  * More than kSelMax of them (long runs of equal logits) take an 8-bit radix selection
@@ -413,16 +417,23 @@ __global__ __launch_bounds__(kSelThreads) void lm_select_kernel(SelectArgs a) {
     if (p[q].x != neg_inf()) se += p[q].y * __builtin_amdgcn_exp2f((p[q].x - mx) * kLog2e);
   se = wave_sum(se);
   if (lane == 0) red[kSelWaves + w] = se;
-  // The bound, found by every wave for itself; none when fewer than K pairs hold a group.
-  uint32_t bound;
-  {
+  // The K-th largest (about) of the entries of `best`, found by every wave for itself; 1 with fewer
+  // than K of them.  few: that bound is poor or none.
+  bool few;
+  auto kth_best = [&]() {
     const uint4 o = reinterpret_cast<const uint4*>(best)[lane];
     const uint32_t key[4] = {o.x, o.y, o.z, o.w};
     uint64_t live[4];
+    int have = 0;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) live[r] = ballot(key[r] != 0u);
-    bound = max(wave_threshold<4>(key, live, K, K + K / 8), 1u);  // key 0: no column
-  }
+    for (int r = 0; r < 4; ++r) {
+      live[r] = ballot(key[r] != 0u);
+      have += popc(live[r]);
+    }
+    few = have < (K > 16 ? K + K / 8 + 1 : K);
+    return max(wave_threshold<4>(key, live, K, K + K / 8), 1u);  // key 0: no column
+  };
+  uint32_t bound = kth_best();
   __syncthreads();
   float tot = red[kSelWaves];
 #pragma unroll
@@ -461,6 +472,14 @@ __global__ __launch_bounds__(kSelThreads) void lm_select_kernel(SelectArgs a) {
       }
     }
   };
+  if (few) {
+    uint32_t top = 0u;
+    visit([&](uint64_t o) { top = max(top, static_cast<uint32_t>(o >> 32)); });
+    top = max(top, static_cast<uint32_t>(__shfl_xor(static_cast<int>(top), 1)));
+    if (!(tid & 1)) best[tid >> 1] = top;
+    __syncthreads();
+    bound = max(bound, kth_best());
+  }
   visit([&](uint64_t o) {
     const uint32_t at = atomicAdd(&misc[3], 1u);
     if (at < kSelMax) cand[at] = o;

@@ -207,3 +207,45 @@ def test_lm_head_row_groups_integer_inputs_exact(M, d, V, K):
     assert ws.numel() < min(M, 512) * V * 4  # no room for the logits
     ws.fill_(0x7F)
     parity.check_lm_head(_run(hb, wb, K, workspace=ws), hb, wb, K, exact=True)
+
+
+@pytest.mark.parametrize("M,d,V,K", [
+    # fewer than K thread pairs of the select kernel hold a group of 64 columns, in one range or in
+    # many: fewer columns than threads, one column per thread, the last such length and the first past it
+    (5, 96, 64, 64), (5, 96, 300, 64), (17, 96, 500, 33), (17, 64, 1500, 64), (200, 64, 1500, 64), (200, 96, 4097, 64),
+    (480, 32, 8128, 64), (480, 32, 8257, 64), (300, 64, 5000, 64), (480, 64, 1000, 17),
+    # the product where both it and the row groups take d
+    (160, 1024, 2800, 64),
+])
+def test_lm_head_product_few_columns_exact(M, d, V, K):
+    """Exact logits, with every logit of some rows tied (the lowest ids win)."""
+    import paper_2609_39972_amd as ubt
+
+    print(f"lm_head product few columns M={M} d={d} V={V} K={K}", flush=True)
+    hb, wb = _int_bits(M, d, V, seed=M + d + V, lo=-3, hi=3)
+    hb[::5] = 0
+    ws = ubt.lm_head_workspace(M, d, V, K)
+    ws.fill_(0x7F)
+    parity.check_lm_head(_run(hb, wb, K, workspace=ws), hb, wb, K, exact=True)
+
+
+@pytest.mark.parametrize("M,V", [(17, 1500), (480, 4000)])
+def test_lm_head_few_columns_take_little_longer_at_large_k(M, V):
+    """K = 64 against K = 8, d = 2880, where K = 64 thread pairs do not each hold a group: without a
+    bound the select kernel ranked or selected among every element (17 x 1,500: 91.9 us against 28.4;
+    480 x 4,000: 82.2 against 45.5; with one 37.4 and 51.3)."""
+    import torch
+
+    import paper_2609_39972_amd as ubt
+    from gpu_util import best_us
+
+    h, w = torch.randn(M, 2880, device="cuda").bfloat16(), torch.randn(V, 2880, device="cuda").bfloat16()
+
+    def us(K):
+        ws = ubt.lm_head_workspace(M, 2880, V, K)
+        out = ubt.lm_head_topk(h, w, K, workspace=ws)
+        return best_us(lambda: ubt.lm_head_topk(h, w, K, out=out, workspace=ws))
+
+    few, many = us(8), us(64)
+    print(f"M={M} V={V}: K = 8 {few:.1f} us, K = 64 {many:.1f} us", flush=True)
+    assert many < 1.6 * few
