@@ -144,7 +144,8 @@ ubt_status_t ubt_topk_split(const void* logits, ubt_dtype_t dt, int B, int gamma
  * ubt_lm_head_topk_full_workspace_bytes(M, d, V, K) bytes (room for the fp32 logits of up to
  * 512 rows, about 4 * min(M, 512) * V bytes; never less than the plain query) the projection
  * is one matrix product that writes the logits there; with less, the head is read once per
- * 16 rows of h.  Inputs must be finite; non-finite logits give unspecified
+ * 16 rows of h.  For such d = 512 n and a head of few columns (for their M) the second is the
+ * faster one: the two queries are then equal.  Inputs must be finite; non-finite logits give unspecified
  * candidates.  Returns UBT_ERR_WORKSPACE for a missing, small or
  * misaligned workspace, UBT_ERR_UNSUPPORTED for shapes the workspace query rejects
  * (it returns 0 for them: very large V at large K).

@@ -219,7 +219,8 @@ def lm_head_workspace(M: int, d: int, V: int, K: int, device="cuda", full: bool 
     never read before they are written, so it serves calls of any shape in turn).
 
     Calls that run as a matrix product (more than 16 rows, or a d that the kernel for 16 rows
-    does not take) keep the logits of up to 512 rows in it: about 4 min(M, 512) V bytes.
+    does not take; not the few columns at which reading the head once per 16 rows is the faster)
+    keep the logits of up to 512 rows in it: about 4 min(M, 512) V bytes.
     ``full=False`` leaves that room out (a few MB): such calls then read the head once per 16
     rows of h."""
     size = lib().ubt_lm_head_topk_full_workspace_bytes if full else lib().ubt_lm_head_topk_workspace_bytes

@@ -573,7 +573,22 @@ size_t lm_gemm_workspace_bytes(int M, int d, int64_t V, int K) {
   // Up to 16 rows fit one tile of the row-group kernels, which read the head once: the one that
   // splits d (512 n, n in {2, .., 8, 10}) streams it as fast (15 rows, d = 2560: 132 us), the other
   // one at less than half the rate (15 rows, d = 2880: 317 us, here 156).
-  if ((M <= 16 && lm_head_split_fits(d)) || V > (int64_t(1) << 24)) return 0;
+  // Past 16 rows the row groups read the head once each, at a cost in groups * V, while the product's
+  // grid is too small below some 10,000 columns to get faster with V.  Where the two meet, in groups * V,
+  // K = 8, d = 1024 .. 3072 (us, row groups and product on either side, at d = 2560): two groups
+  // 20,000 (V = 8,000: 22.4, 26.8; 14,000: 31.9, 26.8); three 15,000 (4,000: 26.2, 28.4; 6,000: 28.7,
+  // 28.8); four 10,000 (1,500: 21.3, 28.3; 4,000: 32.8, 28.5); 8 to 30 15,000 .. 22,000 (30 groups,
+  // 300: 27.8, 40.8; 1,000: 54.6, 42.2).  A larger K costs the product's selection 1.5 to 2 times
+  // as much there (two groups, K = 64, 10,000: 25.8, 30.9; 14,000: 31.3, 30.6); past d = 3072 the row
+  // groups hold fewer waves (d = 4096, 8 groups: 1,500: 44.4, 50.2; 2,500: 68.1, 51.0).
+  if (lm_head_split_fits(d)) {
+    const int64_t groups = (M + 15) / 16;
+    int64_t line = groups == 2 ? 20480 : groups == 3 ? 15360 : groups == 4 ? 10240 : 18432;
+    if (K > 16) line += line / 2;
+    if (d > 3072) line -= line / 4;
+    if (groups == 1 || groups * V < line) return 0;
+  }
+  if (V > (int64_t(1) << 24)) return 0;
   const GemmPlan p = gm_plan(M < kGmMaxRows ? M : kGmMaxRows, V, gm_grid());
   // The last rows of a longer call: fewer row blocks cut V into more ranges, so at a small V their
   // statistics may take more room than those of 512 rows.

@@ -303,6 +303,22 @@ def test_lm_head_full_workspace_bytes():
     assert full(40, 2560, 2 ** 31 - 1, 64) == 0
 
 
+@pytest.mark.parametrize("d,M,below,above", [
+    (2560, 17, 8000, 12000), (2560, 40, 4000, 6000), (2560, 64, 2000, 4000), (2560, 256, 1000, 1500),
+    (2560, 480, 600, 800), (4096, 17, 6000, 8000), (4096, 256, 800, 1000),
+])
+def test_lm_head_few_columns_stay_with_the_row_groups(d, M, below, above):
+    """Where the kernel for 16 rows takes d, a head of few columns has no larger workspace to ask for:
+    the row groups are faster than the product there (d = 2560, 17 rows of 5,000 columns: 20 us
+    against 26).  K = 1, so that the candidates' room does not hide the logits'."""
+    L = ubt.lib()
+    plain, full = L.ubt_lm_head_topk_workspace_bytes, L.ubt_lm_head_topk_full_workspace_bytes
+    assert full(M, d, below, 1) == plain(M, d, below, 1) < M * below * 4
+    assert full(M, d, above, 1) >= M * above * 4 > plain(M, d, above, 1)
+    assert full(M, d + 32, below, 1) >= M * below * 4  # a d that only the product streams well
+
+
+
 def test_tree_attention_workspace_bytes():
     """Partial outputs (D floats) and (max, sum) per query row and part when few workgroups
     would run, nothing when they fill the chip or the context is short; 0 for bad shapes."""
